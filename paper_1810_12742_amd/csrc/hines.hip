@@ -19,9 +19,10 @@
 //    store their contribution in their own slot and the parent pulls them in
 //    a fixed order (used for re-rooted plans, bitwise mode and workspace
 //    groups);
-//  * groups are bucketed by LDS footprint, one launch per bucket, so the
-//    occupancy follows the footprint; inside a launch the groups with the
-//    longest critical path come first.
+//  * flow groups of different LDS footprints share one workgroup, one wave
+//    each (bins, packed by the setup), so that a solve is one or two launches;
+//    the other groups are bucketed by LDS footprint, one launch per bucket.
+//    Inside a launch the groups with the longest critical path come first.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -118,9 +119,10 @@ struct hines_plan {
   DevTables t{};
   struct Bucket {
     int32_t lds_bytes, first, count, global;
-    int32_t level;  // 1: level-synchronous kernel for an LDS group of a flow plan
+    int32_t level;  // resident launches: the LDS class
   };
-  std::vector<Bucket> buckets;
+  std::vector<Bucket> buckets;        // level-synchronous groups, by LDS footprint
+  std::vector<hines::FlowLaunch> flow_launches;  // flow groups, in bins
   std::vector<Bucket> mixed_buckets;  // FP32+refinement kernel (its own LDS layout)
   std::vector<Bucket> res_buckets;    // LDS-resident kernel, by LDS class
   // LDS classes launch concurrently: bucket i runs on res_lane[i] (0: the
@@ -210,22 +212,35 @@ void launch_bucket(const hines_plan* p, const hines_plan::Bucket& bk, const RhsS
                    const double* u, double* x, hipStream_t s) {
   DevTables t = p->t;
   t.glist = p->t.glist + bk.first;
-  if (p->host.flow && !bk.global && !bk.level) {
-    if (rs.mode == hdev::kRhsGiven)
-      hipLaunchKernelGGL(hdev::k_solve_flow<hdev::kFlowGiven>, dim3(bk.count), dim3(64), bk.lds_bytes, s, t, rs, d, u, x);
-    else if (rs.mode == hdev::kRhsNoise)
-      hipLaunchKernelGGL(hdev::k_solve_flow<hdev::kFlowNoise>, dim3(bk.count), dim3(64), bk.lds_bytes, s, t, rs, d, u, x);
-    else if (rs.icur)
-      hipLaunchKernelGGL(hdev::k_solve_flow<hdev::kFlowCVI>, dim3(bk.count), dim3(64), bk.lds_bytes, s, t, rs, d, u, x);
-    else
-      hipLaunchKernelGGL(hdev::k_solve_flow<hdev::kFlowCV>, dim3(bk.count), dim3(64), bk.lds_bytes, s, t, rs, d, u, x);
-  } else if (p->host.opt.bitwise) {
+  if (p->host.opt.bitwise) {
     launch_level<T, hdev::kModeBitwise>(t, bk, rs, d, u, x, s);
   } else if (p->host.all_ascending) {
     launch_level<T, hdev::kModeAscending>(t, bk, rs, d, u, x, s);
   } else {
     launch_level<T, hdev::kModeFast>(t, bk, rs, d, u, x, s);
   }
+}
+
+template <typename MT>
+hipError_t launch_flow(const hines_plan* p, const RhsSpec& rs, const MT* d, const MT* u, double* x, hipStream_t s) {
+  for (const hines::FlowLaunch& L : p->flow_launches) {
+    DevTables t = p->t;
+    t.fjob = p->t.fjob + L.first;
+    const dim3 grid((unsigned)L.bins), block((unsigned)(64 * L.width));
+    if (rs.mode == hdev::kRhsGiven)
+      hipLaunchKernelGGL((hdev::k_solve_flow<hdev::kFlowGiven, MT>), grid, block, L.lds_bytes, s, t, rs, d, u, x);
+    else if constexpr (sizeof(MT) == 8) {
+      if (rs.mode == hdev::kRhsNoise)
+        hipLaunchKernelGGL((hdev::k_solve_flow<hdev::kFlowNoise, MT>), grid, block, L.lds_bytes, s, t, rs, d, u, x);
+      else if (rs.icur)
+        hipLaunchKernelGGL((hdev::k_solve_flow<hdev::kFlowCVI, MT>), grid, block, L.lds_bytes, s, t, rs, d, u, x);
+      else
+        hipLaunchKernelGGL((hdev::k_solve_flow<hdev::kFlowCV, MT>), grid, block, L.lds_bytes, s, t, rs, d, u, x);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // one instantiation of the resident kernel per LDS class (plane stride S)
@@ -316,6 +331,8 @@ hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d,
       hipLaunchKernelGGL(hdev::k_solve_cells<hdev::kFlowCV>, grid, dim3(64), 0, s, p->t, rs, d, u, x);
     return hipGetLastError();
   }
+  hipError_t ef = launch_flow(p, rs, d, u, x, s);
+  if (ef != hipSuccess) return ef;
   for (const auto& bk : p->buckets) {
     if (bk.count == 0) continue;
     switch (p->host.opt.group_width) {
@@ -364,10 +381,10 @@ hipError_t allow_lds_t() {
 }
 
 hipError_t allow_lds(int T) {
-  const void* fns[] = {(const void*)hdev::k_solve_flow<hdev::kFlowGiven>,
-                       (const void*)hdev::k_solve_flow<hdev::kFlowCV>,
-                       (const void*)hdev::k_solve_flow<hdev::kFlowCVI>,
-                       (const void*)hdev::k_solve_flow<hdev::kFlowNoise>,
+  const void* fns[] = {(const void*)hdev::k_solve_flow<hdev::kFlowGiven, double>,
+                       (const void*)hdev::k_solve_flow<hdev::kFlowCV, double>,
+                       (const void*)hdev::k_solve_flow<hdev::kFlowCVI, double>,
+                       (const void*)hdev::k_solve_flow<hdev::kFlowNoise, double>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeFast, true>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeBitwise, true>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeAscending, true>};
@@ -471,7 +488,7 @@ bool check_kernel_tables(const hines::HostPlan& P, std::string& why, bool& capac
       if (G.ws_off >= 0) continue;
       if (W.nstep == 0 && W.nelem == 0 && W.naux == 0) continue;  // level kernel in LDS
       if (W.nstep < 1 || W.nstep > hines::kMaxSteps || W.nelem != G.user_n || W.naux < 0 || W.nent < W.nelem ||
-          hines::flow_image8(W) > 32767 || W.nent % hines::kFlowChunk || W.step_off < 0 || 2 * (W.step_off + W.nstep) > (int64_t)P.fmask.size() ||
+          hines::flow_image8(W.nent) > 32767 || W.nent % hines::kFlowChunk || W.step_off < 0 || 2 * (W.step_off + W.nstep) > (int64_t)P.fmask.size() ||
           W.pos_off < 0 || W.pos_off + W.nelem > (int64_t)P.fpos.size() || W.aux_off < 0 || (W.aux_off & 1) ||
           W.aux_off + W.naux + 1 > (int64_t)P.faux.size() + 1 || hines::flow_lds_bytes(W) > hines::kLdsLimitBytes) {
         why = "flow group record";
@@ -824,37 +841,49 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
     }
   }
   const hines::HostPlan& P = p->host;
-  // buckets by LDS footprint and kernel: flow groups, level-synchronous LDS
-  // groups (plans without a flow schedule, or groups whose schedule does not
-  // fit LDS), and groups whose image lives in the workspace
+  // flow groups go in bins; the others (plans without a flow schedule, groups
+  // whose schedule does not fit LDS, and groups whose image lives in the
+  // workspace) in buckets by LDS footprint
+  std::vector<hines::KFlowJob> fjobs;
+  try {
+    hines::pack_flow_bins(P, p->flow_launches, fjobs);
+    if (!o.host_only && !hines::check_flow_bins(P, p->flow_launches, fjobs, why)) {
+      delete p;
+      return set_err(HINES_ERR_STATE, "flow bins: %s", why.c_str());
+    }
+  } catch (const std::bad_alloc&) {
+    delete p;
+    return set_err(HINES_ERR_OOM, "host memory exhausted while building the plan tables");
+  }
   const int nbk = (int)(sizeof kBuckets / sizeof kBuckets[0]);
-  std::vector<std::vector<int32_t>> members(2 * nbk + 1);
+  std::vector<std::vector<int32_t>> members(nbk + 1);
   int64_t global_lds = 0;
   for (int64_t g = 0; g < P.ngroups; ++g) {
     const KGroup& G = P.kgroup[g];
+    if (P.flow && G.ws_off < 0 && P.kflow[g].nstep > 0) {
+      p->max_lds = std::max(p->max_lds, hines::flow_lds_bytes(P.kflow[g]));
+      continue;
+    }
+    const int64_t bytes = layout_of(G).bytes();
+    p->max_lds = std::max(p->max_lds, bytes);
     if (G.ws_off >= 0) {
-      const int64_t bytes = layout_of(G).bytes();
-      p->max_lds = std::max(p->max_lds, bytes);
-      members[2 * nbk].push_back((int32_t)g);
+      members[nbk].push_back((int32_t)g);
       global_lds = std::max(global_lds, bytes);
       continue;
     }
-    const bool fl = P.flow && P.kflow[g].nstep > 0;
-    const int64_t bytes = fl ? hines::flow_lds_bytes(P.kflow[g]) : layout_of(G).bytes();
-    p->max_lds = std::max(p->max_lds, bytes);
     int k = 0;
     while (k < nbk && kBuckets[k] < bytes) ++k;
     if (k == nbk) k = nbk - 1;  // host_only plans only; checked above otherwise
-    members[(fl ? 0 : nbk) + k].push_back((int32_t)g);
+    members[k].push_back((int32_t)g);
   }
   std::vector<int32_t> glist;
-  for (int k = 0; k <= 2 * nbk; ++k) {
+  for (int k = 0; k <= nbk; ++k) {
     auto& m = members[k];
     if (m.empty()) continue;
     std::stable_sort(m.begin(), m.end(), [&](int32_t a, int32_t b) { return P.kgroup[a].cost > P.kgroup[b].cost; });
-    const bool glob = k == 2 * nbk;
-    const int32_t lds = glob ? (int32_t)((global_lds + 255) & ~(int64_t)255) : kBuckets[k % nbk];
-    p->buckets.push_back({lds, (int32_t)glist.size(), (int32_t)m.size(), glob ? 1 : 0, (!glob && k >= nbk) ? 1 : 0});
+    const bool glob = k == nbk;
+    const int32_t lds = glob ? (int32_t)((global_lds + 255) & ~(int64_t)255) : kBuckets[k];
+    p->buckets.push_back({lds, (int32_t)glist.size(), (int32_t)m.size(), glob ? 1 : 0, 0});
     glist.insert(glist.end(), m.begin(), m.end());
   }
   // buckets of the FP32+refinement kernel (its LDS image holds 32 bytes per slot)
@@ -925,7 +954,7 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   const int64_t sz_cell = al((int64_t)P.kcell.size() * sizeof(KCell));
   const int64_t sz_gl = al((int64_t)glist.size() * sizeof(int32_t));
   const int64_t sz_ws = al(P.ws_doubles * (int64_t)sizeof(double));
-  const int64_t sz_fl = al((int64_t)P.kflow.size() * sizeof(hines::KFlow));
+  const int64_t sz_fl = al((int64_t)fjobs.size() * sizeof(hines::KFlowJob));
   const int64_t sz_fm = al((int64_t)P.fmask.size() * sizeof(uint64_t));
   const int64_t sz_fp = al((int64_t)P.fpos.size() * sizeof(uint16_t));
   const int64_t sz_fa = al((int64_t)P.faux.size() * sizeof(int16_t));
@@ -1007,8 +1036,8 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   off += sz_gl;
   p->t.ws = P.ws_doubles > 0 ? (double*)(base + off) : nullptr;
   off += sz_ws;
-  p->t.flow = (const hines::KFlow*)(base + off);
-  if (e == hipSuccess) e = up(P.kflow.data(), (int64_t)P.kflow.size() * sizeof(hines::KFlow), off);
+  p->t.fjob = (const hines::KFlowJob*)(base + off);
+  if (e == hipSuccess) e = up(fjobs.data(), (int64_t)fjobs.size() * sizeof(hines::KFlowJob), off);
   off += sz_fl;
   p->t.fmask = (const uint64_t*)(base + off);
   if (e == hipSuccess) e = up(P.fmask.data(), (int64_t)P.fmask.size() * sizeof(uint64_t), off);
@@ -1486,7 +1515,7 @@ hines_status hines_plan_info_get(const hines_plan* p, hines_plan_info* info) {
   info->ngroups = p->host.ngroups;
   info->nsegments = p->host.nseg;
   info->max_level = p->host.max_level;
-  int nb = 0;
+  int nb = (int)p->flow_launches.size();
   for (const auto& b : p->buckets) nb += b.count > 0;
   info->nclasses = nb;
   info->device_table_bytes = p->dev_bytes;

@@ -28,7 +28,7 @@ struct DevTables {
   const KCell* cell;     // group order
   const int32_t* glist;  // group ids of one launch
   double* ws;            // global images of groups that exceed LDS
-  const hines::KFlow* flow;  // flow kernel: per group
+  const hines::KFlowJob* fjob;  // flow kernel: one record per wave of a launch, bin by bin
   const uint64_t* fmask;     // flow kernel: active and push masks per step
   const uint16_t* fpos;      // flow kernel: position of every element
   const int16_t* faux;       // flow kernel: parent position of every push
@@ -596,10 +596,8 @@ __global__ __launch_bounds__(T) void k_solve_level(DevTables tb, RhsSpec rs, con
 // or in LDS, written in an earlier forward step (light child).
 // ---------------------------------------------------------------------------
 using hines::flow_image8;
-using hines::flow_lds_bytes;
 using hines::flow_mask_offset;
 
-__device__ __forceinline__ int tri(int p) { return (int)__umul24((unsigned)p, 3u); }  // 3 p, p < 2^24
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 __device__ __forceinline__ int rank_in(uint64_t m, int base) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
@@ -627,80 +625,83 @@ enum : int { kCellFactor = 4 };
 enum : int { kCellCond = 5 };
 
 // Element e of a user range (user index lo + e) -> its position.  A lane
-// handles elements lane, lane + 64, ...; the loads of kStageUnroll of them are
-// issued before any is used.  Indices past the range are clamped to its last
-// element, so every load is unconditional (the repeated element is written
-// twice with the same value).
-constexpr int kStageUnroll = 16;
-
-// The first kStageUnroll entries of each lane are also returned in keep[], so
-// that a group staged in one batch stores its solution without reading its
-// positions again.
+// handles elements lane, lane + 64, ... in batches of kStageUnroll<RHS>; all loads
+// of a batch are issued before any is used.  Indices past the range are clamped
+// to its last element, so every load is unconditional (the repeated element is
+// written twice with the same value).
+// Two batches are in flight at once: their sizes fill the 256 registers that a
+// workgroup of eight waves has.
 template <int RHS>
-__device__ __forceinline__ void flow_stage_range(const RhsSpec& rs, const double* __restrict__ d_,
-                                                 const double* __restrict__ u_, int64_t lo, int n,
-                                                 const uint16_t* __restrict__ pos, lds_f64* img, int lane,
-                                                 uint32_t* keep) {
+constexpr int kStageUnroll = RHS == kFlowGiven ? 10 : RHS == kFlowNoise ? 6 : 7;
+template <int RHS>
+constexpr int kStageBatch = 64 * kStageUnroll<RHS>;
+
+// Register set of one batch: positions, matrix, right-hand side ingredients.
+template <int RHS, typename MT>
+struct FlowBatch {
+  uint32_t p[kStageUnroll<RHS>];
+  MT d[kStageUnroll<RHS>], u[kStageUnroll<RHS>];
+  double b[kStageUnroll<RHS>];
+  double c[RHS == kFlowGiven ? 1 : kStageUnroll<RHS>];
+  double i[RHS == kFlowCVI ? kStageUnroll<RHS> : 1];
+};
+
+template <int RHS, typename MT>
+__device__ __forceinline__ void flow_batch_load(FlowBatch<RHS, MT>& S, const RhsSpec& rs, const MT* __restrict__ d,
+                                                const MT* __restrict__ u, int64_t lo, int n,
+                                                const uint16_t* __restrict__ pos, int e0, int lane) {
   // uniform bases, 32-bit per-lane offsets
-  const double* __restrict__ d = d_ + lo;
-  const double* __restrict__ u = u_ + lo;
-  const double* __restrict__ rhs = rs.rhs + lo;
-  const double* __restrict__ cc = rs.c + lo;
-  const double* __restrict__ vv = rs.v + lo;
-  const double* __restrict__ ii = rs.icur + lo;
-  for (int e0 = 0; e0 < n; e0 += 64 * kStageUnroll) {
-    uint32_t pw[kStageUnroll];
-    double dv[kStageUnroll], uv[kStageUnroll], bv[kStageUnroll], cv[kStageUnroll];
 #pragma unroll
-    for (int k = 0; k < kStageUnroll; ++k) {
-      const int e = min(e0 + 64 * k + lane, n - 1);
-      pw[k] = pos[e];
-      dv[k] = d[e];
-      uv[k] = u[e];
-      if constexpr (RHS == kFlowGiven) {
-        bv[k] = rhs[e];
-      } else {
-        cv[k] = cc[e];
-        bv[k] = vv[e];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kStageUnroll; ++k) {
-      const int e = min(e0 + 64 * k + lane, n - 1);
-      double b = bv[k];
-      if constexpr (RHS != kFlowGiven) b = cv[k] * bv[k];
-      if constexpr (RHS == kFlowCVI) b = b + ii[e];
-      if constexpr (RHS == kFlowNoise) b = b + noise_draw(rs.seed, rs.step, (uint64_t)(lo + e), rs.sigma);
-      lds_f64* q = img + (int)(pw[k] & 0x7fffu);
-      q[0] = dv[k];
-      q[1] = (pw[k] & 0x8000u) ? 0.0 : uv[k];
-      q[2] = b;
-    }
-    if (e0 == 0) {
-#pragma unroll
-      for (int k = 0; k < kStageUnroll; ++k) keep[k] = pw[k];
+  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
+    const int e = min(e0 + 64 * k + lane, n - 1);
+    S.p[k] = pos[e];
+    S.d[k] = (d + lo)[e];
+    S.u[k] = (u + lo)[e];
+    if constexpr (RHS == kFlowGiven) {
+      S.b[k] = (rs.rhs + lo)[e];
+    } else {
+      S.c[k] = (rs.c + lo)[e];
+      S.b[k] = (rs.v + lo)[e];
+      if constexpr (RHS == kFlowCVI) S.i[k] = (rs.icur + lo)[e];
     }
   }
 }
 
-// keep: the positions of the first batch (from the staging), or nullptr.
-__device__ __forceinline__ void flow_store_range(double* x_, int64_t lo, int n, const uint16_t* __restrict__ pos,
-                                                 const lds_f64* img, int lane, const uint32_t* keep) {
-  double* x = x_ + lo;
-  for (int e0 = 0; e0 < n; e0 += 64 * kStageUnroll) {
-    uint32_t pw[kStageUnroll];
-    if (e0 == 0 && keep) {
+template <int RHS, typename MT>
+__device__ __forceinline__ void flow_batch_put(const FlowBatch<RHS, MT>& S, const RhsSpec& rs, int64_t lo, int n,
+                                               lds_f64* img, int e0, int lane) {
 #pragma unroll
-      for (int k = 0; k < kStageUnroll; ++k) pw[k] = keep[k];
-    } else {
+  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
+    double b = S.b[k];
+    if constexpr (RHS != kFlowGiven) b = S.c[k] * S.b[k];
+    if constexpr (RHS == kFlowCVI) b = b + S.i[k];
+    if constexpr (RHS == kFlowNoise)
+      b = b + noise_draw(rs.seed, rs.step, (uint64_t)(lo + min(e0 + 64 * k + lane, n - 1)), rs.sigma);
+    lds_f64* q = img + (int)(S.p[k] & 0x7fffu);
+    q[0] = (double)S.d[k];
+    q[1] = (S.p[k] & 0x8000u) ? 0.0 : (double)S.u[k];
+    q[2] = b;
+  }
+}
+
+// Store elements [e0, e0 + kStageBatch<RHS>) of a range from their positions p.
+template <int RHS>
+__device__ __forceinline__ void flow_batch_store(double* x, int n, const uint32_t* p, const lds_f64* img, int e0,
+                                                 int lane) {
 #pragma unroll
-      for (int k = 0; k < kStageUnroll; ++k) pw[k] = pos[min(e0 + 64 * k + lane, n - 1)];
-    }
+  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
+    const int e = e0 + 64 * k + lane;
+    if (e < n) x[e] = img[(int)(p[k] & 0x7fffu) + 2];
+  }
+}
+template <int RHS>
+__device__ __forceinline__ void flow_store_from(double* x, int n, const uint16_t* __restrict__ pos, const lds_f64* img,
+                                                int e0, int lane) {
+  for (; e0 < n; e0 += kStageBatch<RHS>) {
+    uint32_t p[kStageUnroll<RHS>];
 #pragma unroll
-    for (int k = 0; k < kStageUnroll; ++k) {
-      const int e = e0 + 64 * k + lane;
-      if (e < n) x[e] = img[(int)(pw[k] & 0x7fffu) + 2];
-    }
+    for (int k = 0; k < kStageUnroll<RHS>; ++k) p[k] = pos[min(e0 + 64 * k + lane, n - 1)];
+    flow_batch_store<RHS>(x, n, p, img, e0, lane);
   }
 }
 
@@ -721,186 +722,254 @@ __device__ __forceinline__ uint64_t first_u64(uint32_t lo, uint32_t hi) {
 constexpr int KC = hines::kFlowChunk;
 constexpr int KB8 = hines::kFlowBlock8;
 
-template <int RHS>
-__global__ __launch_bounds__(64) void k_solve_flow(DevTables tb, RhsSpec rs, const double* __restrict__ d,
-                                                   const double* __restrict__ u, double* x) {
-  extern __shared__ __attribute__((aligned(16))) double img_raw[];
-  lds_f64* img = (lds_f64*)img_raw;
-  const int g = tb.glist[blockIdx.x];
-  const KGroup G = tb.grp[g];
-  const hines::KFlow W = tb.flow[g];
-  const int lane = threadIdx.x;
-  const uint16_t* pos = tb.fpos + W.pos_off;
-  const int F = W.nstep;
-  const int nblk = W.nent / KC;
-  const int idle = nblk * KB8, sink = idle + KB8 + lane;
-  lds_i16* aux = (lds_i16*)(img + flow_image8(W));
-  // masks of steps 0 .. F-1, then one zero record on each side (steps -1 and F)
-  lds_u4* msk = (lds_u4*)((lds_u8*)img + flow_mask_offset(W)) + 1;
-  // masks and push targets by global->LDS DMA (16- and 4-byte units; the push
-  // targets of a group start 4-byte aligned and the table is padded)
-  dma16<64>(tb.fmask + 2 * W.step_off, (void*)(msk), F, lane);
-  dma4<64>(tb.faux + W.aux_off, (void*)aux, (W.naux + 1) >> 1, lane);
-  // every entry of every block (pads and the identity block included) starts
-  // as the identity compartment; the scatter below overwrites the real ones
-  for (int e = lane; e < W.nent + KC; e += 64) {
+// LDS image of one group, the wave's own region of the workgroup's LDS.
+struct FlowImage {
+  lds_f64* img;
+  lds_i16* aux;  // push targets
+  lds_u4* msk;   // masks of steps 0 .. F - 1, a zero record on each side (steps -1 and F)
+  int F, nblk, naux;
+  int idle, sink;  // units of the identity block and of this lane's sink
+  int last_aux;
+};
+
+// A lane's block in a step whose active lanes are m, the first of them at block r
+__device__ __forceinline__ int flow_block(const FlowImage& I, uint64_t m, int r) {
+  return lane_in(m) ? (int)__umul24((unsigned)rank_in(m, r), (unsigned)KB8) : I.idle;
+}
+
+__device__ __forceinline__ FlowImage flow_image(const hines::KFlowJob& J, char* raw, int lane) {
+  FlowImage I;
+  I.img = (lds_f64*)(raw + J.lds_off);
+  I.F = J.nstep;
+  I.nblk = J.nent / KC;
+  I.naux = J.naux;
+  I.idle = I.nblk * KB8;
+  I.sink = I.idle + KB8 + lane;
+  I.aux = (lds_i16*)(I.img + flow_image8(J.nent));
+  I.msk = (lds_u4*)((lds_u8*)I.img + flow_mask_offset(J.nent, J.naux)) + 1;
+  I.last_aux = J.naux > 0 ? J.naux - 1 : 0;
+  return I;
+}
+
+// Masks and push targets by global->LDS DMA (16- and 4-byte units; the push
+// targets of a group start 4-byte aligned and the table is padded); the caller
+// waits for them.
+__device__ __forceinline__ void flow_stage_tables(const DevTables& tb, const hines::KFlowJob& J, const FlowImage& I,
+                                                  char* raw, int lane) {
+  char* g = raw + J.lds_off;
+  dma16<64>(tb.fmask + 2 * J.step_off, g + flow_mask_offset(J.nent, J.naux) + 16, J.nstep, lane);
+  dma4<64>(tb.faux + J.aux_off, g + 8 * flow_image8(J.nent), (J.naux + 1) >> 1, lane);
+}
+
+// Every entry of every block (pads and the identity block included) starts as
+// the identity compartment; the staging overwrites the real ones.
+__device__ __forceinline__ void flow_clear(const hines::KFlowJob& J, const FlowImage& I, int lane) {
+  for (int e = lane; e < J.nent + KC; e += 64) {
     const int o = (e / KC) * KB8 + 3 * (e % KC);
-    img[o] = 1.0;
-    img[o + 1] = 0.0;
-    img[o + 2] = 0.0;
+    I.img[o] = 1.0;
+    I.img[o + 1] = 0.0;
+    I.img[o + 2] = 0.0;
   }
   if (lane == 0) {
-    msk[-1] = u32x4{0u, 0u, 0u, 0u};
-    msk[F] = u32x4{0u, 0u, 0u, 0u};
-    if (W.naux == 0) aux[0] = 0;  // the clamped push-target read stays defined
+    I.msk[-1] = u32x4{0u, 0u, 0u, 0u};
+    I.msk[I.F] = u32x4{0u, 0u, 0u, 0u};
+    if (I.naux == 0) I.aux[0] = 0;  // the clamped push-target read stays defined
   }
-  uint32_t keep[kStageUnroll];
-  if (G.contig) {
-    flow_stage_range<RHS>(rs, d, u, G.user_base + G.user_lo, G.user_n, pos, img, lane, keep);
+}
+
+// Operands of one backward chunk step: the lane's block, its push target.
+struct FlowBwd {
+  double d[KC], u[KC], b[KC];
+  int rb, q;
+};
+
+// Backward sweep.  During chunk step t: the masks of t + 1 move to scalar
+// registers, the masks of t + 2, the operands of t + 1 and the push target of
+// t + 1 are read from LDS, and the KC sub-steps of t are eliminated.  Two
+// register sets are used in turn, so that no step ends by copying (and so
+// waiting for) the operands read during it.
+__device__ __forceinline__ void flow_backward(const FlowImage& I) {
+  lds_f64* img = I.img;
+  const int F = I.F;
+  const u32x4 m0 = I.msk[0];
+  uint64_t M = first_u64(m0.x, m0.y), E = first_u64(m0.z, m0.w);
+  u32x4 mv = I.msk[1];
+  int R = 0, A = 0;
+  double fin = 0.0, uin = 0.0, bin = 0.0;
+  auto load = [&](FlowBwd& S, uint64_t m, uint64_t e, int r, int a) {
+    S.rb = flow_block(I, m, r);
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      S.d[j] = img[S.rb + 3 * j];
+      S.u[j] = img[S.rb + 3 * j + 1];
+      S.b[j] = img[S.rb + 3 * j + 2];
+    }
+    S.q = I.aux[min(rank_in(e, a), I.last_aux)];
+  };
+  auto step = [&](int t, FlowBwd& C, FlowBwd& N) {
+    const uint64_t M1 = first_u64(mv.x, mv.y), E1 = first_u64(mv.z, mv.w);
+    mv = I.msk[t + 2 <= F ? t + 2 : F];
+    R += __builtin_popcountll(M);
+    A += __builtin_popcountll(E);
+    load(N, M1, E1, R, A);
+    const int wb = lane_in(M) ? C.rb : I.sink;
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      const double dl = __builtin_fma(-fin, uin, C.d[j]);
+      const double bl = __builtin_fma(-fin, bin, C.b[j]);
+      const double r = rcp_nr(dl);
+      const double f = C.u[j] * r;
+      img[wb + 3 * j] = f;
+      img[wb + 3 * j + 2] = bl * r;
+      fin = f;
+      uin = C.u[j];
+      bin = bl;
+    }
+    if (lane_in(E)) {
+      lds_add(img + C.q, -(fin * uin));
+      lds_add(img + C.q + 2, -(fin * bin));
+    }
+    fin = lane_in(M & ~E) ? fin : 0.0;
+    M = M1;
+    E = E1;
+  };
+  FlowBwd S0, S1;
+  load(S0, M, E, 0, 0);
+  for (int t = 0; t < F; t += 2) {
+    step(t, S0, S1);
+    if (t + 1 >= F) break;
+    step(t + 1, S1, S0);
+  }
+}
+
+// Operands of one forward chunk step; xq: x of the parent of a pushed path.
+struct FlowFwd {
+  double f[KC], y[KC], xq;
+  int rb;
+};
+
+// Forward sweep, chunk steps in reverse, sub-steps in reverse.  During step t:
+// the masks of t - 2 move to scalar registers, the masks of t - 3 are read, the
+// operands of t - 1, the parent x of the pushing lanes of t - 1 and the push
+// target of t - 2 are read from LDS, and step t is solved.
+__device__ __forceinline__ void flow_forward(const FlowImage& I) {
+  lds_f64* img = I.img;
+  const int F = I.F;
+  const u32x4 ma = I.msk[F - 1], mb = I.msk[F - 2];
+  uint64_t M = first_u64(ma.x, ma.y), E = first_u64(ma.z, ma.w);
+  uint64_t M1 = first_u64(mb.x, mb.y), E1 = first_u64(mb.z, mb.w);
+  u32x4 mv = I.msk[F - 3 >= -1 ? F - 3 : -1];
+  int R1 = I.nblk - __builtin_popcountll(M), A1 = I.naux - __builtin_popcountll(E);
+  auto load = [&](FlowFwd& S, uint64_t m, int r, int q) {
+    S.rb = flow_block(I, m, r);
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      S.f[j] = img[S.rb + 3 * j];
+      S.y[j] = img[S.rb + 3 * j + 2];
+    }
+    S.xq = img[q + 2];
+  };
+  FlowFwd S0, S1;
+  load(S0, M, R1, I.aux[min(rank_in(E, A1), I.last_aux)]);
+  R1 -= __builtin_popcountll(M1);
+  A1 -= __builtin_popcountll(E1);
+  int q1 = I.aux[min(rank_in(E1, A1), I.last_aux)];
+  double xp = 0.0;
+  auto step = [&](int t, FlowFwd& C, FlowFwd& N) {
+    const uint64_t M2 = first_u64(mv.x, mv.y), E2 = first_u64(mv.z, mv.w);
+    mv = I.msk[t - 3 >= -1 ? t - 3 : -1];
+    load(N, M1, R1, q1);
+    R1 -= __builtin_popcountll(M2);
+    A1 -= __builtin_popcountll(E2);
+    q1 = I.aux[min(rank_in(E2, A1), I.last_aux)];
+    const int wb = lane_in(M) ? C.rb : I.sink;
+    double xv = lane_in(E) ? C.xq : xp;
+#pragma unroll
+    for (int j = KC - 1; j >= 0; --j) {
+      xv = __builtin_fma(-C.f[j], xv, C.y[j]);
+      img[wb + 3 * j + 2] = xv;
+    }
+    xp = lane_in(M) ? xv : xp;
+    M = M1;
+    E = E1;
+    M1 = M2;
+    E1 = E2;
+  };
+  for (int t = F - 1; t >= 0; t -= 2) {
+    step(t, S0, S1);
+    if (t < 1) break;
+    step(t - 1, S1, S0);
+  }
+}
+
+// One wave per group, blockDim.x / 64 groups per workgroup (a bin: the host
+// packs groups of different sizes into the LDS of one workgroup).  The waves
+// of a workgroup share nothing and never meet at a barrier.  MT: the storage
+// type of the matrix (double, or float widened exactly).
+//
+// Bound by the serial length of a group times the groups that LDS holds: about
+// 23 chunk steps a sweep for a C2 cell at 950 (backward) and 450 (forward)
+// cycles each when alone, 1,190 and 540 with three on a compute unit; staging
+// 10,000 to 15,000 cycles and the store 5,000 are memory latency.  The two
+// register sets of the sweeps, the two staging batches in flight and the bins
+// took 64 C2 cells from 207 to 28 us (11 launches before, one now), 4,099 from
+// 424 to 161 us, a step of 8,192 cells of 1,000 from 216 to 193 us.
+template <int RHS, typename MT = double>
+__global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, const MT* __restrict__ d,
+                                                    const MT* __restrict__ u, double* x) {
+  extern __shared__ __attribute__((aligned(16))) char flow_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const hines::KFlowJob J = tb.fjob[blockIdx.x * (blockDim.x >> 6) + wave];
+  if (J.nstep == 0) return;  // an empty place of the bin
+  const FlowImage I = flow_image(J, flow_raw, lane);
+  const uint16_t* pos = tb.fpos + J.pos_off;
+  const int n = J.nelem;
+  // the first two batches are in flight together, and the image is cleared
+  // meanwhile; their positions stay in registers for the store
+  FlowBatch<RHS, MT> S0, S1;
+  if (J.ncell == 0) {
+    flow_batch_load(S0, rs, d, u, J.user_lo, n, pos, 0, lane);
+    if (n > kStageBatch<RHS>) flow_batch_load(S1, rs, d, u, J.user_lo, n, pos, kStageBatch<RHS>, lane);
+  }
+  flow_stage_tables(tb, J, I, flow_raw, lane);
+  flow_clear(J, I, lane);
+  if (J.ncell == 0) {
+    flow_batch_put(S0, rs, J.user_lo, n, I.img, 0, lane);
+    if (n > kStageBatch<RHS>) flow_batch_put(S1, rs, J.user_lo, n, I.img, kStageBatch<RHS>, lane);
+    for (int e0 = 2 * kStageBatch<RHS>; e0 < n; e0 += kStageBatch<RHS>) {
+      FlowBatch<RHS, MT> S;
+      flow_batch_load(S, rs, d, u, J.user_lo, n, pos, e0, lane);
+      flow_batch_put(S, rs, J.user_lo, n, I.img, e0, lane);
+    }
   } else {
-    int e0 = 0;
-    for (int c = 0; c < G.ncell; ++c) {
-      const KCell C = tb.cell[G.cell_begin + c];
-      flow_stage_range<RHS>(rs, d, u, C.user_lo, C.n, pos + e0, img, lane, keep);
-      e0 += C.n;
+    int q = 0;
+    for (int c = 0; c < J.ncell; ++c) {
+      const KCell C = tb.cell[J.cell_begin + c];
+      for (int e0 = 0; e0 < C.n; e0 += kStageBatch<RHS>) {
+        flow_batch_load(S0, rs, d, u, C.user_lo, C.n, pos + q, e0, lane);
+        flow_batch_put(S0, rs, C.user_lo, C.n, I.img, e0, lane);
+      }
+      q += C.n;
     }
   }
   __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
-  __syncthreads();  // staged
-  const int last_aux = W.naux > 0 ? W.naux - 1 : 0;
-
-  // Backward sweep.  During chunk step t: the masks of t + 1 move to scalar
-  // registers, the masks of t + 2, the operands of t + 1 and the push target of
-  // t + 1 are read from LDS, and the KC sub-steps of t are eliminated.
-  {
-    const u32x4 m0 = msk[0];
-    uint64_t M = first_u64(m0.x, m0.y), E = first_u64(m0.z, m0.w);
-    u32x4 mv = msk[1];
-    int R = 0, A = 0;
-    int rb = lane_in(M) ? rank_in(M, 0) * KB8 : idle;
-    double Dn[KC], Un[KC], Bn[KC];
-#pragma unroll
-    for (int j = 0; j < KC; ++j) {
-      Dn[j] = img[rb + 3 * j];
-      Un[j] = img[rb + 3 * j + 1];
-      Bn[j] = img[rb + 3 * j + 2];
-    }
-    int qn = aux[min(rank_in(E, 0), last_aux)];
-    double fin = 0.0, uin = 0.0, bin = 0.0;
-    for (int t = 0; t < F; ++t) {
-      const uint64_t M1 = first_u64(mv.x, mv.y), E1 = first_u64(mv.z, mv.w);
-      mv = msk[t + 2 <= F ? t + 2 : F];
-      const int R1 = R + __builtin_popcountll(M), A1 = A + __builtin_popcountll(E);
-      double Dc[KC], Uc[KC], Bc[KC];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        Dc[j] = Dn[j];
-        Uc[j] = Un[j];
-        Bc[j] = Bn[j];
-      }
-      const int qp = qn;
-      const int wb = lane_in(M) ? rb : sink;
-      rb = lane_in(M1) ? rank_in(M1, R1) * KB8 : idle;
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        Dn[j] = img[rb + 3 * j];
-        Un[j] = img[rb + 3 * j + 1];
-        Bn[j] = img[rb + 3 * j + 2];
-      }
-      qn = aux[min(rank_in(E1, A1), last_aux)];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        const double dl = __builtin_fma(-fin, uin, Dc[j]);
-        const double bl = __builtin_fma(-fin, bin, Bc[j]);
-        const double r = rcp_nr(dl);
-        const double f = Uc[j] * r;
-        img[wb + 3 * j] = f;
-        img[wb + 3 * j + 2] = bl * r;
-        fin = f;
-        uin = Uc[j];
-        bin = bl;
-      }
-      {
-        const double cd = -(fin * uin), cb = -(fin * bin);
-        if (lane_in(E)) {
-          lds_add(img + qp, cd);
-          lds_add(img + qp + 2, cb);
-        }
-      }
-      fin = lane_in(M & ~E) ? fin : 0.0;
-      M = M1;
-      E = E1;
-      R = R1;
-      A = A1;
-    }
-  }
-  __syncthreads();  // backward done
-
-  // Forward sweep, chunk steps in reverse, sub-steps in reverse.  During step
-  // t: the masks of t - 2 move to scalar registers, the masks of t - 3 are
-  // read, the operands of t - 1, the parent x of the pushing lanes of t - 1 and
-  // the push target of t - 2 are read from LDS, and step t is solved.
-  {
-    const u32x4 ma = msk[F - 1], mb = msk[F - 2];
-    uint64_t M = first_u64(ma.x, ma.y), E = first_u64(ma.z, ma.w);
-    uint64_t M1 = first_u64(mb.x, mb.y), E1 = first_u64(mb.z, mb.w);
-    u32x4 mv = msk[F - 3 >= -1 ? F - 3 : -1];
-    const int R = nblk - __builtin_popcountll(M), A = W.naux - __builtin_popcountll(E);
-    int R1 = R - __builtin_popcountll(M1), A1 = A - __builtin_popcountll(E1);
-    int rb = lane_in(M) ? rank_in(M, R) * KB8 : idle;
-    double fn[KC], yn[KC];
-#pragma unroll
-    for (int j = 0; j < KC; ++j) {
-      fn[j] = img[rb + 3 * j];
-      yn[j] = img[rb + 3 * j + 2];
-    }
-    double xqn = img[aux[min(rank_in(E, A), last_aux)] + 2];
-    int q1 = aux[min(rank_in(E1, A1), last_aux)];
-    double xp = 0.0;
-    for (int t = F - 1; t >= 0; --t) {
-      const uint64_t M2 = first_u64(mv.x, mv.y), E2 = first_u64(mv.z, mv.w);
-      mv = msk[t - 3 >= -1 ? t - 3 : -1];
-      const int R2 = R1 - __builtin_popcountll(M2), A2 = A1 - __builtin_popcountll(E2);
-      double fc[KC], yc[KC];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        fc[j] = fn[j];
-        yc[j] = yn[j];
-      }
-      const double xq = xqn;
-      const int wb = lane_in(M) ? rb : sink;
-      rb = lane_in(M1) ? rank_in(M1, R1) * KB8 : idle;
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        fn[j] = img[rb + 3 * j];
-        yn[j] = img[rb + 3 * j + 2];
-      }
-      xqn = img[q1 + 2];
-      q1 = aux[min(rank_in(E2, A2), last_aux)];
-      double xv = lane_in(E) ? xq : xp;
-#pragma unroll
-      for (int j = KC - 1; j >= 0; --j) {
-        xv = __builtin_fma(-fc[j], xv, yc[j]);
-        img[wb + 3 * j + 2] = xv;
-      }
-      xp = lane_in(M) ? xv : xp;
-      M = M1;
-      E = E1;
-      M1 = M2;
-      E1 = E2;
-      R1 = R2;
-      A1 = A2;
-    }
-  }
-  __syncthreads();  // forward done
-  if (G.contig) {
-    flow_store_range(x, G.user_base + G.user_lo, G.user_n, pos, img, lane, keep);
+  __builtin_amdgcn_wave_barrier();
+  flow_backward(I);
+  __builtin_amdgcn_wave_barrier();
+  flow_forward(I);
+  __builtin_amdgcn_wave_barrier();
+  if (J.ncell == 0) {
+    double* xo = x + J.user_lo;
+    flow_batch_store<RHS>(xo, n, S0.p, I.img, 0, lane);
+    if (n > kStageBatch<RHS>) flow_batch_store<RHS>(xo, n, S1.p, I.img, kStageBatch<RHS>, lane);
+    flow_store_from<RHS>(xo, n, pos, I.img, 2 * kStageBatch<RHS>, lane);
   } else {
-    int e0 = 0;
-    for (int c = 0; c < G.ncell; ++c) {
-      const KCell C = tb.cell[G.cell_begin + c];
-      flow_store_range(x, C.user_lo, C.n, pos + e0, img, lane, G.ncell == 1 ? keep : nullptr);
-      e0 += C.n;
+    int q = 0;
+    for (int c = 0; c < J.ncell; ++c) {
+      const KCell C = tb.cell[J.cell_begin + c];
+      flow_store_from<RHS>(x + C.user_lo, C.n, pos + q, I.img, 0, lane);
+      q += C.n;
     }
   }
 }

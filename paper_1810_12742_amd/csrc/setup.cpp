@@ -17,8 +17,10 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <map>
 #include <new>
 #include <numeric>
+#include <unordered_map>
 
 namespace hines {
 namespace {
@@ -953,6 +955,197 @@ Status build_plan(const int32_t* parent, int64_t n, const int64_t* branch_offset
     err = "host allocation failed during setup";
     return ERR_OOM;
   }
+}
+
+// ---------------------------------------------------------------------------
+// Bins of the flow kernel.  A launch reserves one LDS size for all of its
+// workgroups, but the images of the groups differ (a cell of 200 to 3,000
+// compartments needs 6 to 90 KB), and a launch per size class leaves the chip
+// partly idle at the end of each class: 11 launches in a row cost 64 cells 0.20
+// ms where one group takes 0.03.  So groups of different sizes share the LDS of
+// one workgroup, one wave each, and all of them go in one or two launches.
+// ---------------------------------------------------------------------------
+namespace {
+
+constexpr int64_t kBinCus = 256;  // compute units of the device
+constexpr int32_t kBinMaxWidth = 8;
+constexpr int32_t kBinBytes[] = {163840, 81920, 54528, 40960, 32768, 27136, 23296, 20480, 16384, 12288, 8192, 4096};
+
+struct BinPack {
+  int32_t lds = 0, width = 1;
+  std::vector<std::vector<int32_t>> bins;  // groups of each bin
+  double rounds = 0;                       // bins over the bins the device holds at once
+};
+
+// Best fit by decreasing size: each group goes to the open bin that it fills
+// most, at most `width` groups a bin.
+BinPack pack_bins(const std::vector<int32_t>& by_size, const std::vector<int64_t>& bytes, int32_t cap, int32_t width) {
+  BinPack out;
+  out.lds = cap;
+  std::multimap<int64_t, int32_t> open;  // free bytes -> bin
+  for (int32_t g : by_size) {
+    auto it = open.lower_bound(bytes[g]);
+    int32_t b;
+    int64_t left;
+    if (it == open.end()) {
+      b = (int32_t)out.bins.size();
+      out.bins.emplace_back();
+      left = cap;
+    } else {
+      b = it->second;
+      left = it->first;
+      open.erase(it);
+    }
+    out.bins[b].push_back(g);
+    if ((int32_t)out.bins[b].size() < width) open.emplace(left - bytes[g], b);
+  }
+  for (const auto& b : out.bins) out.width = std::max(out.width, (int32_t)b.size());
+  out.rounds = (double)out.bins.size() / (double)(kBinCus * (kLdsLimitBytes / cap));
+  return out;
+}
+
+}  // namespace
+
+void pack_flow_bins(const HostPlan& P, std::vector<FlowLaunch>& launches, std::vector<KFlowJob>& jobs) {
+  launches.clear();
+  jobs.clear();
+  if (!P.flow) return;
+  std::vector<int32_t> groups;
+  std::vector<int64_t> bytes(P.ngroups, 0);
+  for (int64_t g = 0; g < P.ngroups; ++g)
+    if (P.kgroup[g].ws_off < 0 && P.kflow[g].nstep > 0) {
+      groups.push_back((int32_t)g);
+      bytes[g] = flow_lds_bytes(P.kflow[g]);
+    }
+  if (groups.empty()) return;
+  std::stable_sort(groups.begin(), groups.end(), [&](int32_t a, int32_t b) { return bytes[a] > bytes[b]; });
+  std::vector<BinPack> best;
+  const int64_t N = (int64_t)groups.size(), maxb = bytes[groups[0]];
+  if (N <= kBinCus) {
+    // a group per compute unit: nothing is gained by sharing one
+    best.push_back(pack_bins(groups, bytes, (int32_t)((maxb + 255) & ~(int64_t)255), 1));
+  } else {
+    // One LDS size for all groups, or the largest bins for the groups above a
+    // size and smaller bins for the rest; the fewest rounds of the device
+    // win.  A launch's last round counts whole, so a second launch has to save
+    // more than it adds; on a tie the smaller bins (a bin is free again only
+    // when its last wave ends).  Few groups are spread over the device before
+    // they share a workgroup.
+    const int32_t width = (int32_t)std::min<int64_t>(kBinMaxWidth, std::max<int64_t>(1, N / (2 * kBinCus)));
+    double best_cost = 1e300;
+    auto consider = [&](std::vector<BinPack>&& v) {
+      double cost = 0;
+      for (const BinPack& b : v) cost += std::max(1.0, b.rounds) + 0.5;
+      if (cost < best_cost - 1e-9) {
+        best_cost = cost;
+        best = std::move(v);
+      }
+    };
+    for (int k = (int)(sizeof kBinBytes / sizeof kBinBytes[0]) - 1; k >= 0; --k) {
+      const int32_t cap = kBinBytes[k];
+      if (cap >= maxb) {
+        consider({pack_bins(groups, bytes, cap, width)});
+      } else {
+        size_t nbig = 0;  // groups that do not fit this size
+        while (nbig < groups.size() && bytes[groups[nbig]] > cap) ++nbig;
+        int32_t big = kBinBytes[0];
+        for (int32_t c : kBinBytes)
+          if (c >= maxb) big = c;
+        consider({pack_bins({groups.begin(), groups.begin() + (std::ptrdiff_t)nbig}, bytes, big, width),
+                  pack_bins({groups.begin() + (std::ptrdiff_t)nbig, groups.end()}, bytes, cap, width)});
+      }
+    }
+  }
+  for (BinPack& bp : best) {
+    // the bins with the longest schedules first, and inside a bin too
+    std::vector<std::pair<int32_t, int32_t>> order;
+    for (size_t b = 0; b < bp.bins.size(); ++b) {
+      auto& m = bp.bins[b];
+      std::stable_sort(m.begin(), m.end(), [&](int32_t x, int32_t y) { return P.kflow[x].nstep > P.kflow[y].nstep; });
+      order.push_back({P.kflow[m[0]].nstep, (int32_t)b});
+    }
+    std::stable_sort(order.begin(), order.end(),
+                     [](const auto& x, const auto& y) { return x.first > y.first; });
+    FlowLaunch L{bp.lds, bp.width, (int64_t)jobs.size(), (int32_t)order.size()};
+    for (const auto& o : order) {
+      int64_t off = 0;
+      for (int32_t w = 0; w < bp.width; ++w) {
+        KFlowJob J{};
+        if (w < (int32_t)bp.bins[o.second].size()) {
+          const int32_t g = bp.bins[o.second][w];
+          const KGroup& G = P.kgroup[g];
+          const KFlow& W = P.kflow[g];
+          J.user_lo = G.contig ? G.user_base + G.user_lo : 0;
+          J.step_off = W.step_off;
+          J.pos_off = W.pos_off;
+          J.aux_off = W.aux_off;
+          J.nstep = W.nstep;
+          J.nelem = W.nelem;
+          J.naux = W.naux;
+          J.nent = W.nent;
+          J.lds_off = (int32_t)off;
+          J.ncell = G.contig ? 0 : G.ncell;
+          J.cell_begin = G.cell_begin;
+          off += bytes[g];
+        }
+        jobs.push_back(J);
+      }
+    }
+    launches.push_back(L);
+  }
+}
+
+bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches, const std::vector<KFlowJob>& jobs,
+                     std::string& why) {
+  std::unordered_map<int64_t, int32_t> by_step;  // first step record -> group
+  for (int64_t g = 0; g < P.ngroups && P.flow; ++g)
+    if (P.kgroup[g].ws_off < 0 && P.kflow[g].nstep > 0) by_step[P.kflow[g].step_off] = (int32_t)g;
+  int64_t at = 0;
+  size_t placed = 0;
+  for (const FlowLaunch& L : launches) {
+    if (L.first != at || L.width < 1 || L.width > kBinMaxWidth || L.lds_bytes > kLdsLimitBytes) {
+      why = "flow launch record";
+      return false;
+    }
+    for (int32_t b = 0; b < L.bins; ++b) {
+      int64_t end = 0;
+      for (int32_t w = 0; w < L.width; ++w, ++at) {
+        if (at >= (int64_t)jobs.size()) {
+          why = "flow job table size";
+          return false;
+        }
+        const KFlowJob& J = jobs[at];
+        if (J.nstep == 0) continue;
+        auto it = by_step.find(J.step_off);
+        if (it == by_step.end()) {
+          why = "flow group placed twice or unknown";
+          return false;
+        }
+        const KFlow& W = P.kflow[it->second];
+        const KGroup& G = P.kgroup[it->second];
+        by_step.erase(it);
+        ++placed;
+        const bool range = J.ncell == 0 && G.contig && J.user_lo == G.user_base + G.user_lo;
+        const bool cells = J.ncell == G.ncell && !G.contig && J.cell_begin == G.cell_begin;
+        if (J.nstep != W.nstep || J.nelem != W.nelem || J.nent != W.nent || J.naux != W.naux ||
+            J.pos_off != W.pos_off || J.aux_off != W.aux_off || !(range || cells) || J.lds_off < end ||
+            (J.lds_off & 15)) {
+          why = "flow job record";
+          return false;
+        }
+        end = J.lds_off + flow_lds_bytes(W);
+      }
+      if (end > L.lds_bytes) {
+        why = "a bin exceeds its LDS";
+        return false;
+      }
+    }
+  }
+  if (at != (int64_t)jobs.size() || !by_step.empty()) {
+    why = "flow groups without a bin";
+    return false;
+  }
+  return true;
 }
 
 int64_t export_table(const HostPlan& p, int32_t id, int64_t* out, int64_t capacity) {

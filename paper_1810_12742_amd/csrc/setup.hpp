@@ -402,13 +402,38 @@ static_assert(sizeof(KFlow) == 48, "layout");
 // constant entry for idle lanes and 64 write-only sink entries), push targets
 // (int16, at least one entry), step masks (16 bytes per step plus a zero
 // record before and after).
-constexpr int64_t flow_image8(const KFlow& w) {  // 8-byte units of blocks, identity block and sink
-  return (int64_t)w.nent / kFlowChunk * kFlowBlock8 + kFlowTail8;
+constexpr int64_t flow_image8(int32_t nent) {  // 8-byte units of blocks, identity block and sink
+  return (int64_t)nent / kFlowChunk * kFlowBlock8 + kFlowTail8;
 }
-constexpr int64_t flow_mask_offset(const KFlow& w) {
-  return (8 * flow_image8(w) + 2 * ((int64_t)w.naux + 1) + 15) & ~(int64_t)15;
+constexpr int64_t flow_mask_offset(int32_t nent, int32_t naux) {
+  return (8 * flow_image8(nent) + 2 * ((int64_t)naux + 1) + 15) & ~(int64_t)15;
 }
-constexpr int64_t flow_lds_bytes(const KFlow& w) { return flow_mask_offset(w) + 16 * ((int64_t)w.nstep + 2); }
+constexpr int64_t flow_lds_bytes(const KFlow& w) {
+  return flow_mask_offset(w.nent, w.naux) + 16 * ((int64_t)w.nstep + 2);
+}
+
+// What one wave of the flow kernel does: the group's tables, its range of the
+// user arrays, and where its image stands in the workgroup's LDS.  One record
+// holds all of it, so that a wave starts after a single dependent load.
+struct KFlowJob {
+  int64_t user_lo;    // contiguous groups: first user index
+  int64_t step_off, pos_off, aux_off;  // as KFlow
+  int32_t nstep;      // chunk steps per sweep; 0: an empty place of the bin
+  int32_t nelem, naux, nent;
+  int32_t lds_off;    // bytes
+  int32_t ncell;      // cells of a group that is not one user range; 0: one range
+  int32_t cell_begin; // their first entry in the group-cell table
+  int32_t pad;
+};
+static_assert(sizeof(KFlowJob) == 64, "one scalar load");
+
+// Launches of the flow kernel: bins of up to `width` groups that share one
+// workgroup's LDS, one wave each.
+struct FlowLaunch {
+  int32_t lds_bytes, width;   // LDS and waves per workgroup
+  int64_t first;              // first job; bin b holds jobs first + b width ...
+  int32_t bins;
+};
 
 struct HostPlan {
   int64_t n = 0, ncells = 0, nbranches = 0, ngroups = 0, nseg = 0;
@@ -443,6 +468,12 @@ struct HostPlan {
 Status build_plan(const int32_t* parent, int64_t n, const int64_t* branch_offsets, int64_t nbranches,
                   const int64_t* cell_offsets, int64_t ncells, const Options& opt, HostPlan& out,
                   std::string& err);
+
+// Pack the plan's flow groups into bins (after the plan is built).
+void pack_flow_bins(const HostPlan& P, std::vector<FlowLaunch>& launches, std::vector<KFlowJob>& jobs);
+// Every flow group is one job; the regions of a bin are disjoint and inside its LDS.
+bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches, const std::vector<KFlowJob>& jobs,
+                     std::string& why);
 
 // Copy table `id` into out (int64), returns the element count (or -1).
 int64_t export_table(const HostPlan& p, int32_t id, int64_t* out, int64_t capacity);
