@@ -291,6 +291,10 @@ hines_status hines_solve_stored32(const hines_plan* plan, const float* diag32, c
  * forms r = rhs - A x in FP64, solves A d = fl32(r) in FP32 and adds d to x
  * in FP64.  The group's matrix, rhs and solution stay in LDS across sweeps,
  * so HBM sees 24 bytes per compartment whatever the number of sweeps.
+ * Groups with a step schedule (hines_plan_info.kernel == 1) need no iteration
+ * to reach what the sweeps converge to: with sweeps >= 1 they are solved by one
+ * FP64 elimination of the widened matrix, so the result is at least as close
+ * to the FP64 solution as that many sweeps give.
  * HINES_ERR_TOO_BIG if a group does not fit this kernel's LDS image (or, on a
  * cell-lane plan, the groups' 16-bit branch records: a cell-lane plan is
  * still built then, and only this call is refused).

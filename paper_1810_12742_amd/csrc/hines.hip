@@ -123,7 +123,9 @@ struct hines_plan {
   };
   std::vector<Bucket> buckets;        // level-synchronous groups, by LDS footprint
   std::vector<hines::FlowLaunch> flow_launches;  // flow groups, in bins
-  std::vector<Bucket> mixed_buckets;  // FP32+refinement kernel (its own LDS layout)
+  // FP32+refinement kernel (its own LDS layout): all groups, and the groups
+  // that are not in flow_launches
+  std::vector<Bucket> mixed_buckets, mixed_level_buckets;
   std::vector<Bucket> res_buckets;    // LDS-resident kernel, by LDS class
   // LDS classes launch concurrently: bucket i runs on res_lane[i] (0: the
   // caller's stream, k > 0: res_streams[k - 1]), forked from and joined back
@@ -348,9 +350,23 @@ hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d,
   return hipSuccess;
 }
 
+// What a refined solve converges to is the FP64 solution of the widened
+// matrix, and one FP64 elimination of it gives that.  FP64 and FP32 vector
+// arithmetic issue at the same rate here, so every correction sweep costs as
+// much as the whole FP64 solve, in a kernel with a barrier per level on top
+// (4,096 C2 cells, 3 sweeps: 4.40 ms against 0.144).  So groups with a step
+// schedule are solved by the flow kernel from the FP32 storage whenever a
+// correction was asked for; sweep 0 alone is the FP32 result and stays FP32.
 hipError_t launch_mixed(const hines_plan* p, const float* d32, const float* u32, const double* b, double* x,
                         int sweeps, hipStream_t s) {
-  for (const auto& bk : p->mixed_buckets) {
+  if (sweeps > 0) {
+    RhsSpec rs{};
+    rs.rhs = b;
+    rs.mode = hdev::kRhsGiven;
+    const hipError_t e = launch_flow(p, rs, d32, u32, x, s);
+    if (e != hipSuccess) return e;
+  }
+  for (const auto& bk : sweeps > 0 ? p->mixed_level_buckets : p->mixed_buckets) {
     if (bk.count == 0) continue;
     DevTables t = p->t;
     t.glist = p->t.glist + bk.first;
@@ -382,6 +398,7 @@ hipError_t allow_lds_t() {
 
 hipError_t allow_lds(int T) {
   const void* fns[] = {(const void*)hdev::k_solve_flow<hdev::kFlowGiven, double>,
+                       (const void*)hdev::k_solve_flow<hdev::kFlowGiven, float>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCV, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCVI, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowNoise, double>,
@@ -897,11 +914,14 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
       if (k == nbk) p->mixed_ok = false;
       else mm[k].push_back((int32_t)g);
     }
-    if (p->mixed_ok)
+    for (int level = 0; level < 2 && p->mixed_ok; ++level)
       for (int k = 0; k < nbk; ++k) {
         auto& m = mm[k];
+        if (level)
+          m.erase(std::remove_if(m.begin(), m.end(), [&](int32_t g) { return P.flow && P.kflow[g].nstep > 0; }), m.end());
         std::stable_sort(m.begin(), m.end(), [&](int32_t a, int32_t b) { return P.kgroup[a].cost > P.kgroup[b].cost; });
-        p->mixed_buckets.push_back({kBuckets[k], (int32_t)glist.size(), (int32_t)m.size(), 0, 0});
+        (level ? p->mixed_level_buckets : p->mixed_buckets)
+            .push_back({kBuckets[k], (int32_t)glist.size(), (int32_t)m.size(), 0, 0});
         glist.insert(glist.end(), m.begin(), m.end());
       }
   }

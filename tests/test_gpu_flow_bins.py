@@ -53,3 +53,44 @@ def test_one_cell_at_the_staging_batch_edges(n):
 def test_bins_of_mixed_groups(cells, opts):
     rng = np.random.default_rng(cells)
     solve_and_check(rng.choice([40, 300, 1000, 2500, 4500], size=cells, p=[0.2, 0.2, 0.4, 0.15, 0.05]), **opts)
+
+
+def comb_cell(n):
+    """A chain with a leaf on every compartment: each leaf is a path of its own,
+    padded to a whole chunk, so the step schedule's image does not fit LDS."""
+    parent = np.empty(n, dtype=np.int32)
+    parent[0::2] = np.arange(-2, n - 2, 2)
+    parent[0] = -1
+    parent[1::2] = np.arange(0, n - 1, 2)
+    return parent
+
+
+# 1e-12 where one FP64 elimination gives the result, 1e-11 (the refinement's
+# bound after three sweeps) where the FP32 sweeps run
+@pytest.mark.parametrize("comb", [0, 2000])
+@pytest.mark.parametrize("sweeps", [1, 3])
+def test_refined_solve_of_scheduled_and_level_groups(comb, sweeps):
+    import torch
+    from paper_1810_12742_amd import Plan
+    from workloads import Forest
+    f = grow_random_forest(np.random.default_rng(5), 40, target_size=np.full(40, 700))
+    parent, offs = f.parent, f.cell_offsets
+    if comb:
+        q = comb_cell(comb)
+        parent = np.concatenate([parent, np.where(q < 0, -1, q + f.n).astype(np.int32)])
+        offs = np.append(offs, offs[-1] + comb)
+    f = Forest(parent, offs, np.arange(len(parent) + 1, dtype=np.int64))
+    s = cable_values(f, np.random.default_rng(6), a_kind="cable", dt=0.025)
+    d32, u32 = s.diag.astype(np.float32), s.upper.astype(np.float32)
+    xo = oracle.solve(f, d32.astype(np.float64), u32.astype(np.float64), s.rhs)
+    p = Plan(parent, offs)
+    assert p.info["kernel"] == 1 and p.info["nclasses"] == (2 if comb else 1)
+    dev = torch.device("cuda")
+    D, U, B = (torch.from_numpy(a).to(dev) for a in (d32, u32, s.rhs))
+    for out in (None, B):  # the second in place
+        x = p.solve_mixed(D, U, B, out=out, sweeps=sweeps).cpu().numpy()
+        err = np.maximum.reduceat(np.abs(x - xo), offs[:-1]) / np.maximum.reduceat(np.abs(xo), offs[:-1])
+        assert np.max(err[:40]) <= TOL
+        if comb and sweeps == 3:
+            assert err[40] <= 1e-11
+    p.close()
