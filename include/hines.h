@@ -343,7 +343,10 @@ hines_status hines_timestep_assembled(const hines_plan* plan, const double* g, c
  * sweeps there and writes v back in user order at the end: the result equals
  * nsteps hines_timestep calls bit for bit.  If that allocation fails, the
  * loop captures nsteps plain hines_timestep launches instead (same results);
- * hines_timeloop_destroy frees what was allocated.  On a plan with no compartments the
+ * hines_timeloop_destroy frees what was allocated.  On a plan whose groups
+ * have a step schedule (hines_plan_info.kernel == 1) the loop runs up to 256
+ * steps of those groups in one launch, with their factors and state in LDS;
+ * the result again equals single steps bit for bit.  On a plan with no compartments the
  * loop holds no graph and its launch does nothing (the arrays may be NULL). */
 hines_status hines_timeloop_create(const hines_plan* plan, const double* diag, const double* upper,
                                    const double* c, double* v, const double* i_inj, double noise_sigma,

@@ -101,6 +101,7 @@ void* static_scratch(int dev) {
 // sit at 160 KiB / n (rounded down to 256 bytes) for the occupancies that
 // matter; each class is one launch, so there are few of them.
 constexpr int kBuckets[] = {4096, 8192, 12288, 16384, 20480, 23296, 27136, 32768, 40960, 54528, 81920, 163840};
+constexpr int32_t kLoopStretch = 256;  // most steps of a time loop in one launch: bounds how long it holds the device
 constexpr int kGlobalT = 256;  // workgroup of groups whose image lives in the workspace
 
 inline LdsLayout layout_of(const KGroup& g) {
@@ -245,6 +246,25 @@ hipError_t launch_flow(const hines_plan* p, const RhsSpec& rs, const MT* d, cons
   return hipSuccess;
 }
 
+// nsteps steps of the flow groups in one launch per kind of bin
+hipError_t launch_flow_loop(const hines_plan* p, const hdev::FlowRun& L, bool noise, const double* d, const double* u,
+                            hipStream_t s) {
+  for (const hines::FlowLaunch& B : p->flow_launches) {
+    DevTables t = p->t;
+    t.fjob = p->t.fjob + B.first;
+    const dim3 grid((unsigned)B.bins), block((unsigned)(64 * B.width));
+    if (noise)
+      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowNoise>, grid, block, B.lds_bytes, s, t, L, d, u);
+    else if (L.icur)
+      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowCVI>, grid, block, B.lds_bytes, s, t, L, d, u);
+    else
+      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowCV>, grid, block, B.lds_bytes, s, t, L, d, u);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // one instantiation of the resident kernel per LDS class (plane stride S)
 template <int C>
 void launch_res_class(const DevTables& t, int32_t count, const double* d, const double* u, const double* b, double* x,
@@ -306,6 +326,24 @@ hipError_t launch_resident(const hines_plan* p, const double* d, const double* u
   return e;
 }
 
+// the groups without a step schedule, level by level
+hipError_t launch_levels(const hines_plan* p, const RhsSpec& rs, const double* d, const double* u, double* x,
+                         hipStream_t s) {
+  for (const auto& bk : p->buckets) {
+    if (bk.count == 0) continue;
+    switch (p->host.opt.group_width) {
+      case 64: launch_bucket<64>(p, bk, rs, d, u, x, s); break;
+      case 128: launch_bucket<128>(p, bk, rs, d, u, x, s); break;
+      case 256: launch_bucket<256>(p, bk, rs, d, u, x, s); break;
+      case 512: launch_bucket<512>(p, bk, rs, d, u, x, s); break;
+      default: launch_bucket<1024>(p, bk, rs, d, u, x, s); break;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d, const double* u, double* x,
                         hipStream_t s) {
   if (p->host.res.built && rs.mode == hdev::kRhsGiven) return launch_resident(p, d, u, rs.rhs, x, s);
@@ -333,21 +371,8 @@ hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d,
       hipLaunchKernelGGL(hdev::k_solve_cells<hdev::kFlowCV>, grid, dim3(64), 0, s, p->t, rs, d, u, x);
     return hipGetLastError();
   }
-  hipError_t ef = launch_flow(p, rs, d, u, x, s);
-  if (ef != hipSuccess) return ef;
-  for (const auto& bk : p->buckets) {
-    if (bk.count == 0) continue;
-    switch (p->host.opt.group_width) {
-      case 64: launch_bucket<64>(p, bk, rs, d, u, x, s); break;
-      case 128: launch_bucket<128>(p, bk, rs, d, u, x, s); break;
-      case 256: launch_bucket<256>(p, bk, rs, d, u, x, s); break;
-      case 512: launch_bucket<512>(p, bk, rs, d, u, x, s); break;
-      default: launch_bucket<1024>(p, bk, rs, d, u, x, s); break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  const hipError_t e = launch_flow(p, rs, d, u, x, s);
+  return e == hipSuccess ? launch_levels(p, rs, d, u, x, s) : e;
 }
 
 // What a refined solve converges to is the FP64 solution of the widened
@@ -399,6 +424,9 @@ hipError_t allow_lds_t() {
 hipError_t allow_lds(int T) {
   const void* fns[] = {(const void*)hdev::k_solve_flow<hdev::kFlowGiven, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowGiven, float>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowCV>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowCVI>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowNoise>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCV, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCVI, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowNoise, double>,
@@ -1313,8 +1341,20 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     L.sigma = noise_sigma;
     L.seed = noise_seed;
   }
-  hipStream_t cs = nullptr;
+  // flow groups: whole stretches of steps in LDS; the plan's other groups, and
+  // every other plan, one step after the other.  The two kinds of groups share
+  // no cell, so they are two branches of the graph.
+  const bool flow = !factored && !p->host.sq.built && !p->host.cl.built && !p->flow_launches.empty();
+  const bool fork = flow && !p->buckets.empty();
+  hipStream_t cs = nullptr, fs = nullptr;
+  hipEvent_t forked = nullptr, joined = nullptr;
   hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+  if (fork && e == hipSuccess) {
+    e = hipStreamCreateWithFlags(&fs, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&forked, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&joined, hipEventDisableTiming);
+  }
+  const hipStream_t ls = fork ? fs : cs;  // the step-by-step branch
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   const bool capturing = e == hipSuccess;
   if (factored && e == hipSuccess) {
@@ -1340,7 +1380,16 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     hipLaunchKernelGGL(hdev::k_cells_from_walk, grid, dim3(64), 0, cs, p->t, (const double*)L.v, v);
     e = hipGetLastError();
   }
-  for (int32_t k = 0; k < nsteps && e == hipSuccess && p->host.n > 0 && !factored; ++k) {
+  if (fork && e == hipSuccess) {
+    e = hipEventRecord(forked, cs);
+    if (e == hipSuccess) e = hipStreamWaitEvent(ls, forked, 0);
+  }
+  for (int32_t k = 0; k < nsteps && e == hipSuccess && flow; k += kLoopStretch) {
+    hdev::FlowRun R{c, v, i_inj, v, noise_sigma, noise_seed, first_step + (uint32_t)k,
+                    std::min(kLoopStretch, nsteps - k), 0};
+    e = launch_flow_loop(p, R, noise, diag, upper, cs);
+  }
+  for (int32_t k = 0; k < nsteps && e == hipSuccess && !factored; ++k) {
     RhsSpec rs{};
     rs.c = c;
     rs.v = v;
@@ -1348,14 +1397,22 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     rs.sigma = noise_sigma;
     rs.seed = noise_seed;
     rs.step = first_step + (uint32_t)k;
-    rs.mode = (i_inj == nullptr && noise_sigma != 0.0) ? hdev::kRhsNoise : hdev::kRhsCV;
-    e = launch_solve(p, rs, diag, upper, v, cs);
+    rs.mode = noise ? hdev::kRhsNoise : hdev::kRhsCV;
+    e = flow ? launch_levels(p, rs, diag, upper, v, ls) : launch_solve(p, rs, diag, upper, v, cs);
+  }
+  if (fork && capturing) {  // also after an error: a capture ends on its first stream with every branch joined
+    hipError_t e2 = hipEventRecord(joined, ls);
+    if (e2 == hipSuccess) e2 = hipStreamWaitEvent(cs, joined, 0);
+    if (e == hipSuccess) e = e2;
   }
   if (capturing) {
     hipError_t e2 = hipStreamEndCapture(cs, &tl->graph);
     if (e == hipSuccess) e = e2;
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&tl->exec, tl->graph, nullptr, nullptr, 0);
+  if (fs) hipStreamDestroy(fs);
+  if (forked) hipEventDestroy(forked);
+  if (joined) hipEventDestroy(joined);
   if (cs) hipStreamDestroy(cs);
   if (e != hipSuccess) {
     if (tl->exec) hipGraphExecDestroy(tl->exec);

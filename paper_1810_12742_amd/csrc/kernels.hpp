@@ -636,6 +636,11 @@ constexpr int kStageUnroll = RHS == kFlowGiven ? 10 : RHS == kFlowNoise ? 6 : 7;
 template <int RHS>
 constexpr int kStageBatch = 64 * kStageUnroll<RHS>;
 
+// Right-hand side of a step, the same rounding in the one-step and in the
+// looping kernel: c v, or c v + i in one rounding.
+__device__ __forceinline__ double flow_rhs(double c, double v) { return c * v; }
+__device__ __forceinline__ double flow_rhs(double c, double v, double i) { return __builtin_fma(c, v, i); }
+
 // Register set of one batch: positions, matrix, right-hand side ingredients.
 template <int RHS, typename MT>
 struct FlowBatch {
@@ -673,10 +678,11 @@ __device__ __forceinline__ void flow_batch_put(const FlowBatch<RHS, MT>& S, cons
 #pragma unroll
   for (int k = 0; k < kStageUnroll<RHS>; ++k) {
     double b = S.b[k];
-    if constexpr (RHS != kFlowGiven) b = S.c[k] * S.b[k];
-    if constexpr (RHS == kFlowCVI) b = b + S.i[k];
+    if constexpr (RHS == kFlowCV) b = flow_rhs(S.c[k], S.b[k]);
+    if constexpr (RHS == kFlowCVI) b = flow_rhs(S.c[k], S.b[k], S.i[k]);
     if constexpr (RHS == kFlowNoise)
-      b = b + noise_draw(rs.seed, rs.step, (uint64_t)(lo + min(e0 + 64 * k + lane, n - 1)), rs.sigma);
+      b = flow_rhs(S.c[k], S.b[k],
+                   noise_draw(rs.seed, rs.step, (uint64_t)(lo + min(e0 + 64 * k + lane, n - 1)), rs.sigma));
     lds_f64* q = img + (int)(S.p[k] & 0x7fffu);
     q[0] = (double)S.d[k];
     q[1] = (S.p[k] & 0x8000u) ? 0.0 : (double)S.u[k];
@@ -788,6 +794,8 @@ struct FlowBwd {
 // t + 1 are read from LDS, and the KC sub-steps of t are eliminated.  Two
 // register sets are used in turn, so that no step ends by copying (and so
 // waiting for) the operands read during it.
+// KEEP: 1 / d' is stored over u, for the steps that reuse the factors.
+template <bool KEEP = false>
 __device__ __forceinline__ void flow_backward(const FlowImage& I) {
   lds_f64* img = I.img;
   const int F = I.F;
@@ -820,6 +828,7 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
       const double r = rcp_nr(dl);
       const double f = C.u[j] * r;
       img[wb + 3 * j] = f;
+      if constexpr (KEEP) img[wb + 3 * j + 1] = r;
       img[wb + 3 * j + 2] = bl * r;
       fin = f;
       uin = C.u[j];
@@ -829,6 +838,55 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
       lds_add(img + C.q, -(fin * uin));
       lds_add(img + C.q + 2, -(fin * bin));
     }
+    fin = lane_in(M & ~E) ? fin : 0.0;
+    M = M1;
+    E = E1;
+  };
+  FlowBwd S0, S1;
+  load(S0, M, E, 0, 0);
+  for (int t = 0; t < F; t += 2) {
+    step(t, S0, S1);
+    if (t + 1 >= F) break;
+    step(t + 1, S1, S0);
+  }
+}
+
+// Backward sweep of the right-hand side alone, on an image that holds
+// (f, 1 / d', b): y = b' / d' over b, the contributions f b' as in the sweep
+// that formed the factors, so the solution is the same bit for bit.
+__device__ __forceinline__ void flow_backward_kept(const FlowImage& I) {
+  lds_f64* img = I.img;
+  const int F = I.F;
+  const u32x4 m0 = I.msk[0];
+  uint64_t M = first_u64(m0.x, m0.y), E = first_u64(m0.z, m0.w);
+  u32x4 mv = I.msk[1];
+  int R = 0, A = 0;
+  double fin = 0.0, bin = 0.0;
+  auto load = [&](FlowBwd& S, uint64_t m, uint64_t e, int r, int a) {
+    S.rb = flow_block(I, m, r);
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      S.d[j] = img[S.rb + 3 * j];      // f
+      S.u[j] = img[S.rb + 3 * j + 1];  // 1 / d'
+      S.b[j] = img[S.rb + 3 * j + 2];
+    }
+    S.q = I.aux[min(rank_in(e, a), I.last_aux)];
+  };
+  auto step = [&](int t, FlowBwd& C, FlowBwd& N) {
+    const uint64_t M1 = first_u64(mv.x, mv.y), E1 = first_u64(mv.z, mv.w);
+    mv = I.msk[t + 2 <= F ? t + 2 : F];
+    R += __builtin_popcountll(M);
+    A += __builtin_popcountll(E);
+    load(N, M1, E1, R, A);
+    const int wb = lane_in(M) ? C.rb : I.sink;
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      const double bl = __builtin_fma(-fin, bin, C.b[j]);
+      img[wb + 3 * j + 2] = bl * C.u[j];
+      fin = C.d[j];
+      bin = bl;
+    }
+    if (lane_in(E)) lds_add(img + C.q + 2, -(fin * bin));
     fin = lane_in(M & ~E) ? fin : 0.0;
     M = M1;
     E = E1;
@@ -971,6 +1029,171 @@ __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, co
       flow_store_from<RHS>(x + C.user_lo, C.n, pos + q, I.img, 0, lane);
       q += C.n;
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Time loop of the flow groups: nsteps implicit-Euler steps V <- A^-1 (c V + I)
+// of a group in one stay in LDS (the cells are independent of each other, so a
+// group needs nothing from outside between its steps).  The first step is
+// k_solve_flow's and leaves (f, 1 / d') in the image; every further step forms
+// its right-hand side in place of x (all lanes busy, c and I from registers
+// for the first NK elements of a lane and streamed for the rest), sweeps it
+// backwards with the kept factors and substitutes forwards.
+//
+// Bound by the serial length of a group like k_solve_flow, without its
+// staging, divisions and store: per step and group about 450 + 450 cycles a
+// chunk step.  100 steps of 257 C2 cells with a current take 1.77 ms, 3.15 ms as
+// 100 launches of k_solve_flow.
+// ---------------------------------------------------------------------------
+struct FlowRun {
+  const double* c;
+  const double* v_in;
+  const double* icur;  // kFlowCVI
+  double* v_out;       // may be v_in
+  double sigma;        // kFlowNoise
+  uint32_t seed, step;
+  int32_t nsteps, pad;
+};
+
+template <int RHS>
+constexpr int kLoopKeep = RHS == kFlowCVI ? 16 : RHS == kFlowNoise ? 10 : 24;  // elements of a lane whose c (and I) stay in registers
+template <int RHS>
+constexpr int kLoopBatch = RHS == kFlowCVI ? 4 : RHS == kFlowNoise ? 2 : 6;  // elements staged, and further ones handled, at a time
+
+template <int RHS>
+__global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, const double* __restrict__ d,
+                                                   const double* __restrict__ u) {
+  extern __shared__ __attribute__((aligned(16))) char flow_raw[];
+  constexpr int NK = kLoopKeep<RHS>, NB = kLoopBatch<RHS>;
+  static_assert(NK % NB == 0, "the kept elements are staged in whole batches");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const hines::KFlowJob J = tb.fjob[blockIdx.x * (blockDim.x >> 6) + wave];
+  if (J.nstep == 0) return;  // an empty place of the bin
+  const FlowImage I = flow_image(J, flow_raw, lane);
+  lds_f64* img = I.img;
+  const uint16_t* pos = tb.fpos + J.pos_off;
+  const int n = J.nelem;
+  flow_stage_tables(tb, J, I, flow_raw, lane);
+  flow_clear(J, I, lane);
+
+  // what one element's right-hand side needs besides its state
+  struct Src {
+    uint32_t p;  // position; past the end of a range: the lane's sink, so that no LDS access is masked
+    double c, i;
+  };
+  auto source = [&](int64_t lo, int m, const uint16_t* ps, int e) {
+    Src s;
+    const int ec = min(e, m - 1);
+    s.p = e < m ? (uint32_t)ps[ec] : (uint32_t)I.sink;
+    s.c = (L.c + lo)[ec];
+    s.i = 0.0;
+    if constexpr (RHS == kFlowCVI) s.i = (L.icur + lo)[ec];
+    return s;
+  };
+  auto rhs = [&](const Src& s, double v, uint32_t step, int64_t i) {
+    if constexpr (RHS == kFlowCV) return flow_rhs(s.c, v);
+    if constexpr (RHS == kFlowCVI) return flow_rhs(s.c, v, s.i);
+    return flow_rhs(s.c, v, noise_draw(L.seed, step, (uint64_t)i, L.sigma));
+  };
+  // NB elements of a range into the image
+  auto stage = [&](int64_t lo, int m, int e0, const Src* s) {
+    double dv[NB], uv[NB], vv[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int e = min(e0 + 64 * k + lane, m - 1);
+      dv[k] = (d + lo)[e];
+      uv[k] = (u + lo)[e];
+      vv[k] = (L.v_in + lo)[e];
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int e = min(e0 + 64 * k + lane, m - 1);
+      lds_f64* q = img + (int)(s[k].p & 0x7fffu);
+      q[0] = dv[k];
+      q[1] = (s[k].p & 0x8000u) ? 0.0 : uv[k];
+      q[2] = rhs(s[k], vv[k], L.step, lo + e);
+    }
+    if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);  // at most NB draws in flight: registers
+  };
+  // NB elements: x of the finished step out (last step), or the next right-hand side over it
+  auto turn = [&](int64_t lo, int m, int e0, const Src* s, uint32_t step, bool last) {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int e = e0 + 64 * k + lane;
+      lds_f64* q = img + (int)(s[k].p & 0x7fffu) + 2;
+      const double x = *q;
+      if (last) {
+        if (e < m) (L.v_out + lo)[e] = x;
+      } else {
+        *q = rhs(s[k], x, step, lo + min(e, m - 1));
+      }
+    }
+    if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);
+  };
+  // every element beyond the kept ones (all of them if the group is not one range)
+  auto streamed = [&](auto&& f) {
+    auto range = [&](int64_t lo, int m, const uint16_t* ps, int e0) {
+      if (e0 >= m) return;
+      // two register sets in turn: the next batch is in flight during this one
+      // (past the end of the range it is loaded clamped and not used)
+      Src s0[NB], s1[NB];
+      auto load = [&](Src* s, int e) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) s[k] = source(lo, m, ps, e + 64 * k + lane);
+      };
+      load(s0, e0);
+      for (;;) {
+        load(s1, e0 + 64 * NB);
+        f(lo, m, e0, s0);
+        e0 += 64 * NB;
+        if (e0 >= m) break;
+        load(s0, e0 + 64 * NB);
+        f(lo, m, e0, s1);
+        e0 += 64 * NB;
+        if (e0 >= m) break;
+      }
+    };
+    if (J.ncell == 0) {
+      range(J.user_lo, n, pos, 64 * NK);
+    } else {
+      int q = 0;
+      for (int c = 0; c < J.ncell; ++c) {
+        const KCell C = tb.cell[J.cell_begin + c];
+        range(C.user_lo, C.n, pos + q, 0);
+        q += C.n;
+      }
+    }
+  };
+
+  Src keep[NK];
+  if (J.ncell == 0) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) keep[k] = source(J.user_lo, n, pos, 64 * k + lane);
+#pragma unroll
+    for (int k = 0; k < NK; k += NB)
+      if (64 * k < n) stage(J.user_lo, n, 64 * k, keep + k);
+  }
+  streamed(stage);
+  __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
+  __builtin_amdgcn_wave_barrier();
+  flow_backward<true>(I);
+  for (int it = 1;; ++it) {
+    __builtin_amdgcn_wave_barrier();
+    flow_forward(I);
+    __builtin_amdgcn_wave_barrier();
+    const bool last = it == L.nsteps;
+    const uint32_t step = L.step + (uint32_t)it;
+    if (J.ncell == 0) {
+#pragma unroll
+      for (int k = 0; k < NK; k += NB)
+        if (64 * k < n) turn(J.user_lo, n, 64 * k, keep + k, step, last);
+    }
+    streamed([&](int64_t lo, int m, int e0, const Src* s) { turn(lo, m, e0, s, step, last); });
+    if (last) break;
+    __builtin_amdgcn_wave_barrier();
+    flow_backward_kept(I);
   }
 }
 

@@ -94,3 +94,51 @@ def test_refined_solve_of_scheduled_and_level_groups(comb, sweeps):
         if comb and sweeps == 3:
             assert err[40] <= 1e-11
     p.close()
+
+
+# Captured loops against the same steps one by one, bit for bit, and against the
+# oracle's loop.  Sizes around the elements that a lane keeps in registers (640
+# with noise, 1,024 with a current, 1,536 without), several cells in a group,
+# groups that are not one user range, loops of more than one launch (256 steps).
+@pytest.mark.parametrize("form", ["cv", "current", "noise"])
+@pytest.mark.parametrize("sizes,steps,opts", [
+    ([640], 3, {}), ([641], 2, {}), ([1024, 1025], 3, {}), ([1536, 1537, 2100], 2, {}),
+    ([1] * 130 + [40] * 30, 5, {}), ([30, 900, 31, 1700, 60] * 60, 3, dict(cell_order=1)),
+    ([25, 300], 256, {}), ([25, 300], 257, {}), ([300], 1, {})])
+def test_captured_loop_equals_single_steps(form, sizes, steps, opts):
+    import torch
+    from paper_1810_12742_amd import Plan
+    sizes = np.asarray(sizes, dtype=np.int64)
+    f = grow_random_forest(np.random.default_rng(31), len(sizes), target_size=sizes)
+    s = cable_values(f, np.random.default_rng(32), a_kind="cable", dt=0.025)
+    p = Plan(f.parent, f.cell_offsets, f.branch_offsets, **opts)
+    assert p.info["kernel"] == 1
+    dev = torch.device("cuda")
+    d, u, c, v0 = (torch.from_numpy(a).to(dev) for a in (s.diag, s.upper, s.c, s.rhs))
+    I = 0.1 * np.random.default_rng(33).standard_normal(f.n)
+    kw = dict(cv={}, current=dict(i_inj=torch.from_numpy(I).to(dev)), noise=dict(noise_sigma=0.1, noise_seed=3))[form]
+    want = v0.clone()
+    for k in range(2 * steps):
+        # the second launch replays the steps of the first
+        p.timestep(d, u, c, want, want, step=4 + k % steps, **kw)
+        if k == steps - 1:
+            first = want.cpu().numpy()
+    v = v0.clone()
+    loop = p.timeloop(d, u, c, v, steps, first_step=4, **kw)
+    loop.launch()
+    assert np.array_equal(v.cpu().numpy(), first)
+    _ = (d * 2).sum().item()
+    loop.launch()
+    assert np.array_equal(v.cpu().numpy(), want.cpu().numpy())
+    loop.close()
+    ref = s.rhs
+    for k in range(steps):
+        rhs = s.c * ref
+        if form == "current":
+            rhs = rhs + I
+        elif form == "noise":
+            rhs = rhs + oracle.noise(3, 4 + k, np.arange(f.n, dtype=np.int64), 0.1)
+        ref = oracle.solve(f, s.diag, s.upper, rhs)
+    err = np.maximum.reduceat(np.abs(first - ref), f.cell_offsets[:-1])
+    assert np.max(err / np.maximum.reduceat(np.abs(ref), f.cell_offsets[:-1])) <= TOL
+    p.close()
