@@ -375,6 +375,32 @@ hines_status hines_adjoint_rhs(hines_plan* plan, const double* c, const double* 
 hines_status hines_adjoint_accumulate(hines_plan* plan, const double* lam, const double* v, const double* v_prev,
                                       double* grad_a, double* grad_c, double* grad_i, void* stream);
 
+/* Several steps of the time loop and of its adjoint in one call (what a fit
+ * to recorded traces runs between two checkpoints; paper §1).  On plans whose
+ * groups all have a step schedule (hines_plan_info.kernel == 1 and no
+ * workspace groups) the steps of a group run inside LDS; other plans run the
+ * single-step calls in turn.  All arrays are device arrays, async on stream.
+ *   hines_run_steps: nsteps steps with the constant current i_inj (NULL: none)
+ *     from v_in; the state after step k goes to states + k n (NULL: not kept),
+ *     the last one to v_out (may be v_in, may be NULL if states is given), the
+ *     cells' roots after step k to traces + k ncells (NULL: not kept).
+ *   hines_adjoint_steps: for k = nsteps - 1 down to 0,
+ *       A lams[k] = c lams[k + 1] + g_roots[k] at the cells' roots,
+ *     lams[nsteps] = lam_in (NULL: zero); lams has nsteps rows of n, g_roots
+ *     nsteps rows of ncells.
+ *   hines_adjoint_accumulate_steps: hines_adjoint_accumulate of step k on
+ *     (lams[k], states[k], states[k - 1]) for k = nsteps - 1 down to 0, with v0
+ *     before states[0]. */
+hines_status hines_run_steps(hines_plan* plan, const double* diag, const double* upper, const double* c,
+                             const double* v_in, const double* i_inj, int32_t nsteps, double* states, double* v_out,
+                             double* traces, int32_t ncells, void* stream);
+hines_status hines_adjoint_steps(hines_plan* plan, const double* diag, const double* upper, const double* c,
+                                 const double* lam_in, const double* g_roots, int32_t nsteps, double* lams,
+                                 int32_t ncells, void* stream);
+hines_status hines_adjoint_accumulate_steps(hines_plan* plan, const double* lams, const double* states,
+                                            const double* v0, int32_t nsteps, double* grad_a, double* grad_c,
+                                            double* grad_i, void* stream);
+
 /* The solver layout of a cell-lane plan (paper §7, Fig 7.1: the solver works
  * on a solver-specific data format; permutation kernels move data into it and
  * the solution out of it).  A compartment's slot is its step in the walk of

@@ -16,13 +16,18 @@ States are checkpointed every ``checkpoint_every`` steps and recomputed one
 segment at a time during the backward pass; the kernels are deterministic,
 so the recomputed states equal the forward ones bit for bit.
 
-All arithmetic runs in the library's kernels (hines_assemble, hines_timestep,
-hines_gather_roots, hines_adjoint_rhs, hines_solve, hines_adjoint_accumulate);
-torch provides the device buffers.
+All arithmetic runs in the library's kernels (hines_assemble, hines_run_steps,
+hines_adjoint_steps, hines_adjoint_accumulate_steps); torch provides the device
+buffers.
 """
 from __future__ import annotations
 
 import torch
+
+# adjoint steps between two accumulations: bounds the adjoint states kept at a
+# time whatever the checkpoint distance (16 steps of a launch against 10 or 100
+# differ by the first step's elimination, a few percent)
+ADJOINT_ROWS = 16
 
 
 class _SomaTraces(torch.autograd.Function):
@@ -34,12 +39,14 @@ class _SomaTraces(torch.autograd.Function):
         diag, upper = plan.assemble(a, c)
         V = torch.zeros_like(c)
         traces = torch.empty(steps, plan.ncells, dtype=torch.float64, device=c.device)
-        ckpts = [V.clone()]
-        for k in range(1, steps + 1):
-            plan.timestep(diag, upper, c, V, V, i_inj=I, step=k - 1)
-            plan.gather_roots(V, out=traces[k - 1])
-            if k % checkpoint_every == 0 and k < steps:
-                ckpts.append(V.clone())
+        ckpts = [V]
+        for k0 in range(0, steps, checkpoint_every):
+            k1 = min(k0 + checkpoint_every, steps)
+            nxt = torch.empty_like(c)
+            plan.run_steps(diag, upper, c, V, k1 - k0, i_inj=I, v_out=nxt, traces=traces[k0:k1])
+            V = nxt
+            if k1 < steps:
+                ckpts.append(V)
         ctx.plan = plan
         ctx.steps = steps
         ctx.every = checkpoint_every
@@ -54,21 +61,23 @@ class _SomaTraces(torch.autograd.Function):
         ga = torch.zeros_like(c)
         gc = torch.zeros_like(c)
         gi = torch.zeros_like(c)
-        lam_next = None
+        n = c.numel()
+        states_buf = torch.empty(min(every, steps), n, dtype=c.dtype, device=c.device)
+        lams_buf = torch.empty(min(every, steps, ADJOINT_ROWS), n, dtype=c.dtype, device=c.device)
+        lam = None
         nseg = (steps + every - 1) // every
         for s in range(nseg - 1, -1, -1):
             k0 = s * every
             k1 = min(k0 + every, steps)
-            states = [ckpts[s]]
-            V = ckpts[s].clone()
-            for k in range(k0 + 1, k1 + 1):
-                plan.timestep(diag, upper, c, V, V, i_inj=I, step=k - 1)
-                states.append(V.clone())
-            for k in range(k1, k0, -1):
-                mu = plan.adjoint_rhs(c, lam_next, G[k - 1])
-                lam = plan.solve(diag, upper, mu)
-                plan.adjoint_accumulate(lam, states[k - k0], states[k - 1 - k0], ga, gc, gi)
-                lam_next = lam
+            states = states_buf[:k1 - k0]
+            plan.run_steps(diag, upper, c, ckpts[s], k1 - k0, i_inj=I, states=states)
+            for e in range(k1, k0, -ADJOINT_ROWS):
+                b = max(e - ADJOINT_ROWS, k0)
+                lams = lams_buf[:e - b]
+                plan.adjoint_steps(diag, upper, c, lam, G[b:e], lams)
+                v0 = ckpts[s] if b == k0 else states[b - k0 - 1]
+                plan.adjoint_accumulate_steps(lams, states[b - k0:e - k0], v0, ga, gc, gi)
+                lam = lams[0].clone()
         return ga, gc, gi, None, None, None
 
 

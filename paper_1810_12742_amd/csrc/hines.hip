@@ -246,23 +246,26 @@ hipError_t launch_flow(const hines_plan* p, const RhsSpec& rs, const MT* d, cons
   return hipSuccess;
 }
 
-// nsteps steps of the flow groups in one launch per kind of bin
-hipError_t launch_flow_loop(const hines_plan* p, const hdev::FlowRun& L, bool noise, const double* d, const double* u,
-                            hipStream_t s) {
+// the steps of a FlowRun for all flow groups, one launch per kind of bin
+template <int RHS, bool OUT>
+hipError_t launch_flow_run(const hines_plan* p, const hdev::FlowRun& L, const double* d, const double* u,
+                           hipStream_t s) {
   for (const hines::FlowLaunch& B : p->flow_launches) {
     DevTables t = p->t;
     t.fjob = p->t.fjob + B.first;
-    const dim3 grid((unsigned)B.bins), block((unsigned)(64 * B.width));
-    if (noise)
-      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowNoise>, grid, block, B.lds_bytes, s, t, L, d, u);
-    else if (L.icur)
-      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowCVI>, grid, block, B.lds_bytes, s, t, L, d, u);
-    else
-      hipLaunchKernelGGL(hdev::k_flow_loop<hdev::kFlowCV>, grid, block, B.lds_bytes, s, t, L, d, u);
+    hipLaunchKernelGGL((hdev::k_flow_loop<RHS, OUT>), dim3((unsigned)B.bins), dim3((unsigned)(64 * B.width)),
+                       B.lds_bytes, s, t, L, d, u);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// hines_solve and hines_timestep run on the group kernels, and every group has
+// a step schedule: whole stretches of steps can stay in LDS
+bool flow_only(const hines_plan* p) {
+  return !p->host.cl.built && !p->host.sq.built && !p->host.res.built && !p->flow_launches.empty() &&
+         p->buckets.empty();
 }
 
 // one instantiation of the resident kernel per LDS class (plane stride S)
@@ -427,6 +430,9 @@ hipError_t allow_lds(int T) {
                        (const void*)hdev::k_flow_loop<hdev::kFlowCV>,
                        (const void*)hdev::k_flow_loop<hdev::kFlowCVI>,
                        (const void*)hdev::k_flow_loop<hdev::kFlowNoise>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowCV, true>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowCVI, true>,
+                       (const void*)hdev::k_flow_loop<hdev::kFlowAdjoint, true>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCV, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCVI, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowNoise, double>,
@@ -1386,8 +1392,10 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   }
   for (int32_t k = 0; k < nsteps && e == hipSuccess && flow; k += kLoopStretch) {
     hdev::FlowRun R{c, v, i_inj, v, noise_sigma, noise_seed, first_step + (uint32_t)k,
-                    std::min(kLoopStretch, nsteps - k), 0};
-    e = launch_flow_loop(p, R, noise, diag, upper, cs);
+                    std::min(kLoopStretch, nsteps - k), 0, nullptr, nullptr, nullptr, 0, 0};
+    e = noise   ? launch_flow_run<hdev::kFlowNoise, false>(p, R, diag, upper, cs)
+        : i_inj ? launch_flow_run<hdev::kFlowCVI, false>(p, R, diag, upper, cs)
+                : launch_flow_run<hdev::kFlowCV, false>(p, R, diag, upper, cs);
   }
   for (int32_t k = 0; k < nsteps && e == hipSuccess && !factored; ++k) {
     RhsSpec rs{};
@@ -1494,17 +1502,101 @@ hines_status hines_adjoint_rhs(hines_plan* p, const double* c, const double* lam
 
 hines_status hines_adjoint_accumulate(hines_plan* p, const double* lam, const double* v, const double* v_prev,
                                       double* grad_a, double* grad_c, double* grad_i, void* stream) {
+  return hines_adjoint_accumulate_steps(p, lam, v, v_prev, 1, grad_a, grad_c, grad_i, stream);
+}
+
+hines_status hines_adjoint_accumulate_steps(hines_plan* p, const double* lams, const double* states, const double* v0,
+                                            int32_t nsteps, double* grad_a, double* grad_c, double* grad_i,
+                                            void* stream) {
   hines_status st = check_call(p, p ? (int32_t)p->host.ncells : 0);
   if (st != HINES_OK) return st;
+  if (nsteps < 1) return set_err(HINES_ERR_OPTION, "nsteps must be >= 1");
   if (p->host.n == 0) return ok();
-  if (!lam || !v || !v_prev || !grad_a || !grad_c || !grad_i)
+  if (!lams || !states || !v0 || !grad_a || !grad_c || !grad_i)
     return set_err(HINES_ERR_NULL, "a device array is NULL");
   st = ensure_adjoint_tables(p);
   if (st != HINES_OK) return st;
   const int64_t n = p->host.n;
-  hipLaunchKernelGGL(hdev::k_adjoint_accumulate, grid_for(n, 256), dim3(256), 0, (hipStream_t)stream, n,
-                     p->d_parent, lam, v, v_prev, grad_a, grad_c, grad_i);
+  hipLaunchKernelGGL(hdev::k_adjoint_accumulate, grid_for(n, 256), dim3(256), 0, (hipStream_t)stream, n, nsteps,
+                     p->d_parent, lams, states, v0, grad_a, grad_c, grad_i);
   return launched();
+}
+
+hines_status hines_run_steps(hines_plan* p, const double* diag, const double* upper, const double* c,
+                             const double* v_in, const double* i_inj, int32_t nsteps, double* states, double* v_out,
+                             double* traces, int32_t ncells, void* stream) {
+  hines_status st = check_call(p, ncells);
+  if (st != HINES_OK) return st;
+  if (nsteps < 1) return set_err(HINES_ERR_OPTION, "nsteps must be >= 1");
+  if (p->host.n == 0) return ok();
+  if (!diag || !upper || !c || !v_in || (!states && !v_out)) return set_err(HINES_ERR_NULL, "a device array is NULL");
+  for (const void* o : {(const void*)states, (const void*)v_out})
+    if (o && (o == diag || o == upper || o == c || o == i_inj))
+      return set_err(HINES_ERR_STATE, "an output must not alias the matrix, c or the current");
+  if (states && (states == v_in || states == v_out))
+    return set_err(HINES_ERR_STATE, "states must not alias v_in or v_out");
+  const hipStream_t s = (hipStream_t)stream;
+  const int64_t n = p->host.n;
+  if (flow_only(p)) {
+    for (int32_t k = 0; k < nsteps; k += kLoopStretch) {
+      const int32_t m = std::min(kLoopStretch, nsteps - k);
+      const double* from = k == 0 ? v_in : states ? states + (k - 1) * n : v_out;
+      // without rows to continue from, a stretch leaves its state in v_out
+      double* to = k + m == nsteps || !states ? v_out : nullptr;
+      hdev::FlowRun R{c, from, i_inj, to, 0.0, 0u, 0u, m, 0, states ? states + k * n : nullptr,
+                      traces ? traces + (int64_t)k * ncells : nullptr, nullptr, n, ncells};
+      const hipError_t e = i_inj ? launch_flow_run<hdev::kFlowCVI, true>(p, R, diag, upper, s)
+                                 : launch_flow_run<hdev::kFlowCV, true>(p, R, diag, upper, s);
+      if (e != hipSuccess) return set_err(HINES_ERR_HIP, "launch: %s", hipGetErrorString(e));
+    }
+    return ok();
+  }
+  const double* from = v_in;
+  for (int32_t k = 0; k < nsteps; ++k) {
+    double* to = states ? states + k * n : v_out;
+    st = hines_timestep(p, diag, upper, c, from, to, i_inj, 0.0, 0u, (uint32_t)k, ncells, stream);
+    if (st == HINES_OK && traces) st = hines_gather_roots(p, to, traces + (int64_t)k * ncells, stream);
+    if (st != HINES_OK) return st;
+    from = to;
+  }
+  if (states && v_out) {
+    const hipError_t e = hipMemcpyAsync(v_out, from, 8 * (size_t)n, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return set_err(HINES_ERR_HIP, "copy: %s", hipGetErrorString(e));
+  }
+  return ok();
+}
+
+hines_status hines_adjoint_steps(hines_plan* p, const double* diag, const double* upper, const double* c,
+                                 const double* lam_in, const double* g_roots, int32_t nsteps, double* lams,
+                                 int32_t ncells, void* stream) {
+  hines_status st = check_call(p, ncells);
+  if (st != HINES_OK) return st;
+  if (nsteps < 1) return set_err(HINES_ERR_OPTION, "nsteps must be >= 1");
+  if (p->host.n == 0) return ok();
+  if (!diag || !upper || !c || !g_roots || !lams) return set_err(HINES_ERR_NULL, "a device array is NULL");
+  for (const void* o : {(const void*)diag, (const void*)upper, (const void*)c, (const void*)lam_in})
+    if (o == lams) return set_err(HINES_ERR_STATE, "lams must not alias an input");
+  const int64_t n = p->host.n;
+  const double* from = lam_in;
+  int32_t k = nsteps - 1;
+  // the last step starts from no adjoint when lam_in is NULL: a solve of its own
+  for (; k >= 0 && (!from || !flow_only(p)); --k) {
+    double* mu = lams + k * n;
+    st = hines_adjoint_rhs(p, c, from, g_roots + (int64_t)k * ncells, mu, stream);
+    if (st == HINES_OK) st = hines_solve(p, diag, upper, mu, mu, ncells, stream);
+    if (st != HINES_OK) return st;
+    from = mu;
+  }
+  while (k >= 0) {
+    const int32_t m = std::min(kLoopStretch, k + 1);
+    hdev::FlowRun R{c, from, nullptr, nullptr, 0.0, 0u, 0u, m, 0, lams + k * n, nullptr,
+                    g_roots + (int64_t)k * ncells, -n, -(int64_t)ncells};
+    const hipError_t e = launch_flow_run<hdev::kFlowAdjoint, true>(p, R, diag, upper, (hipStream_t)stream);
+    if (e != hipSuccess) return set_err(HINES_ERR_HIP, "launch: %s", hipGetErrorString(e));
+    k -= m;
+    from = lams + (k + 1) * n;
+  }
+  return ok();
 }
 
 hines_status hines_layout_size(const hines_plan* p, int64_t* slots) {

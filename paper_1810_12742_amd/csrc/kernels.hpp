@@ -623,6 +623,9 @@ enum : int { kCellFactor = 4 };
 // a = -u (paper §1) while it eliminates, with b = c v + g E.  The d argument
 // carries g and rs.icur carries g E.
 enum : int { kCellCond = 5 };
+// Flow loop only: the adjoint step's right-hand side, c lambda plus a given
+// value at each cell's root.
+enum : int { kFlowAdjoint = 6 };
 
 // Element e of a user range (user index lo + e) -> its position.  A lane
 // handles elements lane, lane + 64, ... in batches of kStageUnroll<RHS>; all loads
@@ -986,13 +989,13 @@ __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, co
   // the first two batches are in flight together, and the image is cleared
   // meanwhile; their positions stay in registers for the store
   FlowBatch<RHS, MT> S0, S1;
-  if (J.ncell == 0) {
+  if (J.contig) {
     flow_batch_load(S0, rs, d, u, J.user_lo, n, pos, 0, lane);
     if (n > kStageBatch<RHS>) flow_batch_load(S1, rs, d, u, J.user_lo, n, pos, kStageBatch<RHS>, lane);
   }
   flow_stage_tables(tb, J, I, flow_raw, lane);
   flow_clear(J, I, lane);
-  if (J.ncell == 0) {
+  if (J.contig) {
     flow_batch_put(S0, rs, J.user_lo, n, I.img, 0, lane);
     if (n > kStageBatch<RHS>) flow_batch_put(S1, rs, J.user_lo, n, I.img, kStageBatch<RHS>, lane);
     for (int e0 = 2 * kStageBatch<RHS>; e0 < n; e0 += kStageBatch<RHS>) {
@@ -1017,7 +1020,7 @@ __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, co
   __builtin_amdgcn_wave_barrier();
   flow_forward(I);
   __builtin_amdgcn_wave_barrier();
-  if (J.ncell == 0) {
+  if (J.contig) {
     double* xo = x + J.user_lo;
     flow_batch_store<RHS>(xo, n, S0.p, I.img, 0, lane);
     if (n > kStageBatch<RHS>) flow_batch_store<RHS>(xo, n, S1.p, I.img, kStageBatch<RHS>, lane);
@@ -1054,18 +1057,29 @@ struct FlowRun {
   double sigma;        // kFlowNoise
   uint32_t seed, step;
   int32_t nsteps, pad;
+  // OUT: what each step leaves behind, step k (0, 1, ...) in row k; either may
+  // be null.  Rows follow each other at the given strides (negative for steps
+  // that run backwards in time).
+  double* states;      // the state
+  double* traces;      // the root of each cell
+  const double* g;     // kFlowAdjoint: values at the roots, rows as traces
+  int64_t state_stride, root_stride;
 };
 
-template <int RHS>
-constexpr int kLoopKeep = RHS == kFlowCVI ? 16 : RHS == kFlowNoise ? 10 : 24;  // elements of a lane whose c (and I) stay in registers
-template <int RHS>
-constexpr int kLoopBatch = RHS == kFlowCVI ? 4 : RHS == kFlowNoise ? 2 : 6;  // elements staged, and further ones handled, at a time
+// Elements of a lane whose c (and I) stay in registers, and elements staged, or
+// handled beyond those, at a time: what 256 registers hold beside the sweeps.
+template <int RHS, bool OUT>
+constexpr int kLoopKeep = RHS == kFlowNoise ? 10 : (RHS == kFlowCVI || OUT) ? 16 : 24;
+template <int RHS, bool OUT>
+constexpr int kLoopBatch = (RHS == kFlowNoise || (RHS == kFlowCVI && OUT)) ? 2 : (RHS == kFlowCVI || OUT) ? 4 : 6;
 
-template <int RHS>
+// OUT: the states and root traces of every step are stored (the forward run of
+// a fit and its adjoint).
+template <int RHS, bool OUT = false>
 __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, const double* __restrict__ d,
                                                    const double* __restrict__ u) {
   extern __shared__ __attribute__((aligned(16))) char flow_raw[];
-  constexpr int NK = kLoopKeep<RHS>, NB = kLoopBatch<RHS>;
+  constexpr int NK = kLoopKeep<RHS, OUT>, NB = kLoopBatch<RHS, OUT>;
   static_assert(NK % NB == 0, "the kept elements are staged in whole batches");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1093,7 +1107,7 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
     return s;
   };
   auto rhs = [&](const Src& s, double v, uint32_t step, int64_t i) {
-    if constexpr (RHS == kFlowCV) return flow_rhs(s.c, v);
+    if constexpr (RHS == kFlowCV || RHS == kFlowAdjoint) return flow_rhs(s.c, v);
     if constexpr (RHS == kFlowCVI) return flow_rhs(s.c, v, s.i);
     return flow_rhs(s.c, v, noise_draw(L.seed, step, (uint64_t)i, L.sigma));
   };
@@ -1118,14 +1132,17 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
     if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);  // at most NB draws in flight: registers
   };
   // NB elements: x of the finished step out (last step), or the next right-hand side over it
-  auto turn = [&](int64_t lo, int m, int e0, const Src* s, uint32_t step, bool last) {
+  auto turn = [&](int64_t lo, int m, int e0, const Src* s, uint32_t step, bool last, double* row) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int e = e0 + 64 * k + lane;
       lds_f64* q = img + (int)(s[k].p & 0x7fffu) + 2;
       const double x = *q;
+      if constexpr (OUT) {
+        if (row && e < m) (row + lo)[e] = x;
+      }
       if (last) {
-        if (e < m) (L.v_out + lo)[e] = x;
+        if ((!OUT || L.v_out) && e < m) (L.v_out + lo)[e] = x;
       } else {
         *q = rhs(s[k], x, step, lo + min(e, m - 1));
       }
@@ -1155,7 +1172,7 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
         if (e0 >= m) break;
       }
     };
-    if (J.ncell == 0) {
+    if (J.contig) {
       range(J.user_lo, n, pos, 64 * NK);
     } else {
       int q = 0;
@@ -1167,8 +1184,25 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
     }
   };
 
+  // the roots of the group's cells, a lane each (the first 64 kept)
+  auto root = [&](int j) {
+    const KCell C = tb.cell[J.cell_begin + j];
+    return int2{(int)(pos[C.elem] & 0x7fffu) + 2, C.id};
+  };
+  int2 root0{0, 0};
+  if constexpr (OUT) {
+    if (lane < J.ncell) root0 = root(lane);
+  }
+  auto roots = [&](auto&& f) {
+    for (int j = lane; j < J.ncell; j += 64) f(j == lane ? root0 : root(j));
+  };
+  auto add_roots = [&](int k) {  // kFlowAdjoint: the given values of step k
+    const double* g = L.g + k * L.root_stride;
+    roots([&](int2 r) { img[r.x] += g[r.y]; });
+  };
+
   Src keep[NK];
-  if (J.ncell == 0) {
+  if (J.contig) {
 #pragma unroll
     for (int k = 0; k < NK; ++k) keep[k] = source(J.user_lo, n, pos, 64 * k + lane);
 #pragma unroll
@@ -1178,6 +1212,7 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
   streamed(stage);
   __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
   __builtin_amdgcn_wave_barrier();
+  if constexpr (RHS == kFlowAdjoint) add_roots(0);
   flow_backward<true>(I);
   for (int it = 1;; ++it) {
     __builtin_amdgcn_wave_barrier();
@@ -1185,14 +1220,23 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
     __builtin_amdgcn_wave_barrier();
     const bool last = it == L.nsteps;
     const uint32_t step = L.step + (uint32_t)it;
-    if (J.ncell == 0) {
+    double* row = nullptr;
+    if constexpr (OUT) {
+      if (L.states) row = L.states + (it - 1) * L.state_stride;
+      if (L.traces) {
+        double* t = L.traces + (it - 1) * L.root_stride;
+        roots([&](int2 r) { t[r.y] = img[r.x]; });
+      }
+    }
+    if (J.contig) {
 #pragma unroll
       for (int k = 0; k < NK; k += NB)
-        if (64 * k < n) turn(J.user_lo, n, 64 * k, keep + k, step, last);
+        if (64 * k < n) turn(J.user_lo, n, 64 * k, keep + k, step, last, row);
     }
-    streamed([&](int64_t lo, int m, int e0, const Src* s) { turn(lo, m, e0, s, step, last); });
+    streamed([&](int64_t lo, int m, int e0, const Src* s) { turn(lo, m, e0, s, step, last, row); });
     if (last) break;
     __builtin_amdgcn_wave_barrier();
+    if constexpr (RHS == kFlowAdjoint) add_roots(it);
     flow_backward_kept(I);
   }
 }
@@ -2795,17 +2839,34 @@ __global__ void k_gather_roots(int32_t ncells, const int64_t* __restrict__ cell_
   out[c] = v[cell_off[c]];
 }
 
-// Per step k: gI += lam; gc += lam (v_prev - v); ga_i += -(lam_i - lam_p)(v_i - v_p).
-__global__ void k_adjoint_accumulate(int64_t n, const int32_t* __restrict__ parent, const double* __restrict__ lam,
-                                     const double* __restrict__ v, const double* __restrict__ v_prev,
-                                     double* __restrict__ ga, double* __restrict__ gc, double* __restrict__ gi) {
+// For steps k = nsteps - 1 down to 0, states V^k (rows of v, v0 before the first)
+// and adjoints lam^k: gI += lam; gc += lam (V^{k-1} - V^k);
+// ga_i += -(lam_i - lam_p)(V_i - V_p).  Bound by memory: 16 bytes per step and
+// compartment (the parent's values are neighbours' in the same lines) and the
+// gradients once per call, where a call per step moved 72 (13.7 us a step on
+// 1,024 cells of 1,000).
+__global__ void k_adjoint_accumulate(int64_t n, int32_t nsteps, const int32_t* __restrict__ parent,
+                                     const double* __restrict__ lam, const double* __restrict__ v,
+                                     const double* __restrict__ v0, double* __restrict__ ga, double* __restrict__ gc,
+                                     double* __restrict__ gi) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double l = lam[i];
-  gi[i] = gi[i] + l;
-  gc[i] = gc[i] + l * (v_prev[i] - v[i]);
   const int32_t p = parent[i];
-  if (p >= 0) ga[i] = ga[i] - (l - lam[p]) * (v[i] - v[p]);
+  const int64_t q = p >= 0 ? p : i;
+  double a = ga[i], c = gc[i], s = gi[i];
+  double vk = v[(int64_t)(nsteps - 1) * n + i];
+  for (int32_t k = nsteps - 1; k >= 0; --k) {
+    const double* lk = lam + (int64_t)k * n;
+    const double l = lk[i], lp = lk[q], vq = v[(int64_t)k * n + q];
+    const double vm = k > 0 ? v[(int64_t)(k - 1) * n + i] : v0[i];
+    s = s + l;
+    c = c + l * (vm - vk);
+    if (p >= 0) a = a - (l - lp) * (vk - vq);
+    vk = vm;
+  }
+  ga[i] = a;
+  gc[i] = c;
+  gi[i] = s;
 }
 
 }  // namespace hdev

@@ -709,10 +709,10 @@ struct Builder {
       for (int64_t e = P.group_offsets[g]; e < P.group_offsets[g + 1]; ++e) {
         int64_t c = P.group_cells[e];
         if (!contig) U = (U + 1) & ~(int64_t)1;  // each cell starts 16-byte aligned in the LDS image
+        P.kcell[e] = KCell{coff[c], (int32_t)(coff[c + 1] - coff[c]), (int32_t)U, (int32_t)c, G.user_n};
         G.user_n += (int32_t)(coff[c + 1] - coff[c]);
         cell_lds[c] = (int32_t)U;
         cell_gbr[c] = (int32_t)nbr;
-        P.kcell[e] = KCell{coff[c], (int32_t)(coff[c + 1] - coff[c]), (int32_t)U};
         U += coff[c + 1] - coff[c];
         nbr += cell_br_lo[c + 1] - cell_br_lo[c];
         gnl = std::max(gnl, (int32_t)(cnt_off[c + 1] - cnt_off[c]));
@@ -1084,8 +1084,9 @@ void pack_flow_bins(const HostPlan& P, std::vector<FlowLaunch>& launches, std::v
           J.naux = W.naux;
           J.nent = W.nent;
           J.lds_off = (int32_t)off;
-          J.ncell = G.contig ? 0 : G.ncell;
+          J.ncell = G.ncell;
           J.cell_begin = G.cell_begin;
+          J.contig = G.contig;
           off += bytes[g];
         }
         jobs.push_back(J);
@@ -1125,10 +1126,10 @@ bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches,
         const KGroup& G = P.kgroup[it->second];
         by_step.erase(it);
         ++placed;
-        const bool range = J.ncell == 0 && G.contig && J.user_lo == G.user_base + G.user_lo;
-        const bool cells = J.ncell == G.ncell && !G.contig && J.cell_begin == G.cell_begin;
+        const bool range = !G.contig || J.user_lo == G.user_base + G.user_lo;
+        const bool cells = J.ncell == G.ncell && J.contig == G.contig && J.cell_begin == G.cell_begin;
         if (J.nstep != W.nstep || J.nelem != W.nelem || J.nent != W.nent || J.naux != W.naux ||
-            J.pos_off != W.pos_off || J.aux_off != W.aux_off || !(range || cells) || J.lds_off < end ||
+            J.pos_off != W.pos_off || J.aux_off != W.aux_off || !range || !cells || J.lds_off < end ||
             (J.lds_off & 15)) {
           why = "flow job record";
           return false;

@@ -374,6 +374,8 @@ struct KCell {
   int64_t user_lo;  // first user index of the cell
   int32_t n;        // compartments
   int32_t lds;      // offset of the cell in the group's LDS image
+  int32_t id;       // the cell
+  int32_t elem;     // compartments of the group before it
 };
 
 // Flow kernel tables of one group.  The compartments (and path pads) get LDS
@@ -421,9 +423,9 @@ struct KFlowJob {
   int32_t nstep;      // chunk steps per sweep; 0: an empty place of the bin
   int32_t nelem, naux, nent;
   int32_t lds_off;    // bytes
-  int32_t ncell;      // cells of a group that is not one user range; 0: one range
+  int32_t ncell;      // cells of the group
   int32_t cell_begin; // their first entry in the group-cell table
-  int32_t pad;
+  int32_t contig;     // 1: the group is the user range from user_lo
 };
 static_assert(sizeof(KFlowJob) == 64, "one scalar load");
 

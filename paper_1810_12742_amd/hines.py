@@ -89,6 +89,9 @@ def load():
     lib.hines_gather_roots.argtypes = [P, P, P, P]
     lib.hines_adjoint_rhs.argtypes = [P, P, P, P, P, P]
     lib.hines_adjoint_accumulate.argtypes = [P, P, P, P, P, P, P, P]
+    lib.hines_run_steps.argtypes = [P, P, P, P, P, P, I32, P, P, P, I32, P]
+    lib.hines_adjoint_steps.argtypes = [P, P, P, P, P, P, I32, P, I32, P]
+    lib.hines_adjoint_accumulate_steps.argtypes = [P, P, P, P, I32, P, P, P, P]
     lib.hines_check_matrix.argtypes = [P, P, P, ctypes.POINTER(I64), P]
     lib.hines_layout_size.argtypes = [P, ctypes.POINTER(I64)]
     lib.hines_to_layout.argtypes = [P, P, P, P]
@@ -100,6 +103,7 @@ def load():
                  "hines_destroy",
                  "hines_timestep", "hines_timeloop_create", "hines_timeloop_launch", "hines_timeloop_destroy",
                  "hines_assemble", "hines_gather_roots", "hines_adjoint_rhs", "hines_adjoint_accumulate",
+                 "hines_run_steps", "hines_adjoint_steps", "hines_adjoint_accumulate_steps",
                  "hines_check_matrix", "hines_layout_size", "hines_to_layout", "hines_from_layout",
                  "hines_solve_layout"):
         getattr(lib, name).restype = I32
@@ -377,6 +381,46 @@ class Plan:
             self._h, _dev(lam, self.n, f64, "lam"), _dev(v, self.n, f64, "v"), _dev(v_prev, self.n, f64, "v_prev"),
             _dev(grad_a, self.n, f64, "grad_a"), _dev(grad_c, self.n, f64, "grad_c"),
             _dev(grad_i, self.n, f64, "grad_i"), ctypes.c_void_p(st.cuda_stream)))
+
+    def run_steps(self, diag, upper, c, v_in, nsteps, i_inj=None, states=None, v_out=None, traces=None, stream=None):
+        """``nsteps`` steps from ``v_in`` (``hines_run_steps``): every state into the rows
+        of ``states``, the last into ``v_out``, the roots into the rows of ``traces``."""
+        import torch
+        st = stream if stream is not None else torch.cuda.current_stream()
+        f64 = torch.float64
+
+        def opt(t, m, name):
+            return None if t is None else _dev(t, m, f64, name)
+        _check(load().hines_run_steps(
+            self._h, _dev(diag, self.n, f64, "diag"), _dev(upper, self.n, f64, "upper"), _dev(c, self.n, f64, "c"),
+            _dev(v_in, self.n, f64, "v_in"), opt(i_inj, self.n, "i_inj"), int(nsteps),
+            opt(states, nsteps * self.n, "states"), opt(v_out, self.n, "v_out"),
+            opt(traces, nsteps * self.ncells, "traces"), self.ncells, ctypes.c_void_p(st.cuda_stream)))
+
+    def adjoint_steps(self, diag, upper, c, lam_in, g_roots, lams, stream=None):
+        """The adjoints of ``len(lams)`` steps, last first (``hines_adjoint_steps``)."""
+        import torch
+        st = stream if stream is not None else torch.cuda.current_stream()
+        f64 = torch.float64
+        m = lams.shape[0]
+        _check(load().hines_adjoint_steps(
+            self._h, _dev(diag, self.n, f64, "diag"), _dev(upper, self.n, f64, "upper"), _dev(c, self.n, f64, "c"),
+            None if lam_in is None else _dev(lam_in, self.n, f64, "lam_in"),
+            _dev(g_roots, m * self.ncells, f64, "g_roots"), m, _dev(lams, m * self.n, f64, "lams"), self.ncells,
+            ctypes.c_void_p(st.cuda_stream)))
+
+    def adjoint_accumulate_steps(self, lams, states, v0, grad_a, grad_c, grad_i, stream=None):
+        """``adjoint_accumulate`` over the rows of ``lams`` and ``states``, last first
+        (``hines_adjoint_accumulate_steps``); ``v0`` is the state before the first."""
+        import torch
+        st = stream if stream is not None else torch.cuda.current_stream()
+        f64 = torch.float64
+        m = lams.shape[0]
+        _check(load().hines_adjoint_accumulate_steps(
+            self._h, _dev(lams, m * self.n, f64, "lams"), _dev(states, m * self.n, f64, "states"),
+            _dev(v0, self.n, f64, "v0"), m, _dev(grad_a, self.n, f64, "grad_a"),
+            _dev(grad_c, self.n, f64, "grad_c"), _dev(grad_i, self.n, f64, "grad_i"),
+            ctypes.c_void_p(st.cuda_stream)))
 
 
 class TimeLoop:
