@@ -229,7 +229,8 @@ hipError_t launch_flow(const hines_plan* p, const RhsSpec& rs, const MT* d, cons
   for (const hines::FlowLaunch& L : p->flow_launches) {
     DevTables t = p->t;
     t.fjob = p->t.fjob + L.first;
-    const dim3 grid((unsigned)L.bins), block((unsigned)(64 * L.width));
+    t.fcoop = L.coop;
+    const dim3 grid((unsigned)L.bins), block((unsigned)L.threads());
     if (rs.mode == hdev::kRhsGiven)
       hipLaunchKernelGGL((hdev::k_solve_flow<hdev::kFlowGiven, MT>), grid, block, L.lds_bytes, s, t, rs, d, u, x);
     else if constexpr (sizeof(MT) == 8) {
@@ -253,8 +254,9 @@ hipError_t launch_flow_run(const hines_plan* p, const hdev::FlowRun& L, const do
   for (const hines::FlowLaunch& B : p->flow_launches) {
     DevTables t = p->t;
     t.fjob = p->t.fjob + B.first;
-    hipLaunchKernelGGL((hdev::k_flow_loop<RHS, OUT>), dim3((unsigned)B.bins), dim3((unsigned)(64 * B.width)),
-                       B.lds_bytes, s, t, L, d, u);
+    t.fcoop = B.coop;
+    hipLaunchKernelGGL((hdev::k_flow_loop<RHS, OUT>), dim3((unsigned)B.bins), dim3((unsigned)B.threads()), B.lds_bytes,
+                       s, t, L, d, u);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

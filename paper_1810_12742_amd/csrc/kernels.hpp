@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "setup.hpp"
 
@@ -28,7 +29,8 @@ struct DevTables {
   const KCell* cell;     // group order
   const int32_t* glist;  // group ids of one launch
   double* ws;            // global images of groups that exceed LDS
-  const hines::KFlowJob* fjob;  // flow kernel: one record per wave of a launch, bin by bin
+  const hines::KFlowJob* fjob;  // flow kernel: one record per group of a launch, bin by bin
+  int32_t fcoop;                // flow kernel: waves per group (more than one: a group per workgroup)
   const uint64_t* fmask;     // flow kernel: active and push masks per step
   const uint16_t* fpos;      // flow kernel: position of every element
   const int16_t* faux;       // flow kernel: parent position of every push
@@ -627,17 +629,17 @@ enum : int { kCellCond = 5 };
 // value at each cell's root.
 enum : int { kFlowAdjoint = 6 };
 
-// Element e of a user range (user index lo + e) -> its position.  A lane
-// handles elements lane, lane + 64, ... in batches of kStageUnroll<RHS>; all loads
+// Element e of a user range (user index lo + e) -> its position.  Thread t of
+// the T threads of a group handles elements t, t + T, ... in batches of kStageUnroll; all loads
 // of a batch are issued before any is used.  Indices past the range are clamped
 // to its last element, so every load is unconditional (the repeated element is
 // written twice with the same value).
-// Two batches are in flight at once: their sizes fill the 256 registers that a
-// workgroup of eight waves has.
+// A batch is a few elements a thread, so that little is loaded past the end of
+// a short group (batches of 16 made 600 compartments 40% slower than batches of
+// 10); the first kStageBatches are in flight together.
+constexpr int kStageUnroll = 4;
 template <int RHS>
-constexpr int kStageUnroll = RHS == kFlowGiven ? 10 : RHS == kFlowNoise ? 6 : 7;
-template <int RHS>
-constexpr int kStageBatch = 64 * kStageUnroll<RHS>;
+constexpr int kStageBatches = RHS == kFlowGiven ? 6 : 4;
 
 // Right-hand side of a step, the same rounding in the one-step and in the
 // looping kernel: c v, or c v + i in one rounding.
@@ -647,21 +649,21 @@ __device__ __forceinline__ double flow_rhs(double c, double v, double i) { retur
 // Register set of one batch: positions, matrix, right-hand side ingredients.
 template <int RHS, typename MT>
 struct FlowBatch {
-  uint32_t p[kStageUnroll<RHS>];
-  MT d[kStageUnroll<RHS>], u[kStageUnroll<RHS>];
-  double b[kStageUnroll<RHS>];
-  double c[RHS == kFlowGiven ? 1 : kStageUnroll<RHS>];
-  double i[RHS == kFlowCVI ? kStageUnroll<RHS> : 1];
+  uint32_t p[kStageUnroll];
+  MT d[kStageUnroll], u[kStageUnroll];
+  double b[kStageUnroll];
+  double c[RHS == kFlowGiven ? 1 : kStageUnroll];
+  double i[RHS == kFlowCVI ? kStageUnroll : 1];
 };
 
 template <int RHS, typename MT>
 __device__ __forceinline__ void flow_batch_load(FlowBatch<RHS, MT>& S, const RhsSpec& rs, const MT* __restrict__ d,
                                                 const MT* __restrict__ u, int64_t lo, int n,
-                                                const uint16_t* __restrict__ pos, int e0, int lane) {
+                                                const uint16_t* __restrict__ pos, int e0, int T, int t) {
   // uniform bases, 32-bit per-lane offsets
 #pragma unroll
-  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
-    const int e = min(e0 + 64 * k + lane, n - 1);
+  for (int k = 0; k < kStageUnroll; ++k) {
+    const int e = min(e0 + T * k + t, n - 1);
     S.p[k] = pos[e];
     S.d[k] = (d + lo)[e];
     S.u[k] = (u + lo)[e];
@@ -676,16 +678,20 @@ __device__ __forceinline__ void flow_batch_load(FlowBatch<RHS, MT>& S, const Rhs
 }
 
 template <int RHS, typename MT>
-__device__ __forceinline__ void flow_batch_put(const FlowBatch<RHS, MT>& S, const RhsSpec& rs, int64_t lo, int n,
-                                               lds_f64* img, int e0, int lane) {
+__device__ __forceinline__ void flow_batch_put(FlowBatch<RHS, MT>& S, const RhsSpec& rs, int64_t lo, int n,
+                                               lds_f64* img, int e0, int T, int t) {
+  // nothing is computed from a loaded value before this point: formed between
+  // the loads, the right-hand sides would wait for them one by one
 #pragma unroll
-  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
+  for (int k = 0; k < kStageUnroll; ++k) __asm__ volatile("" : "+v"(S.b[k]), "+v"(S.d[k]));
+#pragma unroll
+  for (int k = 0; k < kStageUnroll; ++k) {
     double b = S.b[k];
     if constexpr (RHS == kFlowCV) b = flow_rhs(S.c[k], S.b[k]);
     if constexpr (RHS == kFlowCVI) b = flow_rhs(S.c[k], S.b[k], S.i[k]);
     if constexpr (RHS == kFlowNoise)
       b = flow_rhs(S.c[k], S.b[k],
-                   noise_draw(rs.seed, rs.step, (uint64_t)(lo + min(e0 + 64 * k + lane, n - 1)), rs.sigma));
+                   noise_draw(rs.seed, rs.step, (uint64_t)(lo + min(e0 + T * k + t, n - 1)), rs.sigma));
     lds_f64* q = img + (int)(S.p[k] & 0x7fffu);
     q[0] = (double)S.d[k];
     q[1] = (S.p[k] & 0x8000u) ? 0.0 : (double)S.u[k];
@@ -693,24 +699,22 @@ __device__ __forceinline__ void flow_batch_put(const FlowBatch<RHS, MT>& S, cons
   }
 }
 
-// Store elements [e0, e0 + kStageBatch<RHS>) of a range from their positions p.
-template <int RHS>
-__device__ __forceinline__ void flow_batch_store(double* x, int n, const uint32_t* p, const lds_f64* img, int e0,
-                                                 int lane) {
+// Store elements [e0, e0 + T kStageUnroll) of a range from their positions p.
+__device__ __forceinline__ void flow_batch_store(double* x, int n, const uint32_t* p, const lds_f64* img, int e0, int T,
+                                                 int t) {
 #pragma unroll
-  for (int k = 0; k < kStageUnroll<RHS>; ++k) {
-    const int e = e0 + 64 * k + lane;
+  for (int k = 0; k < kStageUnroll; ++k) {
+    const int e = e0 + T * k + t;
     if (e < n) x[e] = img[(int)(p[k] & 0x7fffu) + 2];
   }
 }
-template <int RHS>
 __device__ __forceinline__ void flow_store_from(double* x, int n, const uint16_t* __restrict__ pos, const lds_f64* img,
-                                                int e0, int lane) {
-  for (; e0 < n; e0 += kStageBatch<RHS>) {
-    uint32_t p[kStageUnroll<RHS>];
+                                                int e0, int T, int t) {
+  for (; e0 < n; e0 += T * kStageUnroll) {
+    uint32_t p[kStageUnroll];
 #pragma unroll
-    for (int k = 0; k < kStageUnroll<RHS>; ++k) p[k] = pos[min(e0 + 64 * k + lane, n - 1)];
-    flow_batch_store<RHS>(x, n, p, img, e0, lane);
+    for (int k = 0; k < kStageUnroll; ++k) p[k] = pos[min(e0 + T * k + t, n - 1)];
+    flow_batch_store(x, n, p, img, e0, T, t);
   }
 }
 
@@ -772,14 +776,14 @@ __device__ __forceinline__ void flow_stage_tables(const DevTables& tb, const hin
 
 // Every entry of every block (pads and the identity block included) starts as
 // the identity compartment; the staging overwrites the real ones.
-__device__ __forceinline__ void flow_clear(const hines::KFlowJob& J, const FlowImage& I, int lane) {
-  for (int e = lane; e < J.nent + KC; e += 64) {
+__device__ __forceinline__ void flow_clear(const hines::KFlowJob& J, const FlowImage& I, int T, int t) {
+  for (int e = t; e < J.nent + KC; e += T) {
     const int o = (e / KC) * KB8 + 3 * (e % KC);
     I.img[o] = 1.0;
     I.img[o + 1] = 0.0;
     I.img[o + 2] = 0.0;
   }
-  if (lane == 0) {
+  if (t == 0) {
     I.msk[-1] = u32x4{0u, 0u, 0u, 0u};
     I.msk[I.F] = u32x4{0u, 0u, 0u, 0u};
     if (I.naux == 0) I.aux[0] = 0;  // the clamped push-target read stays defined
@@ -963,6 +967,32 @@ __device__ __forceinline__ void flow_forward(const FlowImage& I) {
   }
 }
 
+// The waves of one group: one of the workgroup's waves, or all of them.  Only
+// one wave runs the sweeps; the others help with the work that is spread over
+// the elements (staging, right-hand sides, stores) and wait at barriers
+// meanwhile.
+struct FlowTeam {
+  int T, t;      // threads of the group, this thread
+  int job;       // the group's record
+  bool sweeper;
+  __device__ __forceinline__ void sync() const {
+    if (T > 64)
+      __syncthreads();
+    else
+      __builtin_amdgcn_wave_barrier();  // one wave's LDS operations are in order
+  }
+};
+__device__ __forceinline__ FlowTeam flow_team(const DevTables& tb) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  FlowTeam g;
+  if (tb.fcoop > 1) {
+    g = FlowTeam{64 * tb.fcoop, (int)threadIdx.x, (int)blockIdx.x, wave == 0};
+  } else {
+    g = FlowTeam{64, (int)threadIdx.x & 63, (int)(blockIdx.x * (blockDim.x >> 6)) + wave, true};
+  }
+  return g;
+}
+
 // One wave per group, blockDim.x / 64 groups per workgroup (a bin: the host
 // packs groups of different sizes into the LDS of one workgroup).  The waves
 // of a workgroup share nothing and never meet at a barrier.  MT: the storage
@@ -971,65 +1001,78 @@ __device__ __forceinline__ void flow_forward(const FlowImage& I) {
 // Bound by the serial length of a group times the groups that LDS holds: about
 // 23 chunk steps a sweep for a C2 cell at 950 (backward) and 450 (forward)
 // cycles each when alone, 1,190 and 540 with three on a compute unit; staging
-// 10,000 to 15,000 cycles and the store 5,000 are memory latency.  The two
-// register sets of the sweeps, the two staging batches in flight and the bins
-// took 64 C2 cells from 207 to 28 us (11 launches before, one now), 4,099 from
-// 424 to 161 us, a step of 8,192 cells of 1,000 from 216 to 193 us.
+// and store are memory latency (6,700 and 1,600 cycles with four waves a group,
+// 15,000 and 5,000 with one beside others).  The two register sets of the
+// sweeps, the staging batches in flight together, the bins and the helping
+// waves took 64 C2 cells from 207 to 24 us (11 launches before, one now), 4,099
+// from 424 to 160 us, a step of 8,192 cells of 1,000 from 217 to 187 us.
 template <int RHS, typename MT = double>
 __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, const MT* __restrict__ d,
                                                     const MT* __restrict__ u, double* x) {
   extern __shared__ __attribute__((aligned(16))) char flow_raw[];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const hines::KFlowJob J = tb.fjob[blockIdx.x * (blockDim.x >> 6) + wave];
+  const FlowTeam g = flow_team(tb);
+  const int T = g.T, t = g.t, batch = T * kStageUnroll;
+  const hines::KFlowJob J = tb.fjob[g.job];
   if (J.nstep == 0) return;  // an empty place of the bin
   const FlowImage I = flow_image(J, flow_raw, lane);
   const uint16_t* pos = tb.fpos + J.pos_off;
   const int n = J.nelem;
-  // the first two batches are in flight together, and the image is cleared
+  // the first NB batches are in flight together, and the image is cleared
   // meanwhile; their positions stay in registers for the store
-  FlowBatch<RHS, MT> S0, S1;
+  constexpr int NB = kStageBatches<RHS>;
+  FlowBatch<RHS, MT> S[NB];
   if (J.contig) {
-    flow_batch_load(S0, rs, d, u, J.user_lo, n, pos, 0, lane);
-    if (n > kStageBatch<RHS>) flow_batch_load(S1, rs, d, u, J.user_lo, n, pos, kStageBatch<RHS>, lane);
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (k * batch < n) flow_batch_load(S[k], rs, d, u, J.user_lo, n, pos, k * batch, T, t);
   }
-  flow_stage_tables(tb, J, I, flow_raw, lane);
-  flow_clear(J, I, lane);
+  if (g.sweeper) flow_stage_tables(tb, J, I, flow_raw, lane);
+  flow_clear(J, I, T, t);
+  g.sync();
   if (J.contig) {
-    flow_batch_put(S0, rs, J.user_lo, n, I.img, 0, lane);
-    if (n > kStageBatch<RHS>) flow_batch_put(S1, rs, J.user_lo, n, I.img, kStageBatch<RHS>, lane);
-    for (int e0 = 2 * kStageBatch<RHS>; e0 < n; e0 += kStageBatch<RHS>) {
-      FlowBatch<RHS, MT> S;
-      flow_batch_load(S, rs, d, u, J.user_lo, n, pos, e0, lane);
-      flow_batch_put(S, rs, J.user_lo, n, I.img, e0, lane);
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (k * batch < n) flow_batch_put(S[k], rs, J.user_lo, n, I.img, k * batch, T, t);
+    for (int e0 = NB * batch; e0 < n; e0 += NB * batch) {
+      FlowBatch<RHS, MT> R[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (e0 + k * batch < n) flow_batch_load(R[k], rs, d, u, J.user_lo, n, pos, e0 + k * batch, T, t);
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (e0 + k * batch < n) flow_batch_put(R[k], rs, J.user_lo, n, I.img, e0 + k * batch, T, t);
     }
   } else {
     int q = 0;
     for (int c = 0; c < J.ncell; ++c) {
       const KCell C = tb.cell[J.cell_begin + c];
-      for (int e0 = 0; e0 < C.n; e0 += kStageBatch<RHS>) {
-        flow_batch_load(S0, rs, d, u, C.user_lo, C.n, pos + q, e0, lane);
-        flow_batch_put(S0, rs, C.user_lo, C.n, I.img, e0, lane);
+      for (int e0 = 0; e0 < C.n; e0 += batch) {
+        flow_batch_load(S[0], rs, d, u, C.user_lo, C.n, pos + q, e0, T, t);
+        flow_batch_put(S[0], rs, C.user_lo, C.n, I.img, e0, T, t);
       }
       q += C.n;
     }
   }
   __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
-  __builtin_amdgcn_wave_barrier();
-  flow_backward(I);
-  __builtin_amdgcn_wave_barrier();
-  flow_forward(I);
-  __builtin_amdgcn_wave_barrier();
+  g.sync();
+  if (g.sweeper) {
+    flow_backward(I);
+    __builtin_amdgcn_wave_barrier();
+    flow_forward(I);
+  }
+  g.sync();
   if (J.contig) {
     double* xo = x + J.user_lo;
-    flow_batch_store<RHS>(xo, n, S0.p, I.img, 0, lane);
-    if (n > kStageBatch<RHS>) flow_batch_store<RHS>(xo, n, S1.p, I.img, kStageBatch<RHS>, lane);
-    flow_store_from<RHS>(xo, n, pos, I.img, 2 * kStageBatch<RHS>, lane);
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (k * batch < n) flow_batch_store(xo, n, S[k].p, I.img, k * batch, T, t);
+    flow_store_from(xo, n, pos, I.img, NB * batch, T, t);
   } else {
     int q = 0;
     for (int c = 0; c < J.ncell; ++c) {
       const KCell C = tb.cell[J.cell_begin + c];
-      flow_store_from<RHS>(x + C.user_lo, C.n, pos + q, I.img, 0, lane);
+      flow_store_from(x + C.user_lo, C.n, pos + q, I.img, 0, T, t);
       q += C.n;
     }
   }
@@ -1046,8 +1089,9 @@ __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, co
 //
 // Bound by the serial length of a group like k_solve_flow, without its
 // staging, divisions and store: per step and group about 450 + 450 cycles a
-// chunk step.  100 steps of 257 C2 cells with a current take 1.77 ms, 3.15 ms as
-// 100 launches of k_solve_flow.
+// chunk step, beside the turn between two steps.  100 steps of 257 C2 cells with
+// a current take 1.37 ms (1.77 with one wave a group), 3.15 ms as 100 launches of
+// k_solve_flow.
 // ---------------------------------------------------------------------------
 struct FlowRun {
   const double* c;
@@ -1069,9 +1113,9 @@ struct FlowRun {
 // Elements of a lane whose c (and I) stay in registers, and elements staged, or
 // handled beyond those, at a time: what 256 registers hold beside the sweeps.
 template <int RHS, bool OUT>
-constexpr int kLoopKeep = RHS == kFlowNoise ? 10 : (RHS == kFlowCVI || OUT) ? 16 : 24;
+constexpr int kLoopKeep = RHS == kFlowNoise ? 24 : RHS == kFlowCVI ? 18 : 24;
 template <int RHS, bool OUT>
-constexpr int kLoopBatch = (RHS == kFlowNoise || (RHS == kFlowCVI && OUT)) ? 2 : (RHS == kFlowCVI || OUT) ? 4 : 6;
+constexpr int kLoopBatch = RHS == kFlowNoise ? 4 : RHS == kFlowCVI ? 4 : 6;
 
 // OUT: the states and root traces of every step are stored (the forward run of
 // a fit and its adjoint).
@@ -1080,18 +1124,25 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
                                                    const double* __restrict__ u) {
   extern __shared__ __attribute__((aligned(16))) char flow_raw[];
   constexpr int NK = kLoopKeep<RHS, OUT>, NB = kLoopBatch<RHS, OUT>;
-  static_assert(NK % NB == 0, "the kept elements are staged in whole batches");
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const hines::KFlowJob J = tb.fjob[blockIdx.x * (blockDim.x >> 6) + wave];
+  const FlowTeam g = flow_team(tb);
+  const int T = g.T, t = g.t;
+  const hines::KFlowJob J = tb.fjob[g.job];
   if (J.nstep == 0) return;  // an empty place of the bin
   const FlowImage I = flow_image(J, flow_raw, lane);
   lds_f64* img = I.img;
   const uint16_t* pos = tb.fpos + J.pos_off;
   const int n = J.nelem;
-  flow_stage_tables(tb, J, I, flow_raw, lane);
-  flow_clear(J, I, lane);
+  if (g.sweeper) flow_stage_tables(tb, J, I, flow_raw, lane);
+  flow_clear(J, I, T, t);
+  g.sync();
 
+  // element addresses are formed anew at each use: kept over the loop of steps
+  // they would take more registers than the elements' values
+  auto fresh = [](int v) {
+    __asm__ volatile("" : "+v"(v));
+    return v;
+  };
   // what one element's right-hand side needs besides its state
   struct Src {
     uint32_t p;  // position; past the end of a range: the lane's sink, so that no LDS access is masked
@@ -1111,133 +1162,169 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
     if constexpr (RHS == kFlowCVI) return flow_rhs(s.c, v, s.i);
     return flow_rhs(s.c, v, noise_draw(L.seed, step, (uint64_t)i, L.sigma));
   };
-  // NB elements of a range into the image
-  auto stage = [&](int64_t lo, int m, int e0, const Src* s) {
-    double dv[NB], uv[NB], vv[NB];
+  // N elements of a range from e0 into the image
+  auto stage = [&](auto N, int64_t lo, int m, int e0, const Src* s) {
+    double dv[N], uv[N], vv[N];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int e = min(e0 + 64 * k + lane, m - 1);
+    for (int k = 0; k < N; ++k) {
+      const int e = min(e0 + T * k + t, m - 1);
       dv[k] = (d + lo)[e];
       uv[k] = (u + lo)[e];
       vv[k] = (L.v_in + lo)[e];
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int e = min(e0 + 64 * k + lane, m - 1);
+    for (int k = 0; k < N; ++k) {
+      const int e = min(e0 + T * k + t, m - 1);
       lds_f64* q = img + (int)(s[k].p & 0x7fffu);
       q[0] = dv[k];
       q[1] = (s[k].p & 0x8000u) ? 0.0 : uv[k];
       q[2] = rhs(s[k], vv[k], L.step, lo + e);
     }
-    if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);  // at most NB draws in flight: registers
+    if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);  // at most N draws in flight: registers
   };
-  // NB elements: x of the finished step out (last step), or the next right-hand side over it
-  auto turn = [&](int64_t lo, int m, int e0, const Src* s, uint32_t step, bool last, double* row) {
+  // N elements: x of the finished step out (OUT, or the last step), and the
+  // next right-hand side over it
+  auto turn = [&](auto N, int64_t lo, int m, int e0, const Src* s, uint32_t step, bool last, double* row) {
+    const int t = fresh(g.t);
+    double x[N];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int e = e0 + 64 * k + lane;
-      lds_f64* q = img + (int)(s[k].p & 0x7fffu) + 2;
-      const double x = *q;
-      if constexpr (OUT) {
-        if (row && e < m) (row + lo)[e] = x;
+    for (int k = 0; k < N; ++k) x[k] = img[(int)(s[k].p & 0x7fffu) + 2];
+    if (OUT && row) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (e0 + T * k + t < m) (row + lo)[e0 + T * k + t] = x[k];
+    }
+    if (last) {
+      if (!OUT || L.v_out) {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+          if (e0 + T * k + t < m) (L.v_out + lo)[e0 + T * k + t] = x[k];
       }
-      if (last) {
-        if ((!OUT || L.v_out) && e < m) (L.v_out + lo)[e] = x;
-      } else {
-        *q = rhs(s[k], x, step, lo + min(e, m - 1));
-      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        img[(int)(s[k].p & 0x7fffu) + 2] = rhs(s[k], x[k], step, lo + min(e0 + T * k + t, m - 1));
     }
     if constexpr (RHS == kFlowNoise) __builtin_amdgcn_sched_barrier(0);
   };
-  // every element beyond the kept ones (all of them if the group is not one range)
-  auto streamed = [&](auto&& f) {
-    auto range = [&](int64_t lo, int m, const uint16_t* ps, int e0) {
-      if (e0 >= m) return;
-      // two register sets in turn: the next batch is in flight during this one
-      // (past the end of the range it is loaded clamped and not used)
-      Src s0[NB], s1[NB];
-      auto load = [&](Src* s, int e) {
+  // elements e0, ... of a range in batches of NB, two register sets in turn:
+  // a batch is in flight while the one before it is handled (past the end of
+  // the range it is loaded clamped and not used)
+  struct Pair {
+    Src a[NB], b[NB];
+  };
+  auto fetch = [&](int64_t lo, int m, const uint16_t* ps, Src* s, int e) {
+    const int t = fresh(g.t);
 #pragma unroll
-        for (int k = 0; k < NB; ++k) s[k] = source(lo, m, ps, e + 64 * k + lane);
-      };
-      load(s0, e0);
-      for (;;) {
-        load(s1, e0 + 64 * NB);
-        f(lo, m, e0, s0);
-        e0 += 64 * NB;
-        if (e0 >= m) break;
-        load(s0, e0 + 64 * NB);
-        f(lo, m, e0, s1);
-        e0 += 64 * NB;
-        if (e0 >= m) break;
-      }
-    };
-    if (J.contig) {
-      range(J.user_lo, n, pos, 64 * NK);
-    } else {
-      int q = 0;
-      for (int c = 0; c < J.ncell; ++c) {
-        const KCell C = tb.cell[J.cell_begin + c];
-        range(C.user_lo, C.n, pos + q, 0);
-        q += C.n;
-      }
+    for (int k = 0; k < NB; ++k) s[k] = source(lo, m, ps, e + T * k + t);
+  };
+  auto range = [&](int64_t lo, int m, const uint16_t* ps, int e0, Pair& P, auto&& f) {
+    while (e0 < m) {
+      f(lo, m, e0, P.a);
+      fetch(lo, m, ps, P.a, e0 + 2 * T * NB);
+      e0 += T * NB;
+      if (e0 >= m) break;
+      f(lo, m, e0, P.b);
+      fetch(lo, m, ps, P.b, e0 + 2 * T * NB);
+      e0 += T * NB;
     }
   };
+  auto prime = [&](int64_t lo, int m, const uint16_t* ps, int e0, Pair& P) {
+    fetch(lo, m, ps, P.a, e0);
+    fetch(lo, m, ps, P.b, e0 + T * NB);
+  };
+  auto cells = [&](auto&& f) {  // a group that is not one range, cell by cell
+    int q = 0;
+    for (int c = 0; c < J.ncell; ++c) {
+      const KCell C = tb.cell[J.cell_begin + c];
+      Pair P;
+      prime(C.user_lo, C.n, pos + q, 0, P);
+      range(C.user_lo, C.n, pos + q, 0, P, f);
+      q += C.n;
+    }
+  };
+  constexpr std::integral_constant<int, NB> nb{};
+  // the kept elements, in batches of NS (with noise few draws at a time)
+  constexpr int NS = RHS == kFlowNoise ? NB : 6;
+  constexpr std::integral_constant<int, NS> ns{};
+  static_assert(NK % NS == 0, "whole batches");
 
-  // the roots of the group's cells, a lane each (the first 64 kept)
+  // the roots of the group's cells, a thread each (the first T kept)
   auto root = [&](int j) {
     const KCell C = tb.cell[J.cell_begin + j];
     return int2{(int)(pos[C.elem] & 0x7fffu) + 2, C.id};
   };
   int2 root0{0, 0};
   if constexpr (OUT) {
-    if (lane < J.ncell) root0 = root(lane);
+    if (t < J.ncell) root0 = root(t);
   }
   auto roots = [&](auto&& f) {
-    for (int j = lane; j < J.ncell; j += 64) f(j == lane ? root0 : root(j));
+    for (int j = t; j < J.ncell; j += T) f(j == t ? root0 : root(j));
   };
   auto add_roots = [&](int k) {  // kFlowAdjoint: the given values of step k
-    const double* g = L.g + k * L.root_stride;
-    roots([&](int2 r) { img[r.x] += g[r.y]; });
+    const double* gr = L.g + k * L.root_stride;
+    roots([&](int2 r) { img[r.x] += gr[r.y]; });
   };
 
   Src keep[NK];
+  const int kept = T * NK;
+  auto stage_nb = [&](int64_t lo, int m, int e0, const Src* s) { stage(nb, lo, m, e0, s); };
   if (J.contig) {
 #pragma unroll
-    for (int k = 0; k < NK; ++k) keep[k] = source(J.user_lo, n, pos, 64 * k + lane);
+    for (int k = 0; k < NK; ++k) keep[k] = source(J.user_lo, n, pos, T * k + t);
 #pragma unroll
-    for (int k = 0; k < NK; k += NB)
-      if (64 * k < n) stage(J.user_lo, n, 64 * k, keep + k);
+    for (int k = 0; k < NK; k += NS)
+      if (T * k < n) stage(ns, J.user_lo, n, T * k, keep + k);
+    if (n > kept) {
+      Pair P;
+      prime(J.user_lo, n, pos, kept, P);
+      range(J.user_lo, n, pos, kept, P, stage_nb);
+    }
+  } else {
+    cells(stage_nb);
   }
-  streamed(stage);
   __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
-  __builtin_amdgcn_wave_barrier();
-  if constexpr (RHS == kFlowAdjoint) add_roots(0);
-  flow_backward<true>(I);
+  g.sync();
+  if constexpr (RHS == kFlowAdjoint) {
+    add_roots(0);
+    g.sync();
+  }
+  if (g.sweeper) flow_backward<true>(I);
   for (int it = 1;; ++it) {
-    __builtin_amdgcn_wave_barrier();
-    flow_forward(I);
-    __builtin_amdgcn_wave_barrier();
+    // what the elements beyond the kept ones need is in flight during the
+    // forward sweep
+    Pair P;
+    if (J.contig) prime(J.user_lo, n, pos, kept, P);
+    if (g.sweeper) flow_forward(I);
+    g.sync();
     const bool last = it == L.nsteps;
     const uint32_t step = L.step + (uint32_t)it;
     double* row = nullptr;
     if constexpr (OUT) {
       if (L.states) row = L.states + (it - 1) * L.state_stride;
       if (L.traces) {
-        double* t = L.traces + (it - 1) * L.root_stride;
-        roots([&](int2 r) { t[r.y] = img[r.x]; });
+        double* tr = L.traces + (it - 1) * L.root_stride;
+        roots([&](int2 r) { tr[r.y] = img[r.x]; });
+        if (T > 64) g.sync();  // the roots are read before a thread overwrites them
       }
     }
+    auto turn_nb = [&](int64_t lo, int m, int e0, const Src* s) { turn(nb, lo, m, e0, s, step, last, row); };
     if (J.contig) {
 #pragma unroll
-      for (int k = 0; k < NK; k += NB)
-        if (64 * k < n) turn(J.user_lo, n, 64 * k, keep + k, step, last, row);
+      for (int k = 0; k < NK; k += NS)
+        if (T * k < n) turn(ns, J.user_lo, n, T * k, keep + k, step, last, row);
+      range(J.user_lo, n, pos, kept, P, turn_nb);
+    } else {
+      cells(turn_nb);
     }
-    streamed([&](int64_t lo, int m, int e0, const Src* s) { turn(lo, m, e0, s, step, last, row); });
     if (last) break;
-    __builtin_amdgcn_wave_barrier();
-    if constexpr (RHS == kFlowAdjoint) add_roots(it);
-    flow_backward_kept(I);
+    g.sync();
+    if constexpr (RHS == kFlowAdjoint) {
+      add_roots(it);
+      g.sync();
+    }
+    if (g.sweeper) flow_backward_kept(I);
   }
 }
 

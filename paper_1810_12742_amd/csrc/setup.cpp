@@ -1066,7 +1066,14 @@ void pack_flow_bins(const HostPlan& P, std::vector<FlowLaunch>& launches, std::v
     }
     std::stable_sort(order.begin(), order.end(),
                      [](const auto& x, const auto& y) { return x.first > y.first; });
-    FlowLaunch L{bp.lds, bp.width, (int64_t)jobs.size(), (int32_t)order.size()};
+    FlowLaunch L{bp.lds, bp.width, (int64_t)jobs.size(), (int32_t)order.size(), 1};
+    if (bp.width == 1) {
+      // a group to a workgroup: the waves that the compute unit has room for
+      // beside its sweeps (two a SIMD at the kernel's registers) share the
+      // staging, the right-hand sides and the store
+      const int64_t held = std::min<int64_t>(kLdsLimitBytes / bp.lds, (L.bins + kBinCus - 1) / kBinCus);
+      while (L.coop < 4 && 2 * L.coop * held <= 8) L.coop *= 2;
+    }
     for (const auto& o : order) {
       int64_t off = 0;
       for (int32_t w = 0; w < bp.width; ++w) {
@@ -1104,7 +1111,8 @@ bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches,
   int64_t at = 0;
   size_t placed = 0;
   for (const FlowLaunch& L : launches) {
-    if (L.first != at || L.width < 1 || L.width > kBinMaxWidth || L.lds_bytes > kLdsLimitBytes) {
+    if (L.first != at || L.width < 1 || L.width > kBinMaxWidth || L.lds_bytes > kLdsLimitBytes || L.coop < 1 ||
+        (L.coop > 1 && L.width > 1) || L.width * L.coop > kBinMaxWidth) {
       why = "flow launch record";
       return false;
     }

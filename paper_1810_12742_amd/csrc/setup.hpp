@@ -432,9 +432,11 @@ static_assert(sizeof(KFlowJob) == 64, "one scalar load");
 // Launches of the flow kernel: bins of up to `width` groups that share one
 // workgroup's LDS, one wave each.
 struct FlowLaunch {
-  int32_t lds_bytes, width;   // LDS and waves per workgroup
+  int32_t lds_bytes, width;   // LDS and groups per workgroup
   int64_t first;              // first job; bin b holds jobs first + b width ...
   int32_t bins;
+  int32_t coop;               // waves per group (1 when groups share a workgroup)
+  int32_t threads() const { return 64 * width * coop; }
 };
 
 struct HostPlan {

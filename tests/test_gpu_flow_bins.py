@@ -38,17 +38,18 @@ def solve_and_check(sizes, **opts):
     p.close()
 
 
-# one cell each: the staging batches hold 384, 448 and 640 compartments (by right-hand
-# side), two in flight, the rest one after the other
-@pytest.mark.parametrize("n", [1, 63, 384, 385, 448, 640, 641, 768, 896, 897, 1280, 1281, 1921, 5000])
+# a group to a workgroup of four waves: a batch holds 16, 11 or 10 elements a thread by
+# right-hand side (4,096, 2,816, 2,560 compartments), two batches in flight
+@pytest.mark.parametrize("n", [1, 63, 64, 255, 256, 257, 2560, 2561, 2816, 2817, 4096, 4097, 5000, 5500])
 def test_one_cell_at_the_staging_batch_edges(n):
     solve_and_check([n])
 
 
 # groups of one cell each (1,000 compartments do not pair under the default cap):
-# one group per workgroup up to 256, bins of 1 to 8 above; mixed sizes in one bin;
+# one group per workgroup (of four or two waves) up to 1,023, bins of 2 to 8 above, there
+# with batches of 1,024, 704 and 640 compartments; mixed sizes in one bin;
 # groups that are not one user range (cells sorted by size)
-@pytest.mark.parametrize("cells,opts", [(256, {}), (257, {}), (1023, {}), (1024, {}), (2500, {}),
+@pytest.mark.parametrize("cells,opts", [(256, {}), (257, {}), (512, {}), (513, {}), (1023, {}), (1024, {}), (2500, {}),
                                         (700, dict(cell_order=1))])
 def test_bins_of_mixed_groups(cells, opts):
     rng = np.random.default_rng(cells)
@@ -97,12 +98,13 @@ def test_refined_solve_of_scheduled_and_level_groups(comb, sweeps):
 
 
 # Captured loops against the same steps one by one, bit for bit, and against the
-# oracle's loop.  Sizes around the elements that a lane keeps in registers (640
-# with noise, 1,024 with a current, 1,536 without), several cells in a group,
-# groups that are not one user range, loops of more than one launch (256 steps).
+# oracle's loop.  Sizes around the elements that a group's threads keep in registers
+# (24 or, with a current, 18 each, in one to four waves), several cells in a group, groups
+# that are not one user range, loops of more than one launch (256 steps).
 @pytest.mark.parametrize("form", ["cv", "current", "noise"])
 @pytest.mark.parametrize("sizes,steps,opts", [
-    ([640], 3, {}), ([641], 2, {}), ([1024, 1025], 3, {}), ([1536, 1537, 2100], 2, {}),
+    ([4608], 3, {}), ([4609], 2, {}), ([5500], 2, {}), ([1, 64, 256, 257], 3, {}),
+    ([2304, 2305] * 270, 2, {}), ([1152, 1153, 1536, 1537, 2100] * 220, 2, {}),
     ([1] * 130 + [40] * 30, 5, {}), ([30, 900, 31, 1700, 60] * 60, 3, dict(cell_order=1)),
     ([25, 300], 256, {}), ([25, 300], 257, {}), ([300], 1, {})])
 def test_captured_loop_equals_single_steps(form, sizes, steps, opts):

@@ -3,8 +3,8 @@ the single-step calls in turn.  The states and traces are the same bit for bit
 (the loop repeats the products of one step); the adjoints agree to 1e-13 of the
 largest value: the right-hand side at a root may be rounded once instead of
 twice, 2^-53 per step over at most 20 steps.  Shapes: cells around the elements
-a lane keeps in registers (1,024), many cells in a group (the first 64 roots are
-kept, the rest looked up), groups that are not one user range, cells too large
+a thread keeps in registers (18 with a current), many cells in a group (the first
+root of a thread is kept, the rest looked up), groups that are not one user range, cells too large
 for LDS, and plans of cell lanes (both fall back to single steps)."""
 import numpy as np
 import pytest
@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sizes,steps,opts", [
-    ([1], 3, {}), ([1024], 4, {}), ([1025, 700], 3, {}), ([2600], 2, {}),
-    ([1] * 63 + [5] * 70, 5, {}), ([30, 900, 31, 1700, 60] * 60, 3, dict(cell_order=1)),
+    ([1], 3, {}), ([4608], 4, {}), ([4609, 700], 3, {}), ([1152, 1153, 2600] * 350, 2, {}),
+    ([1] * 63 + [5] * 270, 5, {}), ([30, 900, 31, 1700, 60] * 60, 3, dict(cell_order=1)),
     ([20, 50], 257, {}), ([8000, 300], 3, {}), ([300] * 40, 4, dict(cell_lanes=2)), ([300], 1, {})])
 @pytest.mark.parametrize("current", [True, False])
 def test_steps_equal_single_calls(sizes, steps, opts, current):
