@@ -124,6 +124,7 @@ struct hines_plan {
   };
   std::vector<Bucket> buckets;        // level-synchronous groups, by LDS footprint
   std::vector<hines::FlowLaunch> flow_launches;  // flow groups, in bins
+  int32_t stream_count = 0, stream_lds = 0;      // streamed groups, LDS of the largest
   // FP32+refinement kernel (its own LDS layout): all groups, and the groups
   // that are not in flow_launches
   std::vector<Bucket> mixed_buckets, mixed_level_buckets;
@@ -267,7 +268,7 @@ hipError_t launch_flow_run(const hines_plan* p, const hdev::FlowRun& L, const do
 // a step schedule: whole stretches of steps can stay in LDS
 bool flow_only(const hines_plan* p) {
   return !p->host.cl.built && !p->host.sq.built && !p->host.res.built && !p->flow_launches.empty() &&
-         p->buckets.empty();
+         p->buckets.empty() && p->stream_count == 0;
 }
 
 // one instantiation of the resident kernel per LDS class (plane stride S)
@@ -331,9 +332,55 @@ hipError_t launch_resident(const hines_plan* p, const double* d, const double* u
   return e;
 }
 
-// the groups without a step schedule, level by level
-hipError_t launch_levels(const hines_plan* p, const RhsSpec& rs, const double* d, const double* u, double* x,
-                         hipStream_t s) {
+// The groups that exceed LDS, streamed: lay out, sweep, put back.  In a loop of
+// steps (more of them: the first of several, or one that follows) the factors
+// and x stay in step order between the steps.
+enum { kAlone = 0, kFirst = 1, kNext = 2, kLast = 3 };
+template <int RHS>
+void stage_stream(const DevTables& t, bool kept, const RhsSpec& rs, const double* d, const double* u, hipStream_t s) {
+  const dim3 grid((unsigned)((t.sused + 255) / 256)), block(256);
+  if constexpr (RHS != hdev::kFlowGiven) {
+    if (kept) {
+      hipLaunchKernelGGL((hdev::k_stream_stage<RHS, true>), grid, block, 0, s, t, rs, d, u);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((hdev::k_stream_stage<RHS, false>), grid, block, 0, s, t, rs, d, u);
+}
+hipError_t launch_stream(const hines_plan* p, const RhsSpec& rs, const double* d, const double* u, double* x,
+                         int where, hipStream_t s) {
+  const DevTables& t = p->t;
+  const bool kept = where == kNext || where == kLast;
+  if (rs.mode == hdev::kRhsGiven)
+    stage_stream<hdev::kFlowGiven>(t, kept, rs, d, u, s);
+  else if (rs.mode == hdev::kRhsNoise)
+    stage_stream<hdev::kFlowNoise>(t, kept, rs, d, u, s);
+  else if (rs.icur)
+    stage_stream<hdev::kFlowCVI>(t, kept, rs, d, u, s);
+  else
+    stage_stream<hdev::kFlowCV>(t, kept, rs, d, u, s);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)p->stream_count), block(64);
+  if (kept)
+    hipLaunchKernelGGL(hdev::k_stream_sweep<hdev::kStreamKept>, grid, block, p->stream_lds, s, t);
+  else if (where == kFirst)
+    hipLaunchKernelGGL(hdev::k_stream_sweep<hdev::kStreamKeep>, grid, block, p->stream_lds, s, t);
+  else
+    hipLaunchKernelGGL(hdev::k_stream_sweep<hdev::kStreamSolve>, grid, block, p->stream_lds, s, t);
+  e = hipGetLastError();
+  if (e != hipSuccess || where == kFirst || where == kNext) return e;
+  hipLaunchKernelGGL(hdev::k_stream_store, dim3((unsigned)((t.sused + 255) / 256)), dim3(256), 0, s, t, x);
+  return hipGetLastError();
+}
+
+// the groups that the flow kernel does not take: streamed, or level by level
+hipError_t launch_others(const hines_plan* p, const RhsSpec& rs, const double* d, const double* u, double* x,
+                         hipStream_t s, int where = kAlone) {
+  if (p->stream_count > 0) {
+    const hipError_t e = launch_stream(p, rs, d, u, x, where, s);
+    if (e != hipSuccess) return e;
+  }
   for (const auto& bk : p->buckets) {
     if (bk.count == 0) continue;
     switch (p->host.opt.group_width) {
@@ -377,7 +424,7 @@ hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d,
     return hipGetLastError();
   }
   const hipError_t e = launch_flow(p, rs, d, u, x, s);
-  return e == hipSuccess ? launch_levels(p, rs, d, u, x, s) : e;
+  return e == hipSuccess ? launch_others(p, rs, d, u, x, s) : e;
 }
 
 // What a refined solve converges to is the FP64 solution of the widened
@@ -438,6 +485,9 @@ hipError_t allow_lds(int T) {
                        (const void*)hdev::k_solve_flow<hdev::kFlowCV, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowCVI, double>,
                        (const void*)hdev::k_solve_flow<hdev::kFlowNoise, double>,
+                       (const void*)hdev::k_stream_sweep<hdev::kStreamSolve>,
+                       (const void*)hdev::k_stream_sweep<hdev::kStreamKeep>,
+                       (const void*)hdev::k_stream_sweep<hdev::kStreamKept>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeFast, true>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeBitwise, true>,
                        (const void*)hdev::k_solve_level<kGlobalT, hdev::kModeAscending, true>};
@@ -478,7 +528,7 @@ bool check_kernel_tables(const hines::HostPlan& P, std::string& why, bool& capac
       capacity = true;
       return false;
     }
-    if (G.ws_off >= 0 && G.ws_off + 3 * (int64_t)G.nunk > P.ws_doubles) {
+    if (G.ws_off >= 0 && P.stream.empty() && G.ws_off + 3 * (int64_t)G.nunk > P.ws_doubles) {
       why = "workspace range";
       return false;
     }
@@ -894,15 +944,16 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
     }
   }
   const hines::HostPlan& P = p->host;
-  // flow groups go in bins; the others (plans without a flow schedule, groups
-  // whose schedule does not fit LDS, and groups whose image lives in the
-  // workspace) in buckets by LDS footprint
+  // flow groups go in bins, groups that exceed LDS are streamed; the others
+  // (plans without a flow schedule, groups whose schedule does not fit LDS,
+  // groups whose image lives in the workspace) go in buckets by LDS footprint
   std::vector<hines::KFlowJob> fjobs;
   try {
     hines::pack_flow_bins(P, p->flow_launches, fjobs);
-    if (!o.host_only && !hines::check_flow_bins(P, p->flow_launches, fjobs, why)) {
+    if ((!o.host_only && !hines::check_flow_bins(P, p->flow_launches, fjobs, why)) ||
+        !hines::check_stream(P, parent, why)) {
       delete p;
-      return set_err(HINES_ERR_STATE, "flow bins: %s", why.c_str());
+      return set_err(HINES_ERR_STATE, "flow tables: %s", why.c_str());
     }
   } catch (const std::bad_alloc&) {
     delete p;
@@ -919,6 +970,7 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
     }
     const int64_t bytes = layout_of(G).bytes();
     p->max_lds = std::max(p->max_lds, bytes);
+    if (G.ws_off >= 0 && !P.stream.empty()) continue;
     if (G.ws_off >= 0) {
       members[nbk].push_back((int32_t)g);
       global_lds = std::max(global_lds, bytes);
@@ -929,6 +981,13 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
     if (k == nbk) k = nbk - 1;  // host_only plans only; checked above otherwise
     members[k].push_back((int32_t)g);
   }
+  // the streamed groups with the longest schedules first
+  std::vector<hines::KStream> streams = P.stream;
+  std::stable_sort(streams.begin(), streams.end(),
+                   [](const hines::KStream& a, const hines::KStream& b) { return a.nstep > b.nstep; });
+  p->stream_count = (int32_t)streams.size();
+  for (const hines::KStream& W : streams)
+    p->stream_lds = std::max(p->stream_lds, (int32_t)hines::stream_lds_bytes(W));
   std::vector<int32_t> glist;
   for (int k = 0; k <= nbk; ++k) {
     auto& m = members[k];
@@ -1014,6 +1073,14 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   const int64_t sz_fm = al((int64_t)P.fmask.size() * sizeof(uint64_t));
   const int64_t sz_fp = al((int64_t)P.fpos.size() * sizeof(uint16_t));
   const int64_t sz_fa = al((int64_t)P.faux.size() * sizeof(int16_t));
+  const int64_t sz_st = al((int64_t)streams.size() * sizeof(hines::KStream));
+  const int64_t sz_sr = al((int64_t)P.sidx.size() * sizeof(int32_t));
+  const int64_t sz_sq = al((int64_t)P.sat.size() * sizeof(hines::KStreamAt));
+  const int64_t sz_sk = al((int64_t)P.sblock.size() * sizeof(hines::KStreamBlock));
+  const int64_t sz_ss = al((int64_t)P.sstep.size() * sizeof(hines::KStreamStep));
+  const int64_t sz_sa = al((int64_t)P.saux.size() * sizeof(uint16_t));
+  const int64_t sused = hines::kStreamUnits * (int64_t)P.sblock.size(), sunits = sused + hines::kStreamSink;
+  const int64_t sz_sy = sused > 0 ? al(3 * 16 * sunits) : 0;
   const hines::CellLanes& CL = P.cl;
   const int64_t sz_cw = al((int64_t)CL.waves.size() * sizeof(hines::KCellWave));
   const int64_t sz_cb = al((int64_t)CL.base.size() * sizeof(int64_t));
@@ -1032,7 +1099,8 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   const int64_t sz_rg = al((int64_t)RP.groups.size() * sizeof(hines::KResGroup));
   const int64_t sz_rl = al((int64_t)p->res_list.size() * sizeof(int32_t));
   const int64_t sz_rb = al((int64_t)RP.blob.size());
-  const int64_t total = sz_br + sz_grp + sz_seg + sz_cell + sz_gl + sz_ws + sz_fl + sz_fm + sz_fp + sz_fa + sz_cw +
+  const int64_t total = sz_br + sz_grp + sz_seg + sz_cell + sz_gl + sz_ws + sz_fl + sz_fm + sz_fp + sz_fa + sz_st +
+                        sz_sr + sz_sq + sz_sk + sz_ss + sz_sa + sz_sy + sz_cw +
                         sz_cb + sz_cp + sz_cf + sz_cm + sz_cr + sz_cz + sz_sw + sz_sb + sz_sp + sz_sc + sz_sm +
                         sz_rg + sz_rl + sz_rb + 256;
   const int64_t scr_bytes = CL.nchunks * hines::kCellChunk * 64 * 16 + SQ.nchunks * hines::kSeqChunk * 64 * 16;
@@ -1104,6 +1172,28 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   p->t.faux = (const int16_t*)(base + off);
   if (e == hipSuccess) e = up(P.faux.data(), (int64_t)P.faux.size() * sizeof(int16_t), off);
   off += sz_fa;
+  p->t.stream = (const hines::KStream*)(base + off);
+  if (e == hipSuccess) e = up(streams.data(), (int64_t)streams.size() * sizeof(hines::KStream), off);
+  off += sz_st;
+  p->t.sidx = (const int32_t*)(base + off);
+  if (e == hipSuccess) e = up(P.sidx.data(), (int64_t)P.sidx.size() * sizeof(int32_t), off);
+  off += sz_sr;
+  p->t.sat = (const hines::KStreamAt*)(base + off);
+  if (e == hipSuccess) e = up(P.sat.data(), (int64_t)P.sat.size() * sizeof(hines::KStreamAt), off);
+  off += sz_sq;
+  p->t.sblock = (const hines::KStreamBlock*)(base + off);
+  if (e == hipSuccess) e = up(P.sblock.data(), (int64_t)P.sblock.size() * sizeof(hines::KStreamBlock), off);
+  off += sz_sk;
+  p->t.sstep = (const hines::KStreamStep*)(base + off);
+  if (e == hipSuccess) e = up(P.sstep.data(), (int64_t)P.sstep.size() * sizeof(hines::KStreamStep), off);
+  off += sz_ss;
+  p->t.saux = (const uint16_t*)(base + off);
+  if (e == hipSuccess) e = up(P.saux.data(), (int64_t)P.saux.size() * sizeof(uint16_t), off);
+  off += sz_sa;
+  p->t.sbuf = (double*)(base + off);
+  p->t.sunits = sunits;
+  p->t.sused = sused;
+  off += sz_sy;
   p->t.cwave = (const hines::KCellWave*)(base + off);
   if (e == hipSuccess) e = up(CL.waves.data(), (int64_t)CL.waves.size() * sizeof(hines::KCellWave), off);
   off += sz_cw;
@@ -1162,6 +1252,11 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   }
   // the kernel tables now live on the device
   std::vector<KBranch>().swap(p->host.kbranch);
+  std::vector<int32_t>().swap(p->host.sidx);
+  std::vector<hines::KStreamAt>().swap(p->host.sat);
+  std::vector<hines::KStreamBlock>().swap(p->host.sblock);
+  std::vector<hines::KStreamStep>().swap(p->host.sstep);
+  std::vector<uint16_t>().swap(p->host.saux);
   if (!o.keep_tables) {
     std::vector<uint64_t>().swap(p->host.fmask);
     std::vector<uint16_t>().swap(p->host.fpos);
@@ -1353,7 +1448,7 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   // every other plan, one step after the other.  The two kinds of groups share
   // no cell, so they are two branches of the graph.
   const bool flow = !factored && !p->host.sq.built && !p->host.cl.built && !p->flow_launches.empty();
-  const bool fork = flow && !p->buckets.empty();
+  const bool fork = flow && (!p->buckets.empty() || p->stream_count > 0);
   hipStream_t cs = nullptr, fs = nullptr;
   hipEvent_t forked = nullptr, joined = nullptr;
   hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
@@ -1408,7 +1503,8 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     rs.seed = noise_seed;
     rs.step = first_step + (uint32_t)k;
     rs.mode = noise ? hdev::kRhsNoise : hdev::kRhsCV;
-    e = flow ? launch_levels(p, rs, diag, upper, v, ls) : launch_solve(p, rs, diag, upper, v, cs);
+    const int where = nsteps == 1 ? kAlone : k == 0 ? kFirst : k + 1 < nsteps ? kNext : kLast;
+    e = flow ? launch_others(p, rs, diag, upper, v, ls, where) : launch_solve(p, rs, diag, upper, v, cs);
   }
   if (fork && capturing) {  // also after an error: a capture ends on its first stream with every branch joined
     hipError_t e2 = hipEventRecord(joined, ls);
@@ -1686,7 +1782,7 @@ hines_status hines_plan_info_get(const hines_plan* p, hines_plan_info* info) {
   info->ngroups = p->host.ngroups;
   info->nsegments = p->host.nseg;
   info->max_level = p->host.max_level;
-  int nb = (int)p->flow_launches.size();
+  int nb = (int)p->flow_launches.size() + (p->stream_count > 0);
   for (const auto& b : p->buckets) nb += b.count > 0;
   info->nclasses = nb;
   info->device_table_bytes = p->dev_bytes;

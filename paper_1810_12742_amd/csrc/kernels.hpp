@@ -36,6 +36,14 @@ struct DevTables {
   const int16_t* faux;       // flow kernel: parent position of every push
   const hines::KCellWave* cwave;  // cell-lane kernel: per wave
   const int64_t* cbase;           // cell-lane kernel: first user index of each lane's cell
+  const hines::KStream* stream;       // streamed groups of a flow plan
+  const int32_t* sidx;                // user index of their entries, eight to a block
+  const hines::KStreamAt* sat;        // the step of each block
+  const hines::KStreamBlock* sblock;  // slots of their blocks
+  const hines::KStreamStep* sstep;    // their steps
+  const uint16_t* saux;               // their push targets
+  double* sbuf;                       // their d, u and b: three planes of `sunits` units
+  int64_t sunits, sused;              // units of a plane; units of the groups (the rest is the sink)
   const uint16_t* cpos;           // cell-lane kernel: positions, staging order
   const uint8_t* cflag;           // cell-lane kernel: flags, cell-lane order
   const uint64_t* cmsrc;          // cell-lane kernel: mailbox source lists per lane
@@ -2236,6 +2244,292 @@ __global__ __launch_bounds__(64) void k_solve_res(DevTables tb, const double* __
     }
   }
 }
+// ---------------------------------------------------------------------------
+// Streamed groups: the flow schedule for cells whose image exceeds LDS.  The
+// whole device lays d, u and the right-hand side out in step order; one wave
+// per group sweeps them there, each step's operands loaded two steps ahead in
+// register sets used in turn, f over u and y over b, then x over y; the whole
+// device puts x back in user order.  What a light path pushes waits in an LDS
+// slot of its parent, where the parent's x waits for the path in the forward
+// sweep; the setup keeps two steps between a push and its taking.
+//
+// Bound by the serial length of the cell (about 60 steps a sweep for 20,000
+// compartments).  Gathering the operands from the user arrays in the sweep
+// itself, in one pass, was bound by the memory operations a wave can have in
+// flight (63): 143 us for 68 cells of 20,000, 163 with the gather turned
+// through LDS; the level-synchronous kernel took 273.  In a loop the sweep takes
+// 59 us a step of those cells and its right-hand sides, drawn on the whole
+// device, 17.  One solve of 64 cells of 20,000 takes 101 us (219 level by
+// level), of one of 7,000 44 (109), of 2,000 of 8,000 649 (698).
+// ---------------------------------------------------------------------------
+constexpr int kStreamSets = 3;  // register sets in turn: a step's loads run two steps ahead (three or four measured the same)
+enum : int { kStreamSolve = 0, kStreamKeep = 1, kStreamKept = 2 };
+
+// Thread v: sub-steps 2 p and 2 p + 1 (p = v % 4) of block v / 4, so that four
+// threads read one run of eight compartments and 64 write four runs of units.
+__device__ __forceinline__ int64_t stream_unit(const DevTables& tb, int64_t v) {
+  const hines::KStreamAt a = tb.sat[v >> 2];
+  return hines::kStreamUnits * a.first + (v & 3) * a.count + ((v >> 2) - a.first);
+}
+
+// d, u, b of every entry in step order (KEPT: b alone, from the x that stands
+// in its place).
+template <int RHS, bool KEPT = false>
+__global__ __launch_bounds__(256) void k_stream_stage(DevTables tb, RhsSpec rs, const double* __restrict__ d,
+                                                      const double* __restrict__ u) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= tb.sused) return;
+  const int2 idx = ((const int2*)tb.sidx)[v];
+  const int64_t unit = stream_unit(tb, v);
+  double2_t* B = (double2_t*)tb.sbuf + 2 * tb.sunits + unit;
+  double2_t D{1.0, 1.0}, U{0.0, 0.0}, b{0.0, 0.0}, old{0.0, 0.0};
+  if constexpr (KEPT) old = *B;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int32_t e = h ? idx.y : idx.x;
+    if (e == hines::kStreamPad) continue;
+    const int64_t i = e < 0 ? ~e : e;
+    if constexpr (!KEPT) {
+      D[h] = d[i];
+      if (e >= 0) U[h] = u[i];  // a root has no coupling
+    }
+    if constexpr (RHS == kFlowGiven) {
+      b[h] = rs.rhs[i];
+    } else {
+      const double c = rs.c[i], x = KEPT ? old[h] : rs.v[i];
+      if constexpr (RHS == kFlowCV) b[h] = flow_rhs(c, x);
+      if constexpr (RHS == kFlowCVI) b[h] = flow_rhs(c, x, rs.icur[i]);
+      if constexpr (RHS == kFlowNoise)
+        b[h] = flow_rhs(c, x, noise_draw(rs.seed, rs.step, (uint64_t)i, rs.sigma));
+    }
+  }
+  if constexpr (!KEPT) {
+    ((double2_t*)tb.sbuf)[unit] = D;
+    ((double2_t*)tb.sbuf)[tb.sunits + unit] = U;
+  }
+  *B = b;
+}
+
+// x in user order
+__global__ __launch_bounds__(256) void k_stream_store(DevTables tb, double* x) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= tb.sused) return;
+  const int2 idx = ((const int2*)tb.sidx)[v];
+  const double2_t b = ((const double2_t*)tb.sbuf)[2 * tb.sunits + stream_unit(tb, v)];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int32_t e = h ? idx.y : idx.x;
+    if (e != hines::kStreamPad) x[e < 0 ? ~e : e] = b[h];
+  }
+}
+
+// A step as a lane sees it.
+struct StreamStep {
+  uint64_t active, push;
+  int unit, stride;  // its first unit, and from one unit of its chunk to the next
+  int push_slot;     // where its contribution goes (its dummy slot: nowhere)
+  u32x4 slot;        // the slots of its compartments
+};
+struct StreamOps {
+  double2_t d[KC / 2], u[KC / 2], b[KC / 2];  // kStreamKept: 1 / d', f, b
+  StreamStep s;
+};
+struct StreamBack {
+  double2_t f[KC / 2], y[KC / 2];
+  StreamStep s;
+};
+
+// MODE: eliminate; eliminate and leave 1 / d' over d; sweep b with the factors left.
+template <int MODE>
+__global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
+  extern __shared__ __attribute__((aligned(16))) char stream_raw[];
+  const int lane = threadIdx.x;
+  const hines::KStream W = tb.stream[blockIdx.x];
+  const int F = W.nstep;
+  lds_char* lds = (lds_char*)stream_raw;
+  lds_d2* slots = (lds_d2*)lds;  // the dummies of the 64 lanes, then slot s at 63 + s
+  const lds_u4* steps = (const lds_u4*)(lds + hines::stream_step_offset(W.nslot));
+  const lds_u16* aux = (const lds_u16*)(lds + hines::stream_aux_offset(W.nslot, F));
+  const u32x4* blocks = (const u32x4*)(tb.sblock + W.blk_off);
+  const int64_t unit0 = hines::kStreamUnits * W.blk_off;
+  double2_t* D = (double2_t*)tb.sbuf + unit0;
+  double2_t* U = D + tb.sunits;
+  double2_t* B = U + tb.sunits;
+  const int sink = (int)(tb.sused - unit0) + lane;  // idle lanes write here, + 64 p
+  dma16<64>(tb.sstep + W.step_off, stream_raw + hines::stream_step_offset(W.nslot), 2 * F, lane);
+  dma4<64>(tb.saux + W.aux_off, stream_raw + hines::stream_aux_offset(W.nslot, F), (W.naux + 1) >> 1, lane);
+  for (int k = lane; k < 64 + W.nslot; k += 64) slots[k] = double2_t{0.0, 0.0};
+  __builtin_amdgcn_s_waitcnt(0);  // every DMA of this wave has landed
+  __builtin_amdgcn_wave_barrier();
+
+  // Records of steps: the raw words are read one step before they are moved to
+  // scalar registers, push targets and slots one step before they are used, so
+  // that no LDS read is waited for in the step that issues it (the sweep with
+  // kept factors took 70 us a step of 68 cells of 20,000 with those waits).
+  // Past either end the nearest step is read, and not used.
+  u32x4 rawa, rawb;
+  auto read_raw = [&](int t) {
+    const int k = max(0, min(t, F - 1));
+    rawa = steps[2 * k];
+    rawb = steps[2 * k + 1];
+  };
+  // the step whose words were read; idle lanes read the first busy lane's chunk
+  auto decode = [&](StreamStep& s, int& e, int& A) {
+    s.active = first_u64(rawa.x, rawa.y);
+    s.push = first_u64(rawa.z, rawa.w);
+    const int R = __builtin_amdgcn_readfirstlane((int)rawb.x), na = __builtin_amdgcn_readfirstlane((int)rawb.y);
+    const bool on = lane_in(s.active);
+    const int rank = on ? rank_in(s.active, 0) : 0;
+    A = __builtin_popcountll(s.active);
+    e = (int)hines::kStreamUnits * R + rank;
+    s.unit = on ? e : sink;
+    s.stride = on ? A : 64;
+    s.push_slot = lane_in(s.push) ? 63 + (int)aux[rank_in(s.push, na)] : lane;
+    s.slot = blocks[R + rank];
+  };
+  auto slot_of = [&](const u32x4& m, int j) {
+    const int k = (int)((m[j >> 1] >> (16 * (j & 1))) & 0xffffu);
+    return slots + (k ? 63 + k : lane);
+  };
+
+  // ---- backward sweep ----
+  {
+    auto load = [&](StreamOps& S, int t) {
+      int e, A;
+      decode(S.s, e, A);
+      read_raw(t + 1);
+#pragma unroll
+      for (int p = 0; p < KC / 2; ++p) {
+        S.d[p] = D[e + p * A];
+        S.u[p] = U[e + p * A];
+        S.b[p] = B[e + p * A];
+      }
+    };
+    auto take = [&](double2_t (&acc)[KC], const StreamStep& s) {
+#pragma unroll
+      for (int j = 0; j < KC; ++j) acc[j] = *slot_of(s.slot, j);
+    };
+    double fin = 0.0, uin = 0.0, bin = 0.0;
+    auto eliminate = [&](const StreamOps& S, const double2_t (&acc)[KC]) {
+      const StreamStep& s = S.s;
+      double2_t f2[KC / 2], r2[KC / 2], y2[KC / 2];
+#pragma unroll
+      for (int j = 0; j < KC; ++j) {
+        const double uu = S.u[j / 2][j % 2];
+        const double bl = __builtin_fma(-fin, bin, S.b[j / 2][j % 2] + acc[j].y);
+        double f, r;
+        if constexpr (MODE == kStreamKept) {
+          f = uu;
+          r = S.d[j / 2][j % 2];
+        } else {
+          const double dl = __builtin_fma(-fin, uin, S.d[j / 2][j % 2] + acc[j].x);
+          r = rcp_nr(dl);
+          f = uu * r;
+        }
+        f2[j / 2][j % 2] = f;
+        r2[j / 2][j % 2] = r;
+        y2[j / 2][j % 2] = bl * r;
+        fin = f;
+        uin = uu;
+        bin = bl;
+      }
+#pragma unroll
+      for (int p = 0; p < KC / 2; ++p) {
+        const int o = s.unit + p * s.stride;
+        if constexpr (MODE != kStreamKept) U[o] = f2[p];
+        if constexpr (MODE == kStreamKeep) D[o] = r2[p];
+        B[o] = y2[p];
+      }
+      if (lane_in(s.push)) {
+        lds_f64* q = (lds_f64*)(slots + s.push_slot);
+        if constexpr (MODE != kStreamKept) lds_add(q, -(fin * uin));
+        lds_add(q + 1, -(fin * bin));
+      }
+      fin = lane_in(s.active & ~s.push) ? fin : 0.0;
+    };
+    StreamOps S0, S1, S2;
+    double2_t a0[KC], a1[KC];
+    read_raw(0);
+    load(S0, 0);
+    load(S1, 1);
+    take(a0, S0.s);
+    // step t: the operands of t + 2, the slots of t + 1
+    auto step = [&](int t, StreamOps& now, StreamOps& next, StreamOps& ahead, double2_t (&acc)[KC],
+                    double2_t (&an)[KC]) {
+      load(ahead, t + 2);
+      take(an, next.s);
+      eliminate(now, acc);
+    };
+    for (int t = 0;; t += 6) {
+      step(t, S0, S1, S2, a0, a1);
+      if (t + 1 >= F) break;
+      step(t + 1, S1, S2, S0, a1, a0);
+      if (t + 2 >= F) break;
+      step(t + 2, S2, S0, S1, a0, a1);
+      if (t + 3 >= F) break;
+      step(t + 3, S0, S1, S2, a1, a0);
+      if (t + 4 >= F) break;
+      step(t + 4, S1, S2, S0, a0, a1);
+      if (t + 5 >= F) break;
+      step(t + 5, S2, S0, S1, a1, a0);
+      if (t + 6 >= F) break;
+    }
+  }
+  // the forward sweep reads back this wave's own stores
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+
+  // ---- forward sweep ----
+  {
+    auto load = [&](StreamBack& S, int t) {
+      int e, A;
+      decode(S.s, e, A);
+      read_raw(t - 1);
+#pragma unroll
+      for (int p = 0; p < KC / 2; ++p) {
+        S.f[p] = U[e + p * A];
+        S.y[p] = B[e + p * A];
+      }
+    };
+    double xp = 0.0, xq = 0.0;  // x of the lane's last step; x of a pushed path's parent, for the next
+    auto substitute = [&](const StreamBack& S, double xqn) {
+      const StreamStep& s = S.s;
+      const bool on = lane_in(s.active);
+      double xv = lane_in(s.push) ? xq : xp;
+      double2_t x2[KC / 2];
+#pragma unroll
+      for (int j = KC - 1; j >= 0; --j) {
+        xv = __builtin_fma(-S.f[j / 2][j % 2], xv, S.y[j / 2][j % 2]);
+        x2[j / 2][j % 2] = xv;
+      }
+#pragma unroll
+      for (int j = KC - 1; j >= 0; --j) *(lds_f64*)(on ? slot_of(s.slot, j) : slots + lane) = x2[j / 2][j % 2];
+#pragma unroll
+      for (int p = 0; p < KC / 2; ++p) B[s.unit + p * s.stride] = x2[p];
+      xp = on ? xv : xp;
+      xq = xqn;
+    };
+    StreamBack S0, S1, S2;
+    read_raw(F - 1);
+    load(S0, F - 1);
+    load(S1, F - 2);
+    // step t: the operands of t - 2, the parent's x for the paths entered at
+    // t - 1 (the last step is entered by roots alone)
+    auto step = [&](int t, StreamBack& now, StreamBack& next, StreamBack& ahead) {
+      load(ahead, t - 2);
+      substitute(now, slots[next.s.push_slot].x);
+    };
+    for (int t = F - 1;; t -= 3) {
+      step(t, S0, S1, S2);
+      if (t < 1) break;
+      step(t - 1, S1, S2, S0);
+      if (t < 2) break;
+      step(t - 2, S2, S0, S1);
+      if (t < 3) break;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Time loop with the factors kept (cell-lane plans).  The matrix of a time
 // loop does not change between steps, so the elimination of A (paper §2: the

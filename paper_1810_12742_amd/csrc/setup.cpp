@@ -15,11 +15,16 @@
 #include "setup.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <new>
 #include <numeric>
+#include <queue>
+#include <system_error>
+#include <thread>
 #include <unordered_map>
 
 namespace hines {
@@ -56,9 +61,38 @@ struct PathPlan {
 
 static inline int32_t nchunks(int32_t len) { return (len + kFlowChunk - 1) / kFlowChunk; }
 
-static bool schedule_paths(const std::vector<SchedIn>& br, PathPlan& pp) {
+// f(0) ... f(count - 1) on host threads: HINES_SETUP_THREADS of them if set, else
+// the host's cores, at most 16.  What the calls write must not depend on the
+// order; running out of memory in one is raised again here.
+template <typename F>
+static void host_parallel(int64_t count, F&& f) {
+  int64_t want = std::thread::hardware_concurrency();
+  if (const char* env = std::getenv("HINES_SETUP_THREADS")) want = std::atoll(env);
+  const int nth = (int)std::max<int64_t>(1, std::min<int64_t>({want, 16, (count + 15) / 16}));
+  std::atomic<int64_t> next{0};
+  std::atomic<bool> oom{false};
+  auto worker = [&]() {
+    try {
+      for (int64_t k; (k = next.fetch_add(1)) < count;) f(k);
+    } catch (const std::bad_alloc&) {
+      oom = true;
+    }
+  };
+  std::vector<std::thread> pool;
+  try {
+    for (int t = 1; t < nth; ++t) pool.emplace_back(worker);
+  } catch (const std::system_error&) {  // no more threads: the ones started and this one finish the work
+  } catch (const std::bad_alloc&) {
+    oom = true;
+  }
+  worker();
+  for (auto& th : pool) th.join();
+  if (oom) throw std::bad_alloc();
+}
+
+// heavy children, path tops (returned, ascending), lengths and positions
+static std::vector<int32_t> plan_paths(const std::vector<SchedIn>& br, PathPlan& pp) {
   const int32_t nb = (int32_t)br.size();
-  const int32_t K = kFlowChunk;
   std::vector<int32_t> fin(nb);
   pp.heavy.assign(nb, -1);
   for (int32_t b = nb - 1; b >= 0; --b) {  // compartment-level as soon as possible: heavy children
@@ -94,14 +128,78 @@ static bool schedule_paths(const std::vector<SchedIn>& br, PathPlan& pp) {
       }
     }
   }
-  // chunk index (within its parent path) of the compartment a light path attaches to:
-  // the far end of its parent branch, processed right after the path part below it
-  auto attach_chunk = [&](int32_t top) {
-    const int32_t pb = br[top].parent;
-    const int32_t q = pp.top_of[pb];
-    const int32_t npad = nchunks(pp.plen[q]) * K - pp.plen[q];
-    return (npad + pp.below[pb]) / K;
+  return tops;
+}
+
+// chunk index (within its parent path) of the compartment a light path attaches to:
+// the far end of its parent branch, processed right after the path part below it
+static int32_t attach_chunk_of(const std::vector<SchedIn>& br, const PathPlan& pp, int32_t top) {
+  const int32_t pb = br[top].parent;
+  const int32_t q = pp.top_of[pb];
+  const int32_t npad = nchunks(pp.plen[q]) * kFlowChunk - pp.plen[q];
+  return (npad + pp.below[pb]) / kFlowChunk;
+}
+
+// Schedule of a large group: the same rules (a light path ends two steps before
+// the chunk that takes its contribution is eliminated), placed by list
+// scheduling from the end, the path with the longest way to a leaf first, in
+// O(paths log paths): the placement above looks at every open path for every
+// path placed, and starts over with one step more until all fit.
+static void schedule_paths_large(const std::vector<SchedIn>& br, PathPlan& pp) {
+  const int32_t nb = (int32_t)br.size();
+  const std::vector<int32_t> tops = plan_paths(br, pp);
+  std::vector<int32_t> crit(nb, 0);  // steps from a path's last to the last of any path below it
+  std::vector<std::vector<int32_t>> light(nb);
+  auto release = [&](int32_t l) {  // reversed steps after its parent path's start
+    return nchunks(pp.plen[pp.top_of[br[l].parent]]) - 1 - attach_chunk_of(br, pp, l) + 2;
   };
+  for (auto it = tops.rbegin(); it != tops.rend(); ++it) {
+    const int32_t q = *it;
+    crit[q] = std::max(crit[q], nchunks(pp.plen[q]));
+    if (br[q].parent >= 0) {
+      const int32_t pq = pp.top_of[br[q].parent];
+      light[pq].push_back(q);
+      crit[pq] = std::max(crit[pq], release(q) + crit[q]);
+    }
+  }
+  pp.start.assign(nb, 0);
+  pp.lane.assign(nb, 0);
+  // reversed time: a path holds its lane for nchunks(plen) steps from its start
+  using Entry = std::pair<int32_t, int32_t>;
+  std::priority_queue<Entry> ready;                                            // (crit, -top)
+  std::priority_queue<Entry, std::vector<Entry>, std::greater<Entry>> waiting;  // (release, top)
+  std::priority_queue<Entry, std::vector<Entry>, std::greater<Entry>> lanes;    // (free from, lane)
+  for (int32_t l = 0; l < kSchedLanes; ++l) lanes.push({0, l});
+  for (int32_t q : tops)
+    if (br[q].parent < 0) ready.push({crit[q], -q});
+  int32_t now = 0, F = 0;
+  std::vector<int32_t> rstart(nb, 0);
+  while (!ready.empty() || !waiting.empty()) {
+    if (ready.empty()) now = std::max(now, waiting.top().first);
+    now = std::max(now, lanes.top().first);
+    while (!waiting.empty() && waiting.top().first <= now) {
+      ready.push({crit[waiting.top().second], -waiting.top().second});
+      waiting.pop();
+    }
+    const int32_t q = -ready.top().second;
+    ready.pop();
+    const int32_t ln = lanes.top().second;
+    lanes.pop();
+    rstart[q] = now;
+    pp.lane[q] = ln;
+    const int32_t end = now + nchunks(pp.plen[q]);
+    lanes.push({end, ln});
+    F = std::max(F, end);
+    for (int32_t l : light[q]) waiting.push({now + release(l), l});
+  }
+  for (int32_t q : tops) pp.start[q] = F - rstart[q] - nchunks(pp.plen[q]);
+  pp.makespan = F;
+}
+
+static bool schedule_paths(const std::vector<SchedIn>& br, PathPlan& pp) {
+  const int32_t nb = (int32_t)br.size();
+  const std::vector<int32_t> tops = plan_paths(br, pp);
+  auto attach_chunk = [&](int32_t top) { return attach_chunk_of(br, pp, top); };
   // as soon as possible in chunk steps (tops in descending id: light children first)
   std::vector<int32_t> pfin(nb, 0), kids_begin, kids;  // light child paths per path
   std::vector<std::vector<int32_t>> light(nb);
@@ -202,6 +300,131 @@ struct Builder {
   Status fail(Status s, const std::string& m) {
     err = m;
     return s;
+  }
+
+  // the branches of a group by group-local id, and the record of each
+  void group_branches(const KGroup& G, std::vector<SchedIn>& sin, std::vector<int32_t>& rec_of) const {
+    sin.assign(G.nbr, SchedIn{0, -1, 0, 0});
+    rec_of.assign(G.nbr, -1);
+    for (int32_t r = 0; r < G.nbr; ++r) {
+      const KBranch& B = P.kbranch[G.br_begin + r];
+      rec_of[B.self] = r;
+      sin[B.self] = SchedIn{B.lendir, -1, B.child0, B.nchild};
+    }
+    for (int32_t b = 0; b < G.nbr; ++b)
+      for (int32_t c = sin[b].child0; c < sin[b].child0 + sin[b].nchild; ++c) sin[c].parent = b;
+  }
+
+  // Step tables of the groups that exceed LDS; without them (one needs more
+  // LDS for its slots and steps than there is) those groups stay level-
+  // synchronous.
+  void stream_groups() {
+    struct Part {
+      KStream W{};
+      std::vector<int32_t> idx;
+      std::vector<KStreamBlock> block;
+      std::vector<KStreamStep> step;
+      std::vector<uint16_t> aux;
+    };
+    std::vector<int64_t> large;
+    for (int64_t g = 0; g < P.ngroups; ++g)
+      if (P.kgroup[g].ws_off >= 0) large.push_back(g);
+    if (large.empty()) return;
+    std::vector<Part> parts(large.size());
+    host_parallel((int64_t)large.size(), [&](int64_t k) {
+      Part& p = parts[k];
+      stream_group(P.kgroup[large[k]], p.W, p.idx, p.block, p.step, p.aux);
+    });
+    for (const Part& p : parts)
+      if (p.W.nslot > kStreamMaxSlots || stream_lds_bytes(p.W) > kLdsLimitBytes) return;
+    int64_t nblk = 0, nstep = 0;
+    for (Part& p : parts) {
+      p.W.blk_off = nblk;
+      p.W.step_off = nstep;
+      nblk += p.W.nblk;
+      nstep += (int64_t)p.step.size();
+    }
+    P.sidx.reserve(kFlowChunk * nblk);
+    P.sblock.reserve(nblk);
+    P.sat.reserve(nblk);
+    P.sstep.reserve(nstep);
+    for (Part& p : parts) {
+      P.sidx.insert(P.sidx.end(), p.idx.begin(), p.idx.end());
+      P.sblock.insert(P.sblock.end(), p.block.begin(), p.block.end());
+      for (const KStreamStep& S : p.step)
+        P.sat.insert(P.sat.end(), popc64(S.active), KStreamAt{(int32_t)(p.W.blk_off + S.block), popc64(S.active)});
+      P.sstep.insert(P.sstep.end(), p.step.begin(), p.step.end());
+      if (P.saux.size() & 1) P.saux.push_back(0);  // 4-byte aligned start of the group's push targets
+      p.W.aux_off = (int64_t)P.saux.size();
+      P.saux.insert(P.saux.end(), p.aux.begin(), p.aux.end());
+      P.stream.push_back(p.W);
+    }
+    P.saux.push_back(0);  // push targets are staged two at a time
+    P.ws_doubles = 0;     // the level kernel's image of these groups is not needed
+  }
+
+  void stream_group(const KGroup& G, KStream& W, std::vector<int32_t>& user, std::vector<KStreamBlock>& block,
+                    std::vector<KStreamStep>& st, std::vector<uint16_t>& aux) const {
+    const int32_t K = kFlowChunk;
+    std::vector<SchedIn> sin;
+    std::vector<int32_t> rec_of, tops, slot_user(G.nunk, -1), slot_of(G.nbr, 0);
+    PathPlan pp;
+    group_branches(G, sin, rec_of);
+    schedule_paths_large(sin, pp);
+    const int32_t F = pp.makespan;
+    W.nstep = F;
+    st.assign(F, KStreamStep{});
+    for (int32_t b = 0; b < G.nbr; ++b)
+      if (pp.top_of[b] == b) {
+        tops.push_back(b);
+        const int32_t s0 = pp.start[b], nc = nchunks(pp.plen[b]);
+        for (int32_t i = 0; i < nc; ++i) st[s0 + i].active |= 1ull << pp.lane[b];
+        if (sin[b].parent >= 0) st[s0 + nc - 1].push |= 1ull << pp.lane[b];
+      }
+    for (int32_t t = 0; t < F; ++t) {
+      st[t].block = W.nblk;
+      st[t].aux = W.naux;
+      W.nblk += popc64(st[t].active);
+      W.naux += popc64(st[t].push);
+    }
+    for (int c = 0; c < G.ncell; ++c) {  // LDS image slot -> user index
+      const KCell& C = P.kcell[G.cell_begin + c];
+      for (int32_t k = 0; k < C.n; ++k) slot_user[C.lds + k] = (int32_t)(C.user_lo + k);
+    }
+    user.assign((int64_t)K * W.nblk, kStreamPad);
+    block.assign(W.nblk, KStreamBlock{});
+    // block of the compartment with processing index idx (pads first) of path q
+    auto block_of = [&](int32_t q, int32_t idx) {
+      const KStreamStep& S = st[pp.start[q] + idx / K];
+      return S.block + popc64(S.active & ((1ull << pp.lane[q]) - 1));
+    };
+    for (int32_t q : tops) {
+      const int32_t npad = nchunks(pp.plen[q]) * K - pp.plen[q];
+      for (int32_t x = q; x >= 0; x = pp.heavy[x]) {
+        const KBranch& B = P.kbranch[G.br_begin + rec_of[x]];
+        for (int32_t k = 0; k < sin[x].len; ++k) {  // far end (k = len - 1) first
+          const int32_t idx = npad + pp.below[x] + (sin[x].len - 1 - k);
+          const int32_t i = slot_user[B.start + k];
+          user[(int64_t)K * block_of(q, idx) + idx % K] = k == 0 && sin[x].parent < 0 ? ~i : i;
+        }
+      }
+    }
+    // push targets in (step, lane) order; a slot for every branch whose far end
+    // takes pushed contributions
+    std::vector<std::pair<int32_t, int32_t>> ends;  // (step, lane) of a path's end, the path
+    for (int32_t q : tops)
+      if (sin[q].parent >= 0) ends.push_back({(pp.start[q] + nchunks(pp.plen[q]) - 1) * kSchedLanes + pp.lane[q], q});
+    std::sort(ends.begin(), ends.end());
+    for (const auto& e : ends) {
+      const int32_t pb = sin[e.second].parent, pq = pp.top_of[pb];
+      if (slot_of[pb] == 0) {
+        slot_of[pb] = ++W.nslot;
+        const int32_t npad = nchunks(pp.plen[pq]) * K - pp.plen[pq];
+        const int32_t idx = npad + pp.below[pb];
+        block[block_of(pq, idx)].slot[idx % K] = (uint16_t)W.nslot;
+      }
+      aux.push_back((uint16_t)slot_of[pb]);
+    }
   }
 
   Status validate() {
@@ -806,13 +1029,32 @@ struct Builder {
     if (opt.scheduler && !opt.bitwise && P.all_ascending && P.kernel_tables_fit && tips_only) {
       const int32_t K = kFlowChunk;
       P.kflow.assign(ng, KFlow{});
-      std::vector<SchedIn> sin;
       std::vector<int32_t> slot_elem, R, tops;
       std::vector<uint64_t> M, E;
-      PathPlan pp;
       bool all_ok = true;
       int64_t steps = 0, elems = 0;
+      // the schedules (most of a flow plan's setup) are independent of each
+      // other: host threads work out a batch of them ahead of its tables
+      constexpr int64_t kBatch = 4096;
+      struct Sched {
+        std::vector<SchedIn> sin;
+        std::vector<int32_t> rec_of;  // group-local BFS id -> record
+        PathPlan pp;
+        bool ok = true;
+      };
+      std::vector<Sched> batch(std::min(ng, kBatch));
       for (int64_t g = 0; g < ng && all_ok; ++g) {
+        if (g % kBatch == 0)
+          host_parallel(std::min(kBatch, ng - g), [&](int64_t k) {
+            if (P.kgroup[g + k].ws_off >= 0) return;
+            Sched& S = batch[k];
+            group_branches(P.kgroup[g + k], S.sin, S.rec_of);
+            S.ok = schedule_paths(S.sin, S.pp);
+          });
+        const Sched& S = batch[g % kBatch];
+        const std::vector<SchedIn>& sin = S.sin;
+        const std::vector<int32_t>& rec_of = S.rec_of;
+        const PathPlan& pp = S.pp;
         const KGroup& G = P.kgroup[g];
         KFlow& W = P.kflow[g];
         W.step_off = steps;
@@ -821,16 +1063,7 @@ struct Builder {
         W.aux_off = (int64_t)P.faux.size();
         if (G.ws_off >= 0) continue;  // level-synchronous from the workspace (all counts 0)
         const int32_t nbg = G.nbr;
-        sin.assign(nbg, SchedIn{0, -1, 0, 0});
-        std::vector<int32_t> rec_of(nbg, -1);  // group-local BFS id -> record
-        for (int32_t r = 0; r < nbg; ++r) {
-          const KBranch& B = P.kbranch[G.br_begin + r];
-          rec_of[B.self] = r;
-          sin[B.self] = SchedIn{B.lendir, -1, B.child0, B.nchild};
-        }
-        for (int32_t b = 0; b < nbg; ++b)
-          for (int32_t c = sin[b].child0; c < sin[b].child0 + sin[b].nchild; ++c) sin[c].parent = b;
-        if (!schedule_paths(sin, pp)) {
+        if (!S.ok) {
           all_ok = false;
           break;
         }
@@ -916,6 +1149,7 @@ struct Builder {
       }
       if (all_ok) {
         P.flow = true;
+        stream_groups();
       } else {  // level-synchronous kernel instead
         std::vector<KFlow>().swap(P.kflow);
         std::vector<uint64_t>().swap(P.fmask);
@@ -1154,6 +1388,124 @@ bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches,
     why = "flow groups without a bin";
     return false;
   }
+  return true;
+}
+
+bool check_stream(const HostPlan& P, const int32_t* parent, std::string& why) {
+  std::vector<int64_t> large;
+  for (int64_t g = 0; g < P.ngroups && !P.stream.empty(); ++g)
+    if (P.kgroup[g].ws_off >= 0) large.push_back(g);
+  if (large.size() != P.stream.size()) {
+    why = "stream group count";
+    return false;
+  }
+  // the first fault of one group, or null
+  auto check = [&](const KGroup& G, const KStream& W) -> const char* {
+    std::vector<int64_t> at;              // step of each of the group's compartments, by user index - lo
+    std::vector<int64_t> pushed, target;  // last step that adds into a slot, and for which compartment
+    if (W.nstep < 1 || W.nblk < 1 || W.blk_off < 0 || W.blk_off + W.nblk > (int64_t)P.sblock.size() ||
+        P.sidx.size() != kFlowChunk * P.sblock.size() || P.sat.size() != P.sblock.size() || W.step_off < 0 ||
+        W.step_off + W.nstep > (int64_t)P.sstep.size() || W.aux_off < 0 || (W.aux_off & 1) ||
+        W.aux_off + ((W.naux + 1) & ~1) > (int64_t)P.saux.size() ||
+        stream_lds_bytes(W) > kLdsLimitBytes) {
+      return "stream group record";
+    }
+    const KStreamStep* st = P.sstep.data() + W.step_off;
+    const KStreamBlock* block = P.sblock.data() + W.blk_off;
+    const int32_t* user = P.sidx.data() + kFlowChunk * W.blk_off;
+    int64_t lo = INT64_MAX, hi = 0, n = 0;
+    for (int c = 0; c < G.ncell; ++c) {
+      const KCell& C = P.kcell[G.cell_begin + c];
+      lo = std::min(lo, C.user_lo);
+      hi = std::max(hi, C.user_lo + C.n);
+      n += C.n;
+    }
+    at.assign(hi - lo, -1);
+    pushed.assign(W.nslot + 1, -1);
+    target.assign(W.nslot + 1, -1);
+    int32_t blk = 0, na = 0;
+    for (int32_t t = 0; t < W.nstep; ++t) {
+      if (st[t].block != blk || st[t].aux != na || (st[t].push & ~st[t].active) ||
+          blk >= W.nblk) {  // a step may have no busy lane, but its (unused) reads stay inside
+        return "stream step record";
+      }
+      blk += popc64(st[t].active);
+      na += popc64(st[t].push);
+    }
+    if (blk != W.nblk || na != W.naux) {
+      return "stream step counts";
+    }
+    // carry[l]: the compartment whose contribution lane l holds
+    int64_t carry[64], last_push = 0;
+    for (int64_t& v : carry) v = -1;
+    for (int32_t t = 0; t < W.nstep; ++t) {
+      for (int l = 0; l < 64; ++l) {
+        if (!((st[t].active >> l) & 1)) {
+          if (carry[l] >= 0) {
+            return "stream contribution dropped";
+          }
+          continue;
+        }
+        const int32_t rank = popc64(st[t].active & ((1ull << l) - 1));
+        const KStreamAt& A = P.sat[W.blk_off + st[t].block + rank];
+        if (A.first != W.blk_off + st[t].block || A.count != popc64(st[t].active)) return "stream block record";
+        for (int j = 0; j < kFlowChunk; ++j) {
+          const int32_t at_entry = user[(int64_t)kFlowChunk * (st[t].block + rank) + j];
+          const bool pad = at_entry == kStreamPad, root = !pad && at_entry < 0;
+          const int64_t i = pad ? lo : root ? ~at_entry : at_entry;
+          const int32_t slot = block[st[t].block + rank].slot[j];
+          bool good = i >= lo && i < hi && slot <= W.nslot;
+          if (good && pad) {
+            good = slot == 0 && carry[l] < 0;
+          } else if (good) {
+            good = at[i - lo] < 0 && (carry[l] < 0 || parent[carry[l]] == i) &&
+                   root == (parent[i] < 0);
+            // a slot's contributions arrive two steps before it is taken
+            if (slot) good = good && pushed[slot] >= 0 && pushed[slot] <= t - 2 && target[slot] == i;
+            if (slot) pushed[slot] = INT64_MAX;  // taken: nothing may arrive later
+            at[i - lo] = t;
+            carry[l] = i;
+            --n;
+          }
+          if (!good) {
+            return "stream entry";
+          }
+        }
+        if (carry[l] < 0) return "stream step without a compartment";
+        if ((st[t].push >> l) & 1) {
+          const uint16_t q = P.saux[W.aux_off + last_push++];
+          if (q < 1 || q > W.nslot || pushed[q] == INT64_MAX ||
+              (pushed[q] >= 0 && target[q] != parent[carry[l]])) {
+            return "stream push target";
+          }
+          pushed[q] = t;
+          target[q] = parent[carry[l]];
+          carry[l] = -1;
+        } else if (parent[carry[l]] < 0) {
+          carry[l] = -1;
+        }
+      }
+    }
+    for (int l = 0; l < 64; ++l)
+      if (carry[l] >= 0) {
+        return "stream contribution dropped";
+      }
+    for (int32_t q = 1; q <= W.nslot; ++q)
+      if (pushed[q] != INT64_MAX) {
+        return "stream slot not taken";
+      }
+    if (n != 0) {
+      return "compartments missing from a stream";
+    }
+    return nullptr;
+  };
+  std::vector<const char*> faults(large.size(), nullptr);
+  host_parallel((int64_t)large.size(), [&](int64_t k) { faults[k] = check(P.kgroup[large[k]], P.stream[k]); });
+  for (const char* f : faults)
+    if (f) {
+      why = f;
+      return false;
+    }
   return true;
 }
 

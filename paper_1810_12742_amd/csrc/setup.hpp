@@ -429,6 +429,44 @@ struct KFlowJob {
 };
 static_assert(sizeof(KFlowJob) == 64, "one scalar load");
 
+// Groups of a flow plan whose image exceeds LDS (single large cells) stream:
+// the chunk steps of the flow schedule on d, u, b laid out in step order in a
+// device scratch, with only the pushed contributions in LDS, one slot of 16
+// bytes per compartment that takes any.  Block R + k holds the chunk of the
+// lane of rank k among the A active lanes of a step, R the lane-chunks before
+// it.  Its sub-steps 2 p and 2 p + 1 are the two entries of unit 4 R + p A + k
+// of the group (16 bytes in each plane), so that a wave's access is contiguous.
+struct KStreamBlock {
+  uint16_t slot[kFlowChunk];  // the slot each compartment takes (0: none)
+};
+struct KStreamAt {
+  int32_t first, count;       // a block's step: its first block (of all groups'), its blocks
+};
+static_assert(sizeof(KStreamBlock) == 16, "one load a lane");
+constexpr int32_t kStreamMaxSlots = 0xffff;
+constexpr int32_t kStreamPad = INT32_MIN;  // index of a padding entry; ~i for a cell root i
+struct KStreamStep {  // per chunk step; 32 bytes
+  uint64_t active, push;  // lane masks
+  int32_t block, aux;     // blocks and pushes before the step
+  int32_t pad[2];
+};
+static_assert(sizeof(KStreamStep) == 32, "layout");
+struct KStream {      // per group
+  int64_t blk_off, step_off, aux_off;  // first block, step, push target (uint16 slots)
+  int32_t nstep, nblk, naux, nslot;
+};
+static_assert(sizeof(KStream) == 40, "layout");
+// LDS: 64 dummy slots (one a lane) and the slots, the steps, the push targets
+constexpr int64_t stream_step_offset(int32_t nslot) { return 16 * (64 + (int64_t)nslot); }
+constexpr int64_t stream_aux_offset(int32_t nslot, int32_t nstep) {
+  return stream_step_offset(nslot) + 32 * (int64_t)nstep;
+}
+constexpr int64_t stream_lds_bytes(const KStream& w) {
+  return (stream_aux_offset(w.nslot, w.nstep) + 2 * ((int64_t)w.naux + 2) + 15) & ~(int64_t)15;
+}
+constexpr int64_t kStreamUnits = kFlowChunk / 2;  // units a block
+constexpr int64_t kStreamSink = 64 * kStreamUnits;  // units written by idle lanes, after all groups' own
+
 // Launches of the flow kernel: bins of up to `width` groups that share one
 // workgroup's LDS, one wave each.
 struct FlowLaunch {
@@ -463,6 +501,13 @@ struct HostPlan {
   std::vector<uint64_t> fmask;    // [2 * total steps]: active and push masks per step
   std::vector<uint16_t> fpos;     // [elements of LDS groups]: position, bit 15 = cell root
   std::vector<int16_t> faux;      // [pushes]: parent position
+  // streamed groups (every group that exceeds LDS, or none)
+  std::vector<KStream> stream;
+  std::vector<int32_t> sidx;           // per block and sub-step: user index, kStreamPad, or ~index of a root
+  std::vector<KStreamAt> sat;          // per block
+  std::vector<KStreamBlock> sblock;
+  std::vector<KStreamStep> sstep;
+  std::vector<uint16_t> saux;
   int64_t ws_doubles = 0;         // global workspace for groups that exceed LDS
   CellLanes cl;                   // cell-lane kernel tables (opt.cell_lanes)
   SeqLanes sq;                    // index-order cell-lane tables (opt.cell_seq)
@@ -478,6 +523,10 @@ void pack_flow_bins(const HostPlan& P, std::vector<FlowLaunch>& launches, std::v
 // Every flow group is one job; the regions of a bin are disjoint and inside its LDS.
 bool check_flow_bins(const HostPlan& P, const std::vector<FlowLaunch>& launches, const std::vector<KFlowJob>& jobs,
                      std::string& why);
+
+// Replay of the streamed groups: every compartment once, after its children,
+// contributions in the lane or, two steps ahead, through a slot.
+bool check_stream(const HostPlan& P, const int32_t* parent, std::string& why);
 
 // Copy table `id` into out (int64), returns the element count (or -1).
 int64_t export_table(const HostPlan& p, int32_t id, int64_t* out, int64_t capacity);
