@@ -1357,10 +1357,9 @@ __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, cons
 //
 // Contributions to a parent (paper §2: d_p -= u_i f_i, b_p -= u_i y_i) stay in
 // registers when the parent is eliminated next.  The contributions of its
-// other children wait in one merged stack entry per pending parent; the top
-// entry lives in registers, the ones below in LDS slots (slot 0 is a dummy
-// that lanes without an entry to spill write into).  The forward sweep keeps
-// x of a compartment with several children on the same kind of stack.
+// other children wait in one merged stack entry per pending parent.  The
+// forward sweep keeps x of a compartment with several children on the same kind
+// of stack.
 // ---------------------------------------------------------------------------
 constexpr int CK = hines::kCellChunk;
 constexpr int CG = hines::kCellSlotCells;  // cells per gather slot (a run of CK lanes each)
@@ -1381,6 +1380,49 @@ typedef __attribute__((address_space(3))) char lds_char;
 // LDS double at an absolute byte address
 __device__ __forceinline__ lds_f64* lds_at(int a) { return (lds_f64*)(uintptr_t)(unsigned)a; }
 typedef unsigned int cflag_t __attribute__((ext_vector_type(CK / 4)));  // CK flag bytes of one lane
+
+// A lane's stack in LDS.  The entry that a step would take is read during the
+// step before it: the compartment whose entry it is has another child between
+// the last one that wrote the entry and itself, so nothing written by the step
+// before is taken.  No step waits for an LDS read that it issues itself: with
+// 64 lanes some lane takes or leaves an entry at most steps, and reads inside
+// branches are waited for where the branches join (8,191 C2 cells: 733 -> 712 us
+// in cell order, 525 -> 510 us in the walk layout).
+template <typename T>
+struct LaneStack {
+  typedef __attribute__((address_space(3))) T lds_t;
+  lds_t* slot;  // entry i (1, 2, ...) at slot[64 (i - 1)]
+  T next{};     // the top entry of the step to come
+  int m = 0;    // entries
+  // at the start of a step: its top entry; drop: taken for the last time, put:
+  // the step opens an entry (at here())
+  __device__ __forceinline__ T take(bool drop, bool put) {
+    const T v = next;
+    m += (put ? 1 : 0) - (drop ? 1 : 0);
+    next = *here();
+    return v;
+  }
+  __device__ __forceinline__ lds_t* here() const { return slot + 64 * max(m - 1, 0); }
+};
+__device__ __forceinline__ void stack_add(lds_d2* p, double2_t v) {
+  lds_add((lds_f64*)p, v.x);
+  lds_add((lds_f64*)p + 1, v.y);
+}
+__device__ __forceinline__ void stack_add(lds_f64* p, double v) { lds_add(p, v); }
+template <typename T>
+__device__ __forceinline__ void stack_leave(const LaneStack<T>& s, unsigned fe, T v) {
+  if (fe & hines::CF_PUSH) *s.here() = v;
+  if (fe & hines::CF_MERGE) stack_add(s.here(), v);
+}
+// The wait for an LDS read inside its branch: a value that may be in flight where
+// branches join makes every step wait there, for its own later reads too.
+template <typename T>
+__device__ __forceinline__ void settle(T& v) {
+  asm volatile("" : "+v"(v));
+}
+// some lane's flag is set (rare flags: a real branch, so that the steps without
+// one wait for nothing)
+__device__ __forceinline__ bool any_lane(bool v) { return __builtin_amdgcn_ballot_w64(v) != 0; }
 
 // The CK 16-bit positions of one lane's gather slots.
 struct CellPos {
@@ -1403,23 +1445,24 @@ __device__ __forceinline__ CellPos pos_ld(const u32x4* p) {
 }
 __device__ __forceinline__ cflag_t flag_ld(const cflag_t* p) { return __builtin_nontemporal_load(p); }
 
-template <int RHS>
+template <int RHS, typename MT>
 struct CellBatch {
-  double dv[CK], uv[CK], bv[CK];
+  MT dv[CK], uv[CK];  // as stored: widened when they are used, not while the loads are in flight
+  double bv[CK];
   double cv[(RHS == kFlowGiven || RHS == kCellFactor) ? 1 : CK];
   double iv[(RHS == kFlowCVI || RHS == kCellCond) ? CK : 1];
 };
 
 // MT: the storage type of the matrix (double, or float widened exactly)
 template <int RHS, typename MT>
-__device__ __forceinline__ void cell_load(CellBatch<RHS>& B, const RhsSpec& rs, const MT* __restrict__ d,
+__device__ __forceinline__ void cell_load(CellBatch<RHS, MT>& B, const RhsSpec& rs, const MT* __restrict__ d,
                                           const MT* __restrict__ u, const int64_t* base, const CellPos& P) {
 #pragma unroll
   for (int r = 0; r < CK; ++r) {
     const unsigned p = cell_pos(P, r);
     const int64_t i = base[r] + (p == hines::kCellPadPos ? 0u : p);
-    B.dv[r] = (double)d[i];
-    B.uv[r] = (double)u[i];
+    B.dv[r] = d[i];
+    B.uv[r] = u[i];
     if constexpr (RHS == kCellFactor) {
       B.bv[r] = 0.0;
     } else if constexpr (RHS == kFlowGiven) {
@@ -1435,21 +1478,26 @@ __device__ __forceinline__ void cell_load(CellBatch<RHS>& B, const RhsSpec& rs, 
 // Into the LDS planes.  A padding element reads its cell's first compartment
 // and a cell root has no coupling: both get u = 0, so they contribute nothing
 // (d > 0 and b of the first compartment keep every value finite).
-template <int RHS>
-__device__ __forceinline__ void cell_put(const CellBatch<RHS>& B, const RhsSpec& rs, const int64_t* base,
+template <int RHS, typename MT>
+__device__ __forceinline__ void cell_put(CellBatch<RHS, MT>& B, const RhsSpec& rs, const int64_t* base,
                                          const CellPos& P, lds_char* lds, int lane) {
   const int e = lane % CK;
+  if constexpr (sizeof(MT) == 4) {  // not widened before this point
+#pragma unroll
+    for (int r = 0; r < CK; ++r) __asm__ volatile("" : "+v"(B.dv[r]), "+v"(B.uv[r]));
+  }
 #pragma unroll
   for (int r = 0; r < CK; ++r) {
     const int c = CG * r + lane / CK;
     const unsigned p = cell_pos(P, r);
     double b = B.bv[r];
-    if constexpr (RHS != kFlowGiven && RHS != kCellFactor) b = B.cv[r] * B.bv[r];
-    if constexpr (RHS == kFlowCVI || RHS == kCellCond) b = b + B.iv[r];
+    if constexpr (RHS == kFlowCV) b = flow_rhs(B.cv[r], B.bv[r]);
+    if constexpr (RHS == kFlowCVI || RHS == kCellCond) b = flow_rhs(B.cv[r], B.bv[r], B.iv[r]);
     if constexpr (RHS == kFlowNoise)
-      b = b + noise_draw(rs.seed, rs.step, (uint64_t)(base[r] + (p == hines::kCellPadPos ? 0u : p)), rs.sigma);
-    const double uu = (p == 0u || p == hines::kCellPadPos) ? 0.0 : B.uv[r];
-    double dd = B.dv[r];
+      b = flow_rhs(B.cv[r], B.bv[r],
+                   noise_draw(rs.seed, rs.step, (uint64_t)(base[r] + (p == hines::kCellPadPos ? 0u : p)), rs.sigma));
+    const double uu = (p == 0u || p == hines::kCellPadPos) ? 0.0 : (double)B.uv[r];
+    double dd = (double)B.dv[r];
     if constexpr (RHS == kCellCond) dd = (B.cv[r] + dd) - uu;  // c + g + a of the edge to the parent
     *(lds_d2*)(lds + e * kCellRowDU + c * 16) = double2_t{dd, uu};
     *(lds_f64*)(lds + kCellLdsB + e * kCellRowB + c * 8) = b;
@@ -1464,9 +1512,9 @@ __device__ __forceinline__ void cell_put(const CellBatch<RHS>& B, const RhsSpec&
 // COND: the parent's diagonal also takes the child's edge conductance a = -u,
 // so the diagonal contribution is u f + u.
 template <bool FACTOR = false, bool COND = false>
-__device__ __forceinline__ void cell_backward(const cflag_t& f, const lds_d2* pdu, const lds_f64* pb, lds_d2* stk,
-                                              lds_d2* mb, int lane, double& cd, double& cb, double& td, double& tb,
-                                              int& m, double2_t* fy, unsigned& msrc) {
+__device__ __forceinline__ void cell_backward(const cflag_t& f, const lds_d2* pdu, const lds_f64* pb,
+                                              LaneStack<double2_t>& stk, lds_d2* mb, int lane, double& cd, double& cb,
+                                              double2_t* fy, unsigned& msrc) {
 #pragma unroll
   for (int e = 0; e < CK; ++e) {
     const unsigned fe = cell_byte(f, e);
@@ -1474,36 +1522,27 @@ __device__ __forceinline__ void cell_backward(const cflag_t& f, const lds_d2* pd
     double dd = du.x, bb = pb[e * (kCellRowB / 8)];
     const double uu = du.y;
     const double kc = (fe & hines::CF_TIP) ? 0.0 : 1.0;  // the carry enters unless this is a tip
+    // the merged entry of the other children
+    const bool pop = (fe & hines::CF_POP) != 0;
+    const double2_t entry = stk.take(pop, (fe & hines::CF_PUSH) != 0);
     dd = __builtin_fma(-kc, cd, dd);
     bb = __builtin_fma(-kc, cb, bb);
-    if (fe & hines::CF_MBIN) {  // a cut-off child's contribution, posted at an earlier step
-      const double2_t mv = mb[msrc & 63u];
-      msrc >>= 6;
-      dd = dd - mv.x;
-      bb = bb - mv.y;
+    if (any_lane(fe & hines::CF_MBIN)) {
+      if (fe & hines::CF_MBIN) {  // a cut-off child's contribution, posted at an earlier step
+        double2_t mv = mb[msrc & 63u];
+        settle(mv);
+        msrc >>= 6;
+        dd = dd - mv.x;
+        bb = bb - mv.y;
+      }
     }
-    if (fe & hines::CF_POP) {  // the merged entry of the other children; refill the top
-      dd = dd - td;
-      bb = bb - tb;
-      m -= 1;
-      const double2_t t = stk[64 * m];
-      td = t.x;
-      tb = t.y;
-    }
+    dd = dd - (pop ? entry.x : 0.0);
+    bb = bb - (pop ? entry.y : 0.0);
     const double rr = rcp_nr(dd);
     const double fv = uu * rr, yv = bb * rr;
     cd = COND ? __builtin_fma(uu, fv, uu) : uu * fv;
     cb = fv * bb;
-    if (fe & hines::CF_PUSH) {
-      stk[64 * m] = double2_t{td, tb};
-      m += 1;
-      td = cd;
-      tb = cb;
-    }
-    if (fe & hines::CF_MERGE) {
-      td = td + cd;
-      tb = tb + cb;
-    }
+    stack_leave(stk, fe, double2_t{cd, cb});
     if (fe & hines::CF_MBOUT) mb[lane] = double2_t{cd, cb};
     fy[e] = double2_t{fv, FACTOR ? rr : yv};
   }
@@ -1512,26 +1551,21 @@ __device__ __forceinline__ void cell_backward(const cflag_t& f, const lds_d2* pd
 // Forward substitution of one chunk (steps in reverse); x per step into the
 // b plane, then through the gather mapping to the user order.
 __device__ __forceinline__ void cell_forward(const cflag_t& f, const CellPos& P, const double2_t* fy,
-                                             lds_f64* pb, const lds_f64* xrd, lds_f64* stx, lds_d2* mb, int lane,
-                                             double& xc, double& xt, int& m, double* x, const int64_t* base,
-                                             unsigned& msrc) {
+                                             lds_f64* pb, const lds_f64* xrd, LaneStack<double>& stx, lds_d2* mb,
+                                             int lane, double& xc, double* x, const int64_t* base, unsigned& msrc) {
 #pragma unroll
   for (int e = CK - 1; e >= 0; --e) {
     const unsigned fe = cell_byte(f, e);
-    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? xt : xc;
-    if (fe & hines::CF_MBOUT) xp = mb[lane].x;  // x of the parent, posted by the other half
-    if (fe & hines::CF_PUSH) {
-      m -= 1;
-      xt = stx[64 * m];
+    const double entry = stx.take((fe & hines::CF_PUSH) != 0, (fe & hines::CF_POP) != 0);
+    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? entry : xc;
+    if (any_lane(fe & hines::CF_MBOUT)) {
+      if (fe & hines::CF_MBOUT) xp = mb[lane].x;  // x of the parent, posted by the other half
+      settle(xp);
     }
     // a padding step's factors were never stored: its value must not reach
     // the next step (a cell root multiplies it by f = 0)
     const double xv = (fe & hines::CF_PAD) ? 0.0 : __builtin_fma(-fy[e].x, xp, fy[e].y);
-    if (fe & hines::CF_POP) {
-      stx[64 * m] = xt;
-      m += 1;
-      xt = xv;
-    }
+    if (fe & hines::CF_POP) *stx.here() = xv;
     if (fe & hines::CF_MBIN) {
       mb[msrc & 63u].x = xv;
       msrc >>= 6;
@@ -1583,83 +1617,78 @@ __global__ __launch_bounds__(64) void k_solve_cells(DevTables tb, RhsSpec rs, co
   const u32x4* posv = (const u32x4*)(tb.cpos + W.chunk_off * hines::kCellChunkElems) + (CK / 8) * lane;
   const cflag_t* flv = (const cflag_t*)(tb.cflag + W.chunk_off * hines::kCellChunkElems) + lane;  // + 64 per chunk
   double2_t* scr = (double2_t*)tb.cscr + W.chunk_off * (CK * 64) + lane;  // + CK * 64 per chunk
-  lds_d2* stk = (lds_d2*)(lds + kCellLdsStack) + lane;                       // slot s at stk[64 s]
+  LaneStack<double2_t> stk{(lds_d2*)(lds + kCellLdsStack) + lane};
   lds_d2* mb = (lds_d2*)(lds + kCellLdsMail);
   const lds_d2* pdu = (const lds_d2*)lds + lane;
   lds_f64* pb = (lds_f64*)(lds + kCellLdsB) + lane;
 
-  // ---- backward sweep: the gather of chunk k + 1 and the stores of chunk
-  // k - 1 overlap the elimination of chunk k ----
-  CellPos P = pos_ld(posv);
-  cflag_t fl = flag_ld(flv);
-  CellBatch<RHS> B;
-  cell_load<RHS, MT>(B, rs, d, u, base, P);
-  CellPos Q = pos_ld(posv + PS * min(1, nk - 1));
-  double cd = 0.0, cb = 0.0, td = 0.0, tb_ = 0.0;
-  int m = 0;
+  // ---- backward sweep: the gather of chunk k + 1 is in flight while chunk k is
+  // eliminated.  Two sets of positions and flags are used in turn and every
+  // load is unconditional (past the end, the last chunk again): no copy at the
+  // end of a chunk waits for a load just issued.  Where few waves run (8,191 C2
+  // cells, FP32 storage: 443 of 1,024 SIMDs) a chunk's latency is the time; the
+  // copies, and widening each FP32 value as it arrived, cost 44 of 738 us ----
+  CellPos P0 = pos_ld(posv), P1 = pos_ld(posv + PS * min(1, nk - 1));
+  cflag_t f0 = flag_ld(flv), f1 = flag_ld(flv + 64 * min(1, nk - 1));
+  CellBatch<RHS, MT> B;
+  cell_load<RHS, MT>(B, rs, d, u, base, P0);
+  double cd = 0.0, cb = 0.0;
   double2_t fy[CK];
   const uint64_t ms = tb.cmsrc[(int64_t)blockIdx.x * 64 + lane];
   unsigned msb = (unsigned)ms, msf = (unsigned)(ms >> 32);
-  cflag_t fprev = fl;
-  for (int k = 0; k < nk; ++k) {
-    cell_put<RHS>(B, rs, base, P, lds, lane);
-    if (k > 0) {  // padding steps store nothing; the forward sweep reads their slots but
-                  // uses no value of a padding step (no carry or stack leaves one)
-      if constexpr (RHS == kCellFactor) {  // f and 1 / d' of every step at its walk slot
-        factor_store(fy, x, tb.cslots, W.chunk_off + k - 1, lane);
-      } else {
-        double2_t* sk = scr + (k - 1) * (CK * 64);
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the list is then plain data, not a load in flight
+  auto bstep = [&](int k, CellPos& P, const CellPos& Pn, cflag_t& f) {
+    cell_put<RHS, MT>(B, rs, base, P, lds, lane);
+    cell_load<RHS, MT>(B, rs, d, u, base, Pn);  // chunk k + 1
+    P = pos_ld(posv + PS * min(k + 2, nk - 1));
+    const cflag_t fc = f;
+    cell_backward<RHS == kCellFactor, RHS == kCellCond>(fc, pdu, pb, stk, mb, lane, cd, cb, fy, msb);
+    // padding steps store nothing; the forward sweep reads their slots but
+    // uses no value of a padding step (no carry or stack leaves one)
+    if constexpr (RHS == kCellFactor) {  // f and 1 / d' of every step at its walk slot
+      factor_store(fy, x, tb.cslots, W.chunk_off + k, lane);
+    } else {
+      double2_t* sk = scr + (int64_t)k * (CK * 64);
 #pragma unroll
-        for (int e = 0; e < CK; ++e)
-          if (!(cell_byte(fprev, e) & hines::CF_PAD)) __builtin_nontemporal_store(fy[e], sk + e * 64);
-      }
+      for (int e = 0; e < CK; ++e)
+        if (!(cell_byte(fc, e) & hines::CF_PAD)) __builtin_nontemporal_store(fy[e], sk + e * 64);
     }
-    const cflag_t f = fl;
-    fprev = f;
-    if (k + 1 < nk) {
-      fl = flag_ld(flv + 64 * (k + 1));
-      cell_load<RHS, MT>(B, rs, d, u, base, Q);
-      P = Q;
-      Q = pos_ld(posv + PS * min(k + 2, nk - 1));
-    }
-    cell_backward<RHS == kCellFactor, RHS == kCellCond>(f, pdu, pb, stk, mb, lane, cd, cb, td, tb_, m, fy, msb);
+    f = flag_ld(flv + 64 * min(k + 2, nk - 1));
+  };
+  for (int k = 0;; k += 2) {
+    bstep(k, P0, P1, f0);
+    if (k + 1 >= nk) break;
+    bstep(k + 1, P1, P0, f1);
+    if (k + 2 >= nk) break;
   }
-  if constexpr (RHS == kCellFactor) {  // the last chunk's factors
-    factor_store(fy, x, tb.cslots, W.chunk_off + nk - 1, lane);
-    return;
-  }
-  // chunk nk - 1 stays in registers: it is the first one of the forward sweep.
-  // The forward sweep reads back this wave's own scratch stores.
+  if constexpr (RHS == kCellFactor) return;
+  // the forward sweep reads back this wave's own scratch stores
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
-  // ---- forward sweep: two register sets, the loads of the next chunk overlap
-  // the substitution of this one ----
-  lds_f64* stx = (lds_f64*)(lds + kCellLdsStack) + lane;  // slot s at stx[64 s]
+  // ---- forward sweep: two register sets in turn, the loads of the next chunk
+  // in flight while this one is substituted (before the first one, the first
+  // again).  Chunk nk - 1 is still in fy. ----
+  LaneStack<double> stx{(lds_f64*)(lds + kCellLdsStack) + lane};
   const lds_f64* xrd = (const lds_f64*)(lds + kCellLdsB + (lane % CK) * kCellRowB) + lane / CK;
-  double xc = 0.0, xt = 0.0;
-  m = 0;
-  CellPos PA = pos_ld(posv + PS * (nk - 1)), PB = PA;
-  cflag_t fa = flag_ld(flv + 64 * (nk - 1)), fb_ = fa;
+  double xc = 0.0;
+  P0 = pos_ld(posv + PS * (nk - 1));
+  f0 = flag_ld(flv + 64 * (nk - 1));
   double2_t fb[CK];
+  auto fload = [&](double2_t* fy_, CellPos& P, cflag_t& f, int k) {
+    const int kc = max(k, 0);
+    const double2_t* sk = scr + (int64_t)kc * (CK * 64);
+#pragma unroll
+    for (int e = 0; e < CK; ++e) fy_[e] = __builtin_nontemporal_load(sk + e * 64);
+    P = pos_ld(posv + PS * kc);
+    f = flag_ld(flv + 64 * kc);
+  };
   for (int k = nk - 1;; k -= 2) {
-    if (k >= 1) {
-      const double2_t* sk = scr + (k - 1) * (CK * 64);
-#pragma unroll
-      for (int e = 0; e < CK; ++e) fb[e] = __builtin_nontemporal_load(sk + e * 64);
-      PB = pos_ld(posv + PS * (k - 1));
-      fb_ = flag_ld(flv + 64 * (k - 1));
-    }
-    cell_forward(fa, PA, fy, pb, xrd, stx, mb, lane, xc, xt, m, x, base, msf);
+    fload(fb, P1, f1, k - 1);
+    cell_forward(f0, P0, fy, pb, xrd, stx, mb, lane, xc, x, base, msf);
     if (k < 1) break;
-    if (k >= 2) {
-      const double2_t* sk = scr + (k - 2) * (CK * 64);
-#pragma unroll
-      for (int e = 0; e < CK; ++e) fy[e] = __builtin_nontemporal_load(sk + e * 64);
-      PA = pos_ld(posv + PS * (k - 2));
-      fa = flag_ld(flv + 64 * (k - 2));
-    }
-    cell_forward(fb_, PB, fb, pb, xrd, stx, mb, lane, xc, xt, m, x, base, msf);
+    fload(fy, P0, f0, k - 2);
+    cell_forward(f1, P1, fb, pb, xrd, stx, mb, lane, xc, x, base, msf);
     if (k < 2) break;
   }
 }
@@ -1732,11 +1761,12 @@ __device__ __forceinline__ void seq_put(const SeqSet<RHS>& S, const RhsSpec& rs,
   for (int r = 0; r < SK; ++r) {
     const int c = SG * r + lane / SK;
     double bb = S.b[r];
-    if constexpr (RHS != kFlowGiven) bb = S.c[r] * S.b[r];
-    if constexpr (RHS == kFlowCVI) bb = bb + S.i[r];
+    if constexpr (RHS == kFlowCV) bb = flow_rhs(S.c[r], S.b[r]);
+    if constexpr (RHS == kFlowCVI) bb = flow_rhs(S.c[r], S.b[r], S.i[r]);
     if constexpr (RHS == kFlowNoise) {
       const unsigned p = seq_field(S.P, r);
-      bb = bb + noise_draw(rs.seed, rs.step, (uint64_t)(base[r] + (p == hines::kCellPadPos ? 0u : p)), rs.sigma);
+      bb = flow_rhs(S.c[r], S.b[r],
+                    noise_draw(rs.seed, rs.step, (uint64_t)(base[r] + (p == hines::kCellPadPos ? 0u : p)), rs.sigma));
     }
     *(lds_d2*)(lds + e * kSeqRowDU + c * 16) = double2_t{S.d[r], S.u[r]};
     *(lds_f64*)(lds + kSeqLdsB + e * kSeqRowB + c * 8) = bb;
@@ -2694,37 +2724,35 @@ __device__ __forceinline__ void step_load_f(StepChunk<RHS>& C, const CellLoop& L
 template <int RHS>
 __device__ __forceinline__ void step_backward(const StepChunk<RHS>& C, const CellLoop& L, const hines::KCellWave& W,
                                               int k, int lane, int lo, int hi, double2_t* zp, int64_t base,
-                                              lds_f64* stk, lds_f64* mb, double& cb, double& tb, int& m,
-                                              unsigned& msrc) {
+                                              LaneStack<double>& stk, lds_f64* mb, double& cb, unsigned& msrc) {
   double y[CK];
 #pragma unroll
   for (int e = 0; e < CK; ++e) {
     const unsigned fe = cell_byte(C.fl, e);
-    double bb = pair_at(C.c, e) * pair_at(C.v, e);
-    if constexpr (RHS == kFlowCVI) bb = bb + pair_at(C.i, e);
+    double bb;
+    if constexpr (RHS == kFlowCV) bb = flow_rhs(pair_at(C.c, e), pair_at(C.v, e));
+    if constexpr (RHS == kFlowCVI) bb = flow_rhs(pair_at(C.c, e), pair_at(C.v, e), pair_at(C.i, e));
     if constexpr (RHS == kFlowNoise) {
       const unsigned p = cell_pos(C.p, e);
-      bb = bb + noise_draw(L.seed, L.step, (uint64_t)(base + (p == hines::kCellPadPos ? 0u : p)), L.sigma);
+      bb = flow_rhs(pair_at(C.c, e), pair_at(C.v, e),
+                    noise_draw(L.seed, L.step, (uint64_t)(base + (p == hines::kCellPadPos ? 0u : p)), L.sigma));
     }
     const double kc = (fe & hines::CF_TIP) ? 0.0 : 1.0;
+    const bool pop = (fe & hines::CF_POP) != 0;
+    const double entry = stk.take(pop, (fe & hines::CF_PUSH) != 0);
     bb = __builtin_fma(-kc, cb, bb);
-    if (fe & hines::CF_MBIN) {
-      bb = bb - mb[msrc & 63u];
-      msrc >>= 6;
+    if (any_lane(fe & hines::CF_MBIN)) {
+      if (fe & hines::CF_MBIN) {
+        double mv = mb[msrc & 63u];
+        settle(mv);
+        bb = bb - mv;
+        msrc >>= 6;
+      }
     }
-    if (fe & hines::CF_POP) {
-      bb = bb - tb;
-      m -= 1;
-      tb = stk[64 * m];
-    }
+    bb = bb - (pop ? entry : 0.0);
     y[e] = bb * pair_at(C.r, e);
     cb = pair_at(C.f, e) * bb;
-    if (fe & hines::CF_PUSH) {
-      stk[64 * m] = tb;
-      m += 1;
-      tb = cb;
-    }
-    if (fe & hines::CF_MERGE) tb = tb + cb;
+    stack_leave(stk, fe, cb);
     if (fe & hines::CF_MBOUT) mb[lane] = cb;
     if (e & 1) {
       const bool real = pair_real(k, e >> 1, lo, hi);
@@ -2735,24 +2763,20 @@ __device__ __forceinline__ void step_backward(const StepChunk<RHS>& C, const Cel
 
 template <int RHS>
 __device__ __forceinline__ void step_forward(const StepChunk<RHS>& C, const CellLoop& L, const hines::KCellWave& W,
-                                             int k, int lane, int lo, int hi, double2_t* zp, lds_f64* stk,
-                                             lds_f64* mb, double& xc, double& xt, int& m, unsigned& msrc) {
+                                             int k, int lane, int lo, int hi, double2_t* zp, LaneStack<double>& stk,
+                                             lds_f64* mb, double& xc, unsigned& msrc) {
   double x[CK];
 #pragma unroll
   for (int e = CK - 1; e >= 0; --e) {
     const unsigned fe = cell_byte(C.fl, e);
-    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? xt : xc;
-    if (fe & hines::CF_MBOUT) xp = mb[lane];
-    if (fe & hines::CF_PUSH) {
-      m -= 1;
-      xt = stk[64 * m];
+    const double entry = stk.take((fe & hines::CF_PUSH) != 0, (fe & hines::CF_POP) != 0);
+    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? entry : xc;
+    if (any_lane(fe & hines::CF_MBOUT)) {
+      if (fe & hines::CF_MBOUT) xp = mb[lane];
+      settle(xp);
     }
     const double xv = __builtin_fma(-pair_at(C.f, e), xp, pair_at(C.v, e));
-    if (fe & hines::CF_POP) {
-      stk[64 * m] = xt;
-      m += 1;
-      xt = xv;
-    }
+    if (fe & hines::CF_POP) *stk.here() = xv;
     if (fe & hines::CF_MBIN) {
       mb[msrc & 63u] = xv;
       msrc >>= 6;
@@ -2769,7 +2793,7 @@ __device__ __forceinline__ void step_forward(const StepChunk<RHS>& C, const Cell
 template <int RHS>
 __global__ __launch_bounds__(64) void k_cells_step(DevTables tb, CellLoop L) {
   __shared__ __attribute__((aligned(16))) double sraw[hines::kCellStack * 64 + 64];
-  lds_f64* stk = (lds_f64*)sraw + threadIdx.x;  // slot s at stk[64 s]
+  LaneStack<double> stk{(lds_f64*)sraw + threadIdx.x}, stx{(lds_f64*)sraw + threadIdx.x};  // backward, forward
   lds_f64* mb = (lds_f64*)sraw + hines::kCellStack * 64;
   const int lane = threadIdx.x;
   const hines::KCellWave W = tb.cwave[blockIdx.x];
@@ -2785,32 +2809,30 @@ __global__ __launch_bounds__(64) void k_cells_step(DevTables tb, CellLoop L) {
   double2_t* zp = (double2_t*)tb.czero + lane;
   lists_settled();
   // backward: y = (b - contributions) / d', in place of V
-  double cb = 0.0, tb_ = 0.0;
-  int m = 0;
+  double cb = 0.0;
   // the next chunk is loaded unconditionally (past the end, the last chunk
   // again, unused): loads under a branch would make the compiler wait for
   // every load in flight where the branches join
   step_load_b<RHS>(A, L, W, flv, 0, lane, lo, hi, zp);
   for (int k = 0;; k += 2) {
     step_load_b<RHS>(B, L, W, flv, min(k + 1, nk - 1), lane, lo, hi, zp);
-    step_backward<RHS>(A, L, W, k, lane, lo, hi, zp, base, stk, mb, cb, tb_, m, msb);
+    step_backward<RHS>(A, L, W, k, lane, lo, hi, zp, base, stk, mb, cb, msb);
     if (k + 1 >= nk) break;
     step_load_b<RHS>(A, L, W, flv, min(k + 2, nk - 1), lane, lo, hi, zp);
-    step_backward<RHS>(B, L, W, k + 1, lane, lo, hi, zp, base, stk, mb, cb, tb_, m, msb);
+    step_backward<RHS>(B, L, W, k + 1, lane, lo, hi, zp, base, stk, mb, cb, msb);
     if (k + 2 >= nk) break;
   }
   // the forward sweep reads back this wave's own stores
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  double xc = 0.0, xt = 0.0;
-  m = 0;
+  double xc = 0.0;
   step_load_f<RHS>(A, L, W, flv, nk - 1, lane, lo, hi, zp);
   for (int k = nk - 1;; k -= 2) {
     step_load_f<RHS>(B, L, W, flv, max(k - 1, 0), lane, lo, hi, zp);
-    step_forward<RHS>(A, L, W, k, lane, lo, hi, zp, stk, mb, xc, xt, m, msf);
+    step_forward<RHS>(A, L, W, k, lane, lo, hi, zp, stx, mb, xc, msf);
     if (k < 1) break;
     step_load_f<RHS>(A, L, W, flv, max(k - 2, 0), lane, lo, hi, zp);
-    step_forward<RHS>(B, L, W, k - 1, lane, lo, hi, zp, stk, mb, xc, xt, m, msf);
+    step_forward<RHS>(B, L, W, k - 1, lane, lo, hi, zp, stx, mb, xc, msf);
     if (k < 2) break;
   }
 }
@@ -2862,8 +2884,8 @@ __device__ __forceinline__ void walk_load_f(WalkChunk& C, const WalkSolve& L, co
 }
 
 __device__ __forceinline__ void walk_backward(const WalkChunk& C, const WalkSolve& L, int64_t chunk, int lane,
-                                              lds_d2* stk, lds_d2* mb, double& cd, double& cb, double& td,
-                                              double& tb, int& m, unsigned& msrc) {
+                                              LaneStack<double2_t>& stk, lds_d2* mb, double& cd, double& cb,
+                                              unsigned& msrc) {
   double fv[CK], yv[CK];
 #pragma unroll
   for (int e = 0; e < CK; ++e) {
@@ -2871,37 +2893,27 @@ __device__ __forceinline__ void walk_backward(const WalkChunk& C, const WalkSolv
     double dd = pair_at(C.d, e), bb = pair_at(C.b, e);
     const double uu = (fe & (hines::CF_ROOT | hines::CF_PAD)) ? 0.0 : pair_at(C.u, e);
     const double kc = (fe & hines::CF_TIP) ? 0.0 : 1.0;
+    const bool pop = (fe & hines::CF_POP) != 0;
+    const double2_t entry = stk.take(pop, (fe & hines::CF_PUSH) != 0);
     dd = __builtin_fma(-kc, cd, dd);
     bb = __builtin_fma(-kc, cb, bb);
-    if (fe & hines::CF_MBIN) {
-      const double2_t mv = mb[msrc & 63u];
-      msrc >>= 6;
-      dd = dd - mv.x;
-      bb = bb - mv.y;
+    if (any_lane(fe & hines::CF_MBIN)) {
+      if (fe & hines::CF_MBIN) {
+        double2_t mv = mb[msrc & 63u];
+        settle(mv);
+        msrc >>= 6;
+        dd = dd - mv.x;
+        bb = bb - mv.y;
+      }
     }
-    if (fe & hines::CF_POP) {
-      dd = dd - td;
-      bb = bb - tb;
-      m -= 1;
-      const double2_t t = stk[64 * m];
-      td = t.x;
-      tb = t.y;
-    }
+    dd = dd - (pop ? entry.x : 0.0);
+    bb = bb - (pop ? entry.y : 0.0);
     const double rr = rcp_nr(dd);
     fv[e] = uu * rr;
     yv[e] = bb * rr;
     cd = uu * fv[e];
     cb = fv[e] * bb;
-    if (fe & hines::CF_PUSH) {
-      stk[64 * m] = double2_t{td, tb};
-      m += 1;
-      td = cd;
-      tb = cb;
-    }
-    if (fe & hines::CF_MERGE) {
-      td = td + cd;
-      tb = tb + cb;
-    }
+    stack_leave(stk, fe, double2_t{cd, cb});
     if (fe & hines::CF_MBOUT) mb[lane] = double2_t{cd, cb};
   }
 #pragma unroll
@@ -2913,24 +2925,19 @@ __device__ __forceinline__ void walk_backward(const WalkChunk& C, const WalkSolv
 }
 
 __device__ __forceinline__ void walk_forward(const WalkChunk& C, const WalkSolve& L, int64_t chunk, int lane,
-                                             lds_f64* stx, lds_d2* mb, double& xc, double& xt, int& m,
-                                             unsigned& msrc) {
+                                             LaneStack<double>& stx, lds_d2* mb, double& xc, unsigned& msrc) {
   double x[CK];
 #pragma unroll
   for (int e = CK - 1; e >= 0; --e) {
     const unsigned fe = cell_byte(C.fl, e);
-    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? xt : xc;
-    if (fe & hines::CF_MBOUT) xp = mb[lane].x;  // x of the parent, posted by the receiving lane
-    if (fe & hines::CF_PUSH) {
-      m -= 1;
-      xt = stx[64 * m];
+    const double entry = stx.take((fe & hines::CF_PUSH) != 0, (fe & hines::CF_POP) != 0);
+    double xp = (fe & (hines::CF_PUSH | hines::CF_MERGE)) ? entry : xc;
+    if (any_lane(fe & hines::CF_MBOUT)) {
+      if (fe & hines::CF_MBOUT) xp = mb[lane].x;  // x of the parent, posted by the receiving lane
+      settle(xp);
     }
     const double xv = __builtin_fma(-pair_at(C.d, e), xp, pair_at(C.b, e));
-    if (fe & hines::CF_POP) {
-      stx[64 * m] = xt;
-      m += 1;
-      xt = xv;
-    }
+    if (fe & hines::CF_POP) *stx.here() = xv;
     if (fe & hines::CF_MBIN) {
       mb[msrc & 63u].x = xv;
       msrc >>= 6;
@@ -2945,7 +2952,7 @@ __device__ __forceinline__ void walk_forward(const WalkChunk& C, const WalkSolve
 
 __global__ __launch_bounds__(64) void k_solve_walk(DevTables tb, WalkSolve L) {
   __shared__ __attribute__((aligned(16))) double2_t wraw[hines::kCellStack * 64 + 64];
-  lds_d2* stk = (lds_d2*)wraw + threadIdx.x;  // slot s at stk[64 s]
+  LaneStack<double2_t> stk{(lds_d2*)wraw + threadIdx.x};
   lds_d2* mb = (lds_d2*)wraw + hines::kCellStack * 64;
   const int lane = threadIdx.x;
   const hines::KCellWave W = tb.cwave[blockIdx.x];
@@ -2954,30 +2961,28 @@ __global__ __launch_bounds__(64) void k_solve_walk(DevTables tb, WalkSolve L) {
   WalkChunk A, B;
   const uint64_t ms = tb.cmsrc[(int64_t)blockIdx.x * 64 + lane];
   unsigned msb = (unsigned)ms, msf = (unsigned)(ms >> 32);
-  double cd = 0.0, cb = 0.0, td = 0.0, tb_ = 0.0;
-  int m = 0;
+  double cd = 0.0, cb = 0.0;
   walk_load_b(A, L, flv, W.chunk_off, 0, lane);
   for (int k = 0;; k += 2) {
     if (k + 1 < nk) walk_load_b(B, L, flv, W.chunk_off + k + 1, k + 1, lane);
-    walk_backward(A, L, W.chunk_off + k, lane, stk, mb, cd, cb, td, tb_, m, msb);
+    walk_backward(A, L, W.chunk_off + k, lane, stk, mb, cd, cb, msb);
     if (k + 1 >= nk) break;
     if (k + 2 < nk) walk_load_b(A, L, flv, W.chunk_off + k + 2, k + 2, lane);
-    walk_backward(B, L, W.chunk_off + k + 1, lane, stk, mb, cd, cb, td, tb_, m, msb);
+    walk_backward(B, L, W.chunk_off + k + 1, lane, stk, mb, cd, cb, msb);
     if (k + 2 >= nk) break;
   }
   // the forward sweep reads back this wave's own stores
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  lds_f64* stx = (lds_f64*)wraw + threadIdx.x;  // slot s at stx[64 s]
-  double xc = 0.0, xt = 0.0;
-  m = 0;
+  LaneStack<double> stx{(lds_f64*)wraw + threadIdx.x};
+  double xc = 0.0;
   walk_load_f(A, L, flv, W.chunk_off + nk - 1, nk - 1, lane);
   for (int k = nk - 1;; k -= 2) {
     if (k >= 1) walk_load_f(B, L, flv, W.chunk_off + k - 1, k - 1, lane);
-    walk_forward(A, L, W.chunk_off + k, lane, stx, mb, xc, xt, m, msf);
+    walk_forward(A, L, W.chunk_off + k, lane, stx, mb, xc, msf);
     if (k < 1) break;
     if (k >= 2) walk_load_f(A, L, flv, W.chunk_off + k - 2, k - 2, lane);
-    walk_forward(B, L, W.chunk_off + k - 1, lane, stx, mb, xc, xt, m, msf);
+    walk_forward(B, L, W.chunk_off + k - 1, lane, stx, mb, xc, msf);
     if (k < 2) break;
   }
 }

@@ -133,7 +133,7 @@ constexpr int64_t cell_pos_index(int64_t chunk, int32_t c, int32_t e) {
 constexpr int64_t cell_flag_index(int64_t chunk, int32_t c, int32_t e) {
   return chunk * kCellChunkElems + (int64_t)c * kCellChunk + e;
 }
-constexpr int32_t kCellStack = 12;           // LDS stack slots per lane; slot 0 is a dummy
+constexpr int32_t kCellStack = 12;           // LDS stack slots (entries) per lane
 constexpr int32_t kCellMaxCuts = 3;          // cut-off subtrees per cell (lanes per cell: up to 4)
 constexpr uint16_t kCellPadPos = 0xFFFF;     // padding element: no user compartment
 constexpr int64_t kCellMaxSize = 65535;      // positions fit 16 bits below kCellPadPos
