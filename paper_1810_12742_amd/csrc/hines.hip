@@ -1417,6 +1417,14 @@ hines_status hines_timestep(const hines_plan* p, const double* diag, const doubl
   return run_solve(p, rs, diag, upper, v_out, stream);
 }
 
+// what is queued on `to` from here on follows what `from` holds
+static hipError_t follow(hipStream_t from, hipEvent_t ev, hipStream_t to) {
+  const hipError_t e = hipEventRecord(ev, from);
+  return e == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e;
+}
+constexpr unsigned kDrawSlabs = 16;       // blocks per wave of k_cells_draw
+constexpr int64_t kDrawMaxWaves = 4 * 256;  // waves of a sweep with a SIMD each
+
 hines_status hines_timeloop_create(const hines_plan* p, const double* diag, const double* upper, const double* c,
                                    double* v, const double* i_inj, double noise_sigma, uint32_t noise_seed,
                                    uint32_t first_step, int32_t nsteps, int32_t ncells, hines_timeloop** out) {
@@ -1442,17 +1450,31 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   // current and V into the walk layout; K steps there; V back at the end
   bool factored = p->host.cl.built && p->host.n > 0;
   hdev::CellLoop L{};
+  // Noise draws: on a second branch of the graph, one step ahead, as a current
+  // that the step adds -- as long as every wave of the sweep has a SIMD to
+  // itself (4 per CU).  Those waves wait most of the time and leave lanes of
+  // the chip idle, and draws inside them lengthen the one chain that is waited
+  // for.  20 steps of C2 cells, in the steps -> beside them: 64 cells (5 waves)
+  // 21.1 -> 9.3 ms, 12,288 (620) 24.5 -> 14.7, 22,528 (1,003) 23.9 -> 19.0; ten
+  // steps of 32,768 cells (1,263 waves), bound by memory, 14.3 -> 15.1 ms.
+  bool drawn = factored && noise && p->host.cl.nwaves <= kDrawMaxWaves;
   if (factored) {
     const int64_t S = p->t.cslots;
-    // f, 1 / d', c, the current, V; positions for the draws
-    const int64_t bytes = 8 * S * (i_inj ? 5 : 4) + (noise ? 2 * S : 0) + 256;
-    if (dev_alloc(&tl->mem, bytes) != hipSuccess) {
-      (void)hipGetLastError();  // no room for the factors: capture the plain steps instead
+    // f, 1 / d', c, V, and the current or two steps' draws; positions for the draws
+    auto room = [&] {
+      tl->bytes = 8 * S * (i_inj ? 5 : drawn ? 6 : 4) + (noise ? 2 * S : 0) + 256;
+      if (dev_alloc(&tl->mem, tl->bytes) == hipSuccess) return true;
+      (void)hipGetLastError();
       tl->mem = nullptr;
-      factored = false;
-    } else {
-      tl->bytes = bytes;
+      tl->bytes = 0;
+      return false;
+    };
+    factored = room();
+    if (!factored && drawn) {  // no room for the draws: they are made in the steps
+      drawn = false;
+      factored = room();
     }
+    // no room for the factors: the plain steps are captured instead
   }
   if (factored) {
     const int64_t S = p->t.cslots;
@@ -1461,8 +1483,8 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     L.r = m + S;
     L.c = m + 2 * S;
     L.v = m + 3 * S;
-    L.ci = i_inj ? m + 4 * S : nullptr;
-    L.lp = noise ? (const uint16_t*)(m + 4 * S) : nullptr;
+    L.ci = i_inj || drawn ? m + 4 * S : nullptr;
+    L.lp = noise ? (const uint16_t*)(m + (drawn ? 6 : 4) * S) : nullptr;
     L.sigma = noise_sigma;
     L.seed = noise_seed;
   }
@@ -1473,11 +1495,12 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   const bool fork = flow && (!p->buckets.empty() || p->stream_count > 0);
   hipStream_t cs = nullptr, fs = nullptr;
   hipEvent_t forked = nullptr, joined = nullptr;
+  hipEvent_t made[2] = {nullptr, nullptr}, used[2] = {nullptr, nullptr};  // a step's draws
   hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-  if (fork && e == hipSuccess) {
+  if ((fork || drawn) && e == hipSuccess) {
     e = hipStreamCreateWithFlags(&fs, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&forked, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&joined, hipEventDisableTiming);
+    for (hipEvent_t* ev : {&forked, &joined, &made[0], &made[1], &used[0], &used[1]})
+      if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
   }
   const hipStream_t ls = fork ? fs : cs;  // the step-by-step branch
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
@@ -1487,28 +1510,35 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     if (noise)
       hipLaunchKernelGGL(hdev::k_cells_lane_pos, grid_for(p->t.cslots, 256), dim3(256), 0, cs, p->t,
                          (uint16_t*)L.lp, p->host.cl.nchunks);
+    if (drawn) e = follow(cs, forked, fs);
     RhsSpec rs0{};
     hipLaunchKernelGGL(hdev::k_solve_cells<hdev::kCellFactor>, grid, dim3(64), 0, cs, p->t, rs0, diag, upper,
                        (double*)L.f);  // f at L.f, 1 / d' at L.f + slots = L.r
     hipLaunchKernelGGL(hdev::k_cells_to_walk, grid, dim3(64), 0, cs, p->t, c, (double*)L.c);
     if (i_inj) hipLaunchKernelGGL(hdev::k_cells_to_walk, grid, dim3(64), 0, cs, p->t, i_inj, (double*)L.ci);
     hipLaunchKernelGGL(hdev::k_cells_to_walk, grid, dim3(64), 0, cs, p->t, (const double*)v, L.v);
-    for (int32_t k = 0; k < nsteps; ++k) {
+    for (int32_t k = 0; k < nsteps && e == hipSuccess; ++k) {
       L.step = first_step + (uint32_t)k;
-      if (noise)
+      if (drawn) {  // on the second branch, beside the step before it
+        L.ci = (double*)tl->mem + (4 + (k & 1)) * p->t.cslots;
+        if (k >= 2) e = hipStreamWaitEvent(fs, used[k & 1], 0);
+        hipLaunchKernelGGL(hdev::k_cells_draw, dim3((unsigned)p->host.cl.nwaves, kDrawSlabs), dim3(256), 0, fs, p->t,
+                           L.lp, noise_sigma, noise_seed, L.step, (double*)L.ci);
+        if (e == hipSuccess) e = follow(fs, made[k & 1], cs);
+      }
+      if (noise && !drawn)
         hipLaunchKernelGGL(hdev::k_cells_step<hdev::kFlowNoise>, grid, dim3(64), 0, cs, p->t, L);
-      else if (i_inj)
+      else if (i_inj || drawn)
         hipLaunchKernelGGL(hdev::k_cells_step<hdev::kFlowCVI>, grid, dim3(64), 0, cs, p->t, L);
       else
         hipLaunchKernelGGL(hdev::k_cells_step<hdev::kFlowCV>, grid, dim3(64), 0, cs, p->t, L);
+      if (drawn && e == hipSuccess) e = hipEventRecord(used[k & 1], cs);
     }
     hipLaunchKernelGGL(hdev::k_cells_from_walk, grid, dim3(64), 0, cs, p->t, (const double*)L.v, v);
-    e = hipGetLastError();
+    const hipError_t e2 = hipGetLastError();
+    if (e == hipSuccess) e = e2;
   }
-  if (fork && e == hipSuccess) {
-    e = hipEventRecord(forked, cs);
-    if (e == hipSuccess) e = hipStreamWaitEvent(ls, forked, 0);
-  }
+  if (fork && e == hipSuccess) e = follow(cs, forked, ls);
   for (int32_t k = 0; k < nsteps && e == hipSuccess && flow; k += kLoopStretch) {
     hdev::FlowRun R{c, v, i_inj, v, noise_sigma, noise_seed, first_step + (uint32_t)k,
                     std::min(kLoopStretch, nsteps - k), 0, nullptr, nullptr, nullptr, 0, 0};
@@ -1528,9 +1558,8 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     const int where = nsteps == 1 ? kAlone : k == 0 ? kFirst : k + 1 < nsteps ? kNext : kLast;
     e = flow ? launch_others(p, rs, diag, upper, v, ls, where) : launch_solve(p, rs, diag, upper, v, cs);
   }
-  if (fork && capturing) {  // also after an error: a capture ends on its first stream with every branch joined
-    hipError_t e2 = hipEventRecord(joined, ls);
-    if (e2 == hipSuccess) e2 = hipStreamWaitEvent(cs, joined, 0);
+  if ((fork || drawn) && capturing) {  // also after an error: a capture ends on its first stream with every branch joined
+    const hipError_t e2 = follow(fs, joined, cs);
     if (e == hipSuccess) e = e2;
   }
   if (capturing) {
@@ -1539,8 +1568,8 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&tl->exec, tl->graph, nullptr, nullptr, 0);
   if (fs) hipStreamDestroy(fs);
-  if (forked) hipEventDestroy(forked);
-  if (joined) hipEventDestroy(joined);
+  for (hipEvent_t ev : {forked, joined, made[0], made[1], used[0], used[1]})
+    if (ev) hipEventDestroy(ev);
   if (cs) hipStreamDestroy(cs);
   if (e != hipSuccess) {
     if (tl->exec) hipGraphExecDestroy(tl->exec);

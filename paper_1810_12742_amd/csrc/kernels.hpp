@@ -2652,6 +2652,54 @@ __global__ void k_cells_lane_pos(DevTables tb, uint16_t* __restrict__ lp, int64_
   lp[t] = tb.cpos[hines::cell_pos_index(g, c, e)];
 }
 
+// Pair q of chunk k (steps k CK + 2q and the next) holds a step of the lane's
+// walk [lo, hi).  A pair of padding steps reads and writes the lane's 16
+// bytes of the zero block instead of its walk slot: its operands are zeros
+// (the carry and the stack skip padding, and products of zeros and finite
+// values are zeros, so only zeros are written back), and a memory line of
+// such pairs is never fetched from HBM.  The choice is an address select,
+// not a branch, so that the loads of the next chunk stay in flight while
+// this one is swept.
+__device__ __forceinline__ bool pair_real(int k, int q, int lo, int hi) {
+  const int t = k * CK + 2 * q;
+  return t + 2 > lo && t < hi;
+}
+__device__ __forceinline__ const double2_t* pair_src(const double* a, int64_t o, bool real, const double2_t* zp) {
+  return real ? (const double2_t*)a + o : zp;
+}
+
+// The noise of one step as a current in the walk layout (0 at padding), for
+// k_cells_step<kFlowCVI>, whose fma(c, V, I) is the noise step's own last
+// operation.  Block (w, y): chunks y, y + gridDim.y, ... of wave w, two pairs
+// of draws per thread.
+// Bound by arithmetic (ten rounds of products, a log, a root and a cospi per
+// draw).  Inside the sweep they were half of a step: 12,288 C2 cells, 1,186 us
+// a step with them and 560 us without; here other waves' draws fill the chip and
+// run beside the step before (20 steps: 24.5 -> 14.7 ms).
+__global__ __launch_bounds__(256) void k_cells_draw(DevTables tb, const uint16_t* __restrict__ lp, double sigma,
+                                                    uint32_t seed, uint32_t step, double* __restrict__ ci) {
+  const hines::KCellWave W = tb.cwave[blockIdx.x];
+  const int lane = threadIdx.x & 63;
+  const int64_t base = tb.cbase[(int64_t)blockIdx.x * 64 + lane];
+  const uint64_t rg = tb.crange[(int64_t)blockIdx.x * 64 + lane];
+  const int lo = (int)(unsigned)rg, hi = (int)(unsigned)(rg >> 32);
+  for (int k = blockIdx.y; k < W.nchunk; k += gridDim.y) {
+    const int64_t g = W.chunk_off + k;
+    for (int q = threadIdx.x >> 6; q < CK / 2; q += 4) {
+      if (!pair_real(k, q, lo, hi)) continue;  // the step reads the zero block for it
+      const uint32_t pp = *(const uint32_t*)(lp + g * hines::kCellChunkElems + lane * CK + 2 * q);
+      double2_t z;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const unsigned p = j ? pp >> 16 : pp & 0xffffu;
+        const double n = noise_draw(seed, step, (uint64_t)(base + (p == hines::kCellPadPos ? 0u : p)), sigma);
+        z[j] = p == hines::kCellPadPos ? 0.0 : n;
+      }
+      *((double2_t*)ci + walk_pair(g, q, lane)) = z;
+    }
+  }
+}
+
 // One implicit-Euler step with the factors kept: V <- A^-1 (c V + I) in the
 // walk layout.  Two register sets: the loads of the next chunk are in flight
 // while this one is swept.
@@ -2671,22 +2719,6 @@ struct StepChunk {
 // load in flight, the next chunk's included, at each mailbox take).
 constexpr int kWaitVm0 = 0x0f70;
 __device__ __forceinline__ void lists_settled() { __builtin_amdgcn_s_waitcnt(kWaitVm0); }
-
-// Pair q of chunk k (steps k CK + 2q and the next) holds a step of the lane's
-// walk [lo, hi).  A pair of padding steps reads and writes the lane's 16
-// bytes of the zero block instead of its walk slot: its operands are zeros
-// (the carry and the stack skip padding, and products of zeros and finite
-// values are zeros, so only zeros are written back), and a memory line of
-// such pairs is never fetched from HBM.  The choice is an address select,
-// not a branch, so that the loads of the next chunk stay in flight while
-// this one is swept.
-__device__ __forceinline__ bool pair_real(int k, int q, int lo, int hi) {
-  const int t = k * CK + 2 * q;
-  return t + 2 > lo && t < hi;
-}
-__device__ __forceinline__ const double2_t* pair_src(const double* a, int64_t o, bool real, const double2_t* zp) {
-  return real ? (const double2_t*)a + o : zp;
-}
 
 template <int RHS>
 __device__ __forceinline__ void step_load_b(StepChunk<RHS>& C, const CellLoop& L, const hines::KCellWave& W,

@@ -308,3 +308,52 @@ def test_layout_resident_solve_through_the_c_abi():
         p.close()
     q = Plan(f.parent, f.cell_offsets, f.branch_offsets)
     assert lib.hines_layout_size(q._h, ctypes.byref(m)) == 12  # not a cell-lane plan
+
+
+@pytest.mark.parametrize("steps,words", [(1, 50), (2, 50), (5, 50), (1, 34), (5, 34)])
+def test_noise_loop_draws_beside_and_inside_the_steps(tmp_path, torch_dev, steps, words):
+    """A noise loop with room for two steps' draws (50 bytes per walk slot) has
+    them made on a second branch of its graph, one with room for the factors
+    only (34) inside the steps.  Both equal the eager steps bit for bit over
+    three launches with other work between them: the same draws, the same
+    fused sum.  Each size of memory runs in a child process, capped to what
+    the plan and the loop take."""
+    import os
+    import subprocess
+    import sys
+    torch, dev = torch_dev
+    from paper_1810_12742_amd import Plan
+    s = configs.c3(300, seed=5)
+    f = s.forest
+    p = Plan(f.parent, f.cell_offsets, f.branch_offsets, cell_lanes=1)
+    cap = p.info["device_table_bytes"] + words * p.layout_size + 256
+    d, u, c = (torch.from_numpy(a).to(dev) for a in (s.diag, s.upper, s.c))
+    V = torch.zeros(f.n, dtype=torch.float64, device=dev)
+    for _ in range(3):
+        for k in range(steps):
+            p.timestep(d, u, c, V, V, noise_sigma=0.1, noise_seed=3, step=7 + k)
+    torch.cuda.synchronize()
+    want = V.cpu().numpy()
+    p.close()
+    code = (
+        "import sys, numpy as np, torch\n"
+        "from workloads import configs\n"
+        "from paper_1810_12742_amd import Plan\n"
+        "s = configs.c3(300, seed=5)\n"
+        "f = s.forest\n"
+        "dev = torch.device('cuda')\n"
+        "p = Plan(f.parent, f.cell_offsets, f.branch_offsets, cell_lanes=1)\n"
+        "d, u, c = (torch.from_numpy(a).to(dev) for a in (s.diag, s.upper, s.c))\n"
+        "V = torch.zeros(f.n, dtype=torch.float64, device=dev)\n"
+        f"loop = p.timeloop(d, u, c, V, {steps}, first_step=7, noise_sigma=0.1, noise_seed=3)\n"
+        "for _ in range(3):\n"
+        "    loop.launch()\n"
+        "    torch.ones(1000, device=dev).sum().item()\n"
+        "np.save(sys.argv[1], V.cpu().numpy())\n")
+    out = str(tmp_path / "v.npy")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, HINES_DEVICE_BYTE_CAP=str(cap), PYTHONPATH=root)
+    print(f"cells: noise loop, {steps} steps, {words} bytes per slot", flush=True)
+    r = subprocess.run([sys.executable, "-c", code, out], capture_output=True, text=True, env=env, cwd=root, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert np.array_equal(np.load(out), want)
