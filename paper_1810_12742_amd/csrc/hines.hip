@@ -2,12 +2,15 @@
 // in include/hines.h.  Device code: kernels.hpp.
 //
 // Design (paper §3-§5 re-thought for CDNA4):
-//  * one workgroup solves one packed group of cells (§3: all work of a matrix
-//    stays inside one block, so only block-level synchronisation is needed);
+//  * one workgroup solves one packed group of cells, or a bin of groups with a
+//    wave each (§3: all work of a matrix stays inside one block, so only
+//    block-level synchronisation is needed);
 //  * every matrix entry crosses HBM once: a group is staged into LDS,
 //    eliminated there and its solution written back (the role of the paper's
-//    interleaved layout, §5, is played by the LDS image); groups too large
-//    for LDS run the level-synchronous sweeps on a global workspace image;
+//    interleaved layout, §5, is played by the LDS image); cells too large
+//    for LDS are laid out in a device scratch in the order of their steps and
+//    swept from there (or, on plans of the level kernel, run the
+//    level-synchronous sweeps on a global workspace image);
 //  * fast path (flow kernel): one wave per group runs a static step schedule
 //    built by the setup: in each step every busy lane eliminates one
 //    compartment, heavy children hand their contribution to the parent in
@@ -17,8 +20,8 @@
 //  * level-synchronous path (§3, §4 Fig 4.1): one lane per branch, lanes of
 //    a level sorted by branch length, a barrier between levels; children
 //    store their contribution in their own slot and the parent pulls them in
-//    a fixed order (used for re-rooted plans, bitwise mode and workspace
-//    groups);
+//    a fixed order (used for re-rooted plans and bitwise mode, and for forests
+//    that the step schedule does not take);
 //  * flow groups of different LDS footprints share one workgroup, one wave
 //    each (bins, packed by the setup), so that a solve is one or two launches;
 //    the other groups are bucketed by LDS footprint, one launch per bucket.
