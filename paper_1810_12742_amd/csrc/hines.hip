@@ -1025,29 +1025,10 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
   }
   // resident groups by LDS class, longest schedules first within a class
   if (P.res.built) {
-    std::vector<std::vector<int32_t>> rm(hines::kResClasses);
-    for (int64_t g = 0; g < (int64_t)P.res.groups.size(); ++g) rm[P.res.groups[g].cls].push_back((int32_t)g);
-    // A launch lasts at least one group, so a class with few groups goes into
-    // the next larger one (an image runs in any class that holds it) when both
-    // together take no longer than one after the other: steps of the longest
-    // group times rounds of the device.  Ten launches, seven of them with 1 to
-    // 89 groups, took 189 us on 2,048 C2 cells; merged they take 116.
-    auto cost = [&](const std::vector<int32_t>& m, int k) {
-      int32_t steps = 0;
-      for (int32_t g : m) steps = std::max(steps, P.res.groups[g].nchunk);
-      const double held = 256.0 * (double)(hines::kLdsLimitBytes / hines::kResClassBytes[k]);
-      return m.empty() ? 0.0 : steps * std::max(1.0, (double)m.size() / held);
-    };
-    for (int k = hines::kResClasses - 1; k > 0; --k) {  // smallest images first
-      int j = k - 1;  // the next larger class with groups
-      while (j >= 0 && rm[j].empty()) --j;
-      if (j < 0 || rm[k].empty()) continue;
-      std::vector<int32_t> both(rm[j]);
-      both.insert(both.end(), rm[k].begin(), rm[k].end());
-      if (cost(both, j) <= cost(rm[k], k) + cost(rm[j], j)) {
-        rm[j] = std::move(both);
-        rm[k].clear();
-      }
+    std::vector<std::vector<int32_t>> rm = hines::res_launches(P.res);
+    if (!hines::check_res_launches(P.res, rm, why)) {
+      delete p;
+      return set_err(HINES_ERR_STATE, "resident launches: %s", why.c_str());
     }
     for (int k = 0; k < hines::kResClasses; ++k) {
       auto& m = rm[k];

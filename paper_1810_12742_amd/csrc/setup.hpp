@@ -327,6 +327,11 @@ Status build_resident(const int32_t* parent, int64_t n, const int64_t* cell_offs
 // group image, every compartment eliminated once, after all its children, and
 // every light path's contribution added two chunks before its parent's chunk.
 bool check_resident(const ResPlan& R, const int32_t* parent, int64_t n, std::string& why);
+// The groups of each launch, by the LDS class it is launched with; classes with
+// few groups share a launch.
+std::vector<std::vector<int32_t>> res_launches(const ResPlan& R);
+// Every group is in one launch, and its image inside that launch's LDS.
+bool check_res_launches(const ResPlan& R, const std::vector<std::vector<int32_t>>& launches, std::string& why);
 
 // Per-branch record of the LDS-staged solve kernel, in (group, level, lane)
 // order; 16 bytes so that one DMA lane moves one record.  All indices are
