@@ -251,6 +251,8 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
  *   diag, upper, rhs, x: device arrays of n doubles in the user numbering.
  *   x may alias rhs; it must not alias diag or upper.
  *   ncells must equal the plan's cell count.
+ * Infinite and NaN values of a cell reach no other cell on plans with a step
+ * schedule (hines_plan_info.kernel == 1), in this and in every other call.
  * Inputs are not modified.  Asynchronous on stream. */
 hines_status hines_solve(const hines_plan* plan, const double* diag, const double* upper,
                          const double* rhs, double* x, int32_t ncells, void* stream);

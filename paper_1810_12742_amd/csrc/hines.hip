@@ -630,7 +630,7 @@ bool check_kernel_tables(const hines::HostPlan& P, std::string& why, bool& capac
         seen[q] = 1;
       }
       for (int32_t k = 0; k < W.naux; ++k) {
-        if (!valid(P.faux[W.aux_off + k])) {
+        if (P.faux[W.aux_off + k] != hines::kFlowRootPush && !valid(P.faux[W.aux_off + k])) {
           why = "flow push target";
           return false;
         }

@@ -613,7 +613,7 @@ __device__ __forceinline__ int rank_in(uint64_t m, int base) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
 }
 typedef __attribute__((address_space(3))) double lds_f64;
-typedef __attribute__((address_space(3))) int16_t lds_i16;
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4 lds_u4;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
@@ -740,13 +740,18 @@ __device__ __forceinline__ uint64_t first_u64(uint32_t lo, uint32_t hi) {
 // immediate offset.  An idle lane reads the identity block (d = 1, u = 0,
 // b = 0 per entry, which eliminates to zeros) and writes into the sink, which
 // is never read.  Only the pushes are masked.
+// A lane takes paths of several cells in turn, and nothing of one may reach the
+// next, were it infinite or NaN (a product with 0 would let it through): the mask
+// of a step's path ends holds the roots too, a path that begins takes no
+// carry, and a root's push target (0xffff) stands for the sink in the backward
+// and for a zero of the identity block in the forward sweep.
 constexpr int KC = hines::kFlowChunk;
 constexpr int KB8 = hines::kFlowBlock8;
 
 // LDS image of one group, the wave's own region of the workgroup's LDS.
 struct FlowImage {
   lds_f64* img;
-  lds_i16* aux;  // push targets
+  lds_u16* aux;  // push targets; kFlowRootPush at a cell's root
   lds_u4* msk;   // masks of steps 0 .. F - 1, a zero record on each side (steps -1 and F)
   int F, nblk, naux;
   int idle, sink;  // units of the identity block and of this lane's sink
@@ -766,11 +771,19 @@ __device__ __forceinline__ FlowImage flow_image(const hines::KFlowJob& J, char* 
   I.naux = J.naux;
   I.idle = I.nblk * KB8;
   I.sink = I.idle + KB8 + lane;
-  I.aux = (lds_i16*)(I.img + flow_image8(J.nent));
+  I.aux = (lds_u16*)(I.img + flow_image8(J.nent));
   I.msk = (lds_u4*)((lds_u8*)I.img + flow_mask_offset(J.nent, J.naux)) + 1;
   I.last_aux = J.naux > 0 ? J.naux - 1 : 0;
   return I;
 }
+
+// Push target of a lane whose path ends (e: the lanes that do, the first of them
+// entry a), and as a unit of the image, `none` at a cell's root.  Apart, so that no
+// step waits for the target that it reads.
+__device__ __forceinline__ int flow_target(const FlowImage& I, uint64_t e, int a) {
+  return I.aux[min(rank_in(e, a), I.last_aux)];
+}
+__device__ __forceinline__ int flow_target_unit(int q, int none) { return min(q, none); }
 
 // Masks and push targets by global->LDS DMA (16- and 4-byte units; the push
 // targets of a group start 4-byte aligned and the table is padded); the caller
@@ -819,6 +832,7 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
   u32x4 mv = I.msk[1];
   int R = 0, A = 0;
   double fin = 0.0, uin = 0.0, bin = 0.0;
+  uint64_t on = 0;  // the lanes whose path goes on from the step before
   auto load = [&](FlowBwd& S, uint64_t m, uint64_t e, int r, int a) {
     S.rb = flow_block(I, m, r);
 #pragma unroll
@@ -827,7 +841,7 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
       S.u[j] = img[S.rb + 3 * j + 1];
       S.b[j] = img[S.rb + 3 * j + 2];
     }
-    S.q = I.aux[min(rank_in(e, a), I.last_aux)];
+    S.q = flow_target(I, e, a);
   };
   auto step = [&](int t, FlowBwd& C, FlowBwd& N) {
     const uint64_t M1 = first_u64(mv.x, mv.y), E1 = first_u64(mv.z, mv.w);
@@ -838,8 +852,11 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
     const int wb = lane_in(M) ? C.rb : I.sink;
 #pragma unroll
     for (int j = 0; j < KC; ++j) {
-      const double dl = __builtin_fma(-fin, uin, C.d[j]);
-      const double bl = __builtin_fma(-fin, bin, C.b[j]);
+      double dl = C.d[j], bl = C.b[j];
+      if (j > 0 || lane_in(on)) {
+        dl = __builtin_fma(-fin, uin, dl);
+        bl = __builtin_fma(-fin, bin, bl);
+      }
       const double r = rcp_nr(dl);
       const double f = C.u[j] * r;
       img[wb + 3 * j] = f;
@@ -850,10 +867,11 @@ __device__ __forceinline__ void flow_backward(const FlowImage& I) {
       bin = bl;
     }
     if (lane_in(E)) {
-      lds_add(img + C.q, -(fin * uin));
-      lds_add(img + C.q + 2, -(fin * bin));
+      const int q = flow_target_unit(C.q, I.sink);
+      lds_add(img + q, -(fin * uin));
+      lds_add(img + q + 2, -(fin * bin));
     }
-    fin = lane_in(M & ~E) ? fin : 0.0;
+    on = M & ~E;
     M = M1;
     E = E1;
   };
@@ -877,6 +895,7 @@ __device__ __forceinline__ void flow_backward_kept(const FlowImage& I) {
   u32x4 mv = I.msk[1];
   int R = 0, A = 0;
   double fin = 0.0, bin = 0.0;
+  uint64_t on = 0;
   auto load = [&](FlowBwd& S, uint64_t m, uint64_t e, int r, int a) {
     S.rb = flow_block(I, m, r);
 #pragma unroll
@@ -885,7 +904,7 @@ __device__ __forceinline__ void flow_backward_kept(const FlowImage& I) {
       S.u[j] = img[S.rb + 3 * j + 1];  // 1 / d'
       S.b[j] = img[S.rb + 3 * j + 2];
     }
-    S.q = I.aux[min(rank_in(e, a), I.last_aux)];
+    S.q = flow_target(I, e, a);
   };
   auto step = [&](int t, FlowBwd& C, FlowBwd& N) {
     const uint64_t M1 = first_u64(mv.x, mv.y), E1 = first_u64(mv.z, mv.w);
@@ -896,13 +915,14 @@ __device__ __forceinline__ void flow_backward_kept(const FlowImage& I) {
     const int wb = lane_in(M) ? C.rb : I.sink;
 #pragma unroll
     for (int j = 0; j < KC; ++j) {
-      const double bl = __builtin_fma(-fin, bin, C.b[j]);
+      double bl = C.b[j];
+      if (j > 0 || lane_in(on)) bl = __builtin_fma(-fin, bin, bl);
       img[wb + 3 * j + 2] = bl * C.u[j];
       fin = C.d[j];
       bin = bl;
     }
-    if (lane_in(E)) lds_add(img + C.q + 2, -(fin * bin));
-    fin = lane_in(M & ~E) ? fin : 0.0;
+    if (lane_in(E)) lds_add(img + flow_target_unit(C.q, I.sink) + 2, -(fin * bin));
+    on = M & ~E;
     M = M1;
     E = E1;
   };
@@ -940,13 +960,13 @@ __device__ __forceinline__ void flow_forward(const FlowImage& I) {
       S.f[j] = img[S.rb + 3 * j];
       S.y[j] = img[S.rb + 3 * j + 2];
     }
-    S.xq = img[q + 2];
+    S.xq = img[flow_target_unit(q, I.idle) + 2];
   };
   FlowFwd S0, S1;
-  load(S0, M, R1, I.aux[min(rank_in(E, A1), I.last_aux)]);
+  load(S0, M, R1, flow_target(I, E, A1));
   R1 -= __builtin_popcountll(M1);
   A1 -= __builtin_popcountll(E1);
-  int q1 = I.aux[min(rank_in(E1, A1), I.last_aux)];
+  int q1 = flow_target(I, E1, A1);
   double xp = 0.0;
   auto step = [&](int t, FlowFwd& C, FlowFwd& N) {
     const uint64_t M2 = first_u64(mv.x, mv.y), E2 = first_u64(mv.z, mv.w);
@@ -954,7 +974,7 @@ __device__ __forceinline__ void flow_forward(const FlowImage& I) {
     load(N, M1, R1, q1);
     R1 -= __builtin_popcountll(M2);
     A1 -= __builtin_popcountll(E2);
-    q1 = I.aux[min(rank_in(E2, A1), I.last_aux)];
+    q1 = flow_target(I, E2, A1);
     const int wb = lane_in(M) ? C.rb : I.sink;
     double xv = lane_in(E) ? C.xq : xp;
 #pragma unroll
@@ -1972,7 +1992,6 @@ __global__ __launch_bounds__(64) void k_solve_seq(DevTables tb, RhsSpec rs, cons
 // down to its bottom: x_j = y_j - f_j x_parent, written over y.  Lanes with no
 // path in a chunk are masked off for the whole chunk.
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) u32x2 lds_u2;
 
@@ -2355,7 +2374,7 @@ __global__ __launch_bounds__(256) void k_stream_store(DevTables tb, double* x) {
 
 // A step as a lane sees it.
 struct StreamStep {
-  uint64_t active, push;
+  uint64_t active, push, root;
   int unit, stride;  // its first unit, and from one unit of its chunk to the next
   int push_slot;     // where its contribution goes (its dummy slot: nowhere)
   u32x4 slot;        // the slots of its compartments
@@ -2407,6 +2426,7 @@ __global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
   auto decode = [&](StreamStep& s, int& e, int& A) {
     s.active = first_u64(rawa.x, rawa.y);
     s.push = first_u64(rawa.z, rawa.w);
+    s.root = first_u64(rawb.z, rawb.w);
     const int R = __builtin_amdgcn_readfirstlane((int)rawb.x), na = __builtin_amdgcn_readfirstlane((int)rawb.y);
     const bool on = lane_in(s.active);
     const int rank = on ? rank_in(s.active, 0) : 0;
@@ -2440,19 +2460,24 @@ __global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
       for (int j = 0; j < KC; ++j) acc[j] = *slot_of(s.slot, j);
     };
     double fin = 0.0, uin = 0.0, bin = 0.0;
+    uint64_t on = 0;  // the lanes whose path goes on from the step before
     auto eliminate = [&](const StreamOps& S, const double2_t (&acc)[KC]) {
       const StreamStep& s = S.s;
       double2_t f2[KC / 2], r2[KC / 2], y2[KC / 2];
 #pragma unroll
       for (int j = 0; j < KC; ++j) {
         const double uu = S.u[j / 2][j % 2];
-        const double bl = __builtin_fma(-fin, bin, S.b[j / 2][j % 2] + acc[j].y);
+        double dl = S.d[j / 2][j % 2], bl = S.b[j / 2][j % 2] + acc[j].y;
+        if constexpr (MODE != kStreamKept) dl = dl + acc[j].x;
+        if (j > 0 || lane_in(on)) {
+          bl = __builtin_fma(-fin, bin, bl);
+          if constexpr (MODE != kStreamKept) dl = __builtin_fma(-fin, uin, dl);
+        }
         double f, r;
         if constexpr (MODE == kStreamKept) {
           f = uu;
-          r = S.d[j / 2][j % 2];
+          r = dl;
         } else {
-          const double dl = __builtin_fma(-fin, uin, S.d[j / 2][j % 2] + acc[j].x);
           r = rcp_nr(dl);
           f = uu * r;
         }
@@ -2475,7 +2500,7 @@ __global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
         if constexpr (MODE != kStreamKept) lds_add(q, -(fin * uin));
         lds_add(q + 1, -(fin * bin));
       }
-      fin = lane_in(s.active & ~s.push) ? fin : 0.0;
+      on = s.active & ~(s.push | s.root);
     };
     StreamOps S0, S1, S2;
     double2_t a0[KC], a1[KC];
@@ -2521,11 +2546,12 @@ __global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
         S.y[p] = B[e + p * A];
       }
     };
-    double xp = 0.0, xq = 0.0;  // x of the lane's last step; x of a pushed path's parent, for the next
+    // x of the lane's last step; x of a pushed path's parent (0 for a root), for the next
+    double xp = 0.0, xq = 0.0;
     auto substitute = [&](const StreamBack& S, double xqn) {
       const StreamStep& s = S.s;
       const bool on = lane_in(s.active);
-      double xv = lane_in(s.push) ? xq : xp;
+      double xv = lane_in(s.push | s.root) ? xq : xp;
       double2_t x2[KC / 2];
 #pragma unroll
       for (int j = KC - 1; j >= 0; --j) {
@@ -2547,7 +2573,8 @@ __global__ __launch_bounds__(64) void k_stream_sweep(DevTables tb) {
     // t - 1 (the last step is entered by roots alone)
     auto step = [&](int t, StreamBack& now, StreamBack& next, StreamBack& ahead) {
       load(ahead, t - 2);
-      substitute(now, slots[next.s.push_slot].x);
+      const double xn = slots[next.s.push_slot].x;
+      substitute(now, lane_in(next.s.root) ? 0.0 : xn);
     };
     for (int t = F - 1;; t -= 3) {
       step(t, S0, S1, S2);

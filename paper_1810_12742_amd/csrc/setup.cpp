@@ -379,7 +379,7 @@ struct Builder {
         tops.push_back(b);
         const int32_t s0 = pp.start[b], nc = nchunks(pp.plen[b]);
         for (int32_t i = 0; i < nc; ++i) st[s0 + i].active |= 1ull << pp.lane[b];
-        if (sin[b].parent >= 0) st[s0 + nc - 1].push |= 1ull << pp.lane[b];
+        (sin[b].parent >= 0 ? st[s0 + nc - 1].push : st[s0 + nc - 1].root) |= 1ull << pp.lane[b];
       }
     for (int32_t t = 0; t < F; ++t) {
       st[t].block = W.nblk;
@@ -1076,7 +1076,7 @@ struct Builder {
             tops.push_back(b);
             const int32_t s = pp.start[b], n = nchunks(pp.plen[b]);
             for (int32_t i = 0; i < n; ++i) M[s + i] |= 1ull << pp.lane[b];
-            if (sin[b].parent >= 0) E[s + n - 1] |= 1ull << pp.lane[b];
+            E[s + n - 1] |= 1ull << pp.lane[b];
           }
         R.assign(F + 1, 0);  // lane-chunks (blocks) before chunk step t
         for (int32_t t = 0; t < F; ++t) R[t + 1] = R[t] + popc64(M[t]);
@@ -1104,6 +1104,7 @@ struct Builder {
         W.nstep = F;
         W.nelem = cum;
         W.nent = nent;
+        W.naux = (int32_t)tops.size();
         W.makespan = F;
         if (flow_lds_bytes(W) > kLdsLimitBytes) {  // e.g. very long single branches: level kernel
           W = KFlow{};
@@ -1126,15 +1127,21 @@ struct Builder {
             }
           }
         }
-        // push targets in (chunk step, lane) order: the far end of the parent branch
+        // push targets in (chunk step, lane) order: the far end of the parent branch,
+        // none for the path of a root
         std::vector<int32_t> end_top((int64_t)F * kSchedLanes, -1);
         for (int32_t q : tops)
-          if (sin[q].parent >= 0) end_top[(int64_t)(pp.start[q] + nchunks(pp.plen[q]) - 1) * kSchedLanes + pp.lane[q]] = q;
+          end_top[(int64_t)(pp.start[q] + nchunks(pp.plen[q]) - 1) * kSchedLanes + pp.lane[q]] = q;
         for (int32_t t = 0; t < F; ++t)
           for (int32_t l = 0; l < kSchedLanes; ++l) {
             const int32_t q = end_top[(int64_t)t * kSchedLanes + l];
             if (q < 0) continue;
-            const int32_t pb = sin[q].parent, pq = pp.top_of[pb];
+            const int32_t pb = sin[q].parent;
+            if (pb < 0) {
+              P.faux.push_back(kFlowRootPush);
+              continue;
+            }
+            const int32_t pq = pp.top_of[pb];
             const int32_t npad = nchunks(pp.plen[pq]) * K - pp.plen[pq];
             P.faux.push_back((int16_t)entry_of(pq, npad + pp.below[pb]));
           }
@@ -1142,7 +1149,6 @@ struct Builder {
           P.fmask.push_back(M[t]);
           P.fmask.push_back(E[t]);
         }
-        W.naux = (int32_t)((int64_t)P.faux.size() - W.aux_off);
         P.kgroup[g].makespan = F;
         steps += F;
         elems += cum;
@@ -1425,7 +1431,8 @@ bool check_stream(const HostPlan& P, const int32_t* parent, std::string& why) {
     target.assign(W.nslot + 1, -1);
     int32_t blk = 0, na = 0;
     for (int32_t t = 0; t < W.nstep; ++t) {
-      if (st[t].block != blk || st[t].aux != na || (st[t].push & ~st[t].active) ||
+      if (st[t].block != blk || st[t].aux != na || ((st[t].push | st[t].root) & ~st[t].active) ||
+          (st[t].push & st[t].root) ||
           blk >= W.nblk) {  // a step may have no busy lane, but its (unused) reads stay inside
         return "stream step record";
       }
@@ -1472,6 +1479,7 @@ bool check_stream(const HostPlan& P, const int32_t* parent, std::string& why) {
           }
         }
         if (carry[l] < 0) return "stream step without a compartment";
+        if (((st[t].root >> l) & 1) != (parent[carry[l]] < 0)) return "stream root mask";
         if ((st[t].push >> l) & 1) {
           const uint16_t q = P.saux[W.aux_off + last_push++];
           if (q < 1 || q > W.nslot || pushed[q] == INT64_MAX ||
@@ -1508,6 +1516,34 @@ bool check_stream(const HostPlan& P, const int32_t* parent, std::string& why) {
     }
   return true;
 }
+
+namespace {
+// The step masks and push targets as they are exported: the paths that end at a
+// root push nothing and are left out.
+struct FlowPushes {
+  std::vector<uint64_t> mask;
+  std::vector<int16_t> aux;
+};
+FlowPushes flow_pushes(const HostPlan& p) {
+  FlowPushes out{p.fmask, {}};
+  for (const KFlow& W : p.kflow) {
+    if (out.aux.size() & 1) out.aux.push_back(0);  // 4-byte aligned start of the group's push targets
+    int64_t k = W.aux_off;
+    for (int64_t t = W.step_off; t < W.step_off + W.nstep; ++t) {
+      uint64_t& ends = out.mask[2 * t + 1];
+      for (int l = 0; l < 64; ++l) {
+        if (!((ends >> l) & 1)) continue;
+        const int16_t target = p.faux[k++];
+        if (target == kFlowRootPush)
+          ends &= ~(1ull << l);
+        else
+          out.aux.push_back(target);
+      }
+    }
+  }
+  return out;
+}
+}  // namespace
 
 int64_t export_table(const HostPlan& p, int32_t id, int64_t* out, int64_t capacity) {
   auto put = [&](const auto& v) -> int64_t {
@@ -1551,24 +1587,27 @@ int64_t export_table(const HostPlan& p, int32_t id, int64_t* out, int64_t capaci
       const int64_t cnt = p.flow ? 8 * (int64_t)p.kflow.size() : 0;
       if (out) {
         if (capacity < cnt) return -1;
+        int64_t aux = 0;
         for (int64_t g = 0; g < cnt / 8; ++g) {
           const KFlow& w = p.kflow[g];
           int64_t* r = out + 8 * g;
           r[0] = w.step_off;
           r[1] = w.pos_off;
-          r[2] = w.aux_off;
+          if (aux & 1) ++aux;  // 4-byte aligned start of the group's push targets
+          r[2] = aux;
           r[3] = w.nstep;
           r[4] = w.nelem;
-          r[5] = w.naux;
+          r[5] = w.nstep > 0 ? w.naux - p.kgroup[g].ncell : 0;
+          aux += r[5];
           r[6] = w.nent;
           r[7] = kFlowChunk;
         }
       }
       return cnt;
     }
-    case T_FLOW_MASKS: return put(p.fmask);
+    case T_FLOW_MASKS: return put(flow_pushes(p).mask);
     case T_FLOW_POS: return put(p.fpos);
-    case T_FLOW_AUX: return put(p.faux);
+    case T_FLOW_AUX: return put(flow_pushes(p).aux);
     case T_CELL_WAVES: {
       const int64_t cnt = 3 * (int64_t)p.cl.waves.size();
       if (out) {

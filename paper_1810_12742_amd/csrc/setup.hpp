@@ -388,17 +388,18 @@ struct KCell {
 // R[t] + (active lanes below l at t), R[t] the active lane-chunks before t,
 // and sub-step j is entry j of that block.  Entries are named by their LDS
 // offset in 8-byte units (block * kFlowBlock8 + 3 j).  Per chunk step the
-// table holds two 64-bit lane masks (active; push: the lane ends a path whose
-// contribution goes to LDS); per element of the group's staging order its
-// entry (bit 15: the cell root, whose coupling is ignored); per push, in
-// (step, lane) order, the entry of the parent compartment.
+// table holds two 64-bit lane masks (active; the lane ends a path); per element
+// of the group's staging order its entry (bit 15: the cell root, whose coupling
+// is ignored); per path end, in (step, lane) order, the entry of the parent
+// compartment, which takes its contribution through LDS (kFlowRootPush: the path
+// ends at a root).
 struct KFlow {
   int64_t step_off;  // first step record (two uint64 masks) of the group
   int64_t pos_off;   // first element entry
   int64_t aux_off;   // first push target
   int32_t nstep;     // chunk steps per sweep (0: not a flow group)
   int32_t nelem;     // compartments
-  int32_t naux;      // pushes
+  int32_t naux;      // path ends
   int32_t makespan;  // chunk steps
   int32_t nent;      // entries: compartments and pads (kFlowChunk per block)
   int32_t pad1;
@@ -418,6 +419,8 @@ constexpr int64_t flow_mask_offset(int32_t nent, int32_t naux) {
 constexpr int64_t flow_lds_bytes(const KFlow& w) {
   return flow_mask_offset(w.nent, w.naux) + 16 * ((int64_t)w.nstep + 2);
 }
+
+constexpr int16_t kFlowRootPush = -1;  // no push: the path ends at its cell's root
 
 // What one wave of the flow kernel does: the group's tables, its range of the
 // user arrays, and where its image stands in the workgroup's LDS.  One record
@@ -453,7 +456,7 @@ constexpr int32_t kStreamPad = INT32_MIN;  // index of a padding entry; ~i for a
 struct KStreamStep {  // per chunk step; 32 bytes
   uint64_t active, push;  // lane masks
   int32_t block, aux;     // blocks and pushes before the step
-  int32_t pad[2];
+  uint64_t root;          // the lanes whose path ends at its cell's root
 };
 static_assert(sizeof(KStreamStep) == 32, "layout");
 struct KStream {      // per group
@@ -503,9 +506,9 @@ struct HostPlan {
   bool all_ascending = true;      // every branch runs toward higher user indices
   bool flow = false;              // every LDS group has a step schedule (flow kernel)
   std::vector<KFlow> kflow;       // [ngroups]
-  std::vector<uint64_t> fmask;    // [2 * total steps]: active and push masks per step
+  std::vector<uint64_t> fmask;    // [2 * total steps]: active lanes and lanes whose path ends, per step
   std::vector<uint16_t> fpos;     // [elements of LDS groups]: position, bit 15 = cell root
-  std::vector<int16_t> faux;      // [pushes]: parent position
+  std::vector<int16_t> faux;      // [path ends]: parent position, kFlowRootPush at a cell's root
   // streamed groups (every group that exceeds LDS, or none)
   std::vector<KStream> stream;
   std::vector<int32_t> sidx;           // per block and sub-step: user index, kStreamPad, or ~index of a root
