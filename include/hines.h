@@ -384,12 +384,15 @@ hines_status hines_adjoint_accumulate(hines_plan* plan, const double* lam, const
  * single-step calls in turn.  All arrays are device arrays, async on stream.
  *   hines_run_steps: nsteps steps with the constant current i_inj (NULL: none)
  *     from v_in; the state after step k goes to states + k n (NULL: not kept),
- *     the last one to v_out (may be v_in, may be NULL if states is given), the
- *     cells' roots after step k to traces + k ncells (NULL: not kept).
+ *     the last one to v_out (may be NULL if states is given), the cells' roots
+ *     after step k to traces + k ncells (NULL: not kept).  v_out may be v_in, and
+ *     either may be a whole row of states after the first; no other array may
+ *     overlap an output (HINES_ERR_STATE).
  *   hines_adjoint_steps: for k = nsteps - 1 down to 0,
  *       A lams[k] = c lams[k + 1] + g_roots[k] at the cells' roots,
  *     lams[nsteps] = lam_in (NULL: zero); lams has nsteps rows of n, g_roots
- *     nsteps rows of ncells.
+ *     nsteps rows of ncells.  lam_in may be a whole row of lams after the first;
+ *     no other input may overlap lams (HINES_ERR_STATE).
  *   hines_adjoint_accumulate_steps: hines_adjoint_accumulate of step k on
  *     (lams[k], states[k], states[k - 1]) for k = nsteps - 1 down to 0, with v0
  *     before states[0]. */

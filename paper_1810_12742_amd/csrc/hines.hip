@@ -1655,6 +1655,18 @@ hines_status hines_adjoint_accumulate_steps(hines_plan* p, const double* lams, c
   return launched();
 }
 
+// two device arrays of na and nb doubles share memory
+static bool overlap(const double* a, int64_t na, const double* b, int64_t nb) {
+  const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+  return a && b && pa < pb + 8 * (uintptr_t)nb && pb < pa + 8 * (uintptr_t)na;
+}
+// v is row 1, 2, ... of an array of rows of n that it overlaps: an element of it is
+// read by the group that writes the same element later
+static bool later_row(const double* v, int64_t n, const double* rows) {
+  const uintptr_t pv = (uintptr_t)v, pr = (uintptr_t)rows;
+  return pv > pr && (pv - pr) % (8 * (uintptr_t)n) == 0;
+}
+
 hines_status hines_run_steps(hines_plan* p, const double* diag, const double* upper, const double* c,
                              const double* v_in, const double* i_inj, int32_t nsteps, double* states, double* v_out,
                              double* traces, int32_t ncells, void* stream) {
@@ -1663,13 +1675,17 @@ hines_status hines_run_steps(hines_plan* p, const double* diag, const double* up
   if (nsteps < 1) return set_err(HINES_ERR_OPTION, "nsteps must be >= 1");
   if (p->host.n == 0) return ok();
   if (!diag || !upper || !c || !v_in || (!states && !v_out)) return set_err(HINES_ERR_NULL, "a device array is NULL");
-  for (const void* o : {(const void*)states, (const void*)v_out})
-    if (o && (o == diag || o == upper || o == c || o == i_inj))
-      return set_err(HINES_ERR_STATE, "an output must not alias the matrix, c or the current");
-  if (states && (states == v_in || states == v_out))
-    return set_err(HINES_ERR_STATE, "states must not alias v_in or v_out");
   const hipStream_t s = (hipStream_t)stream;
-  const int64_t n = p->host.n;
+  const int64_t n = p->host.n, nr = nsteps * n, nt = (int64_t)nsteps * ncells;
+  for (const double* in : {diag, upper, c, i_inj})
+    if (overlap(in, n, states, nr) || overlap(in, n, v_out, n) || overlap(in, n, traces, nt))
+      return set_err(HINES_ERR_STATE, "an output must not alias the matrix, c or the current");
+  for (const double* v : {v_in, (const double*)v_out})
+    if (overlap(v, n, states, nr) && !later_row(v, n, states))
+      return set_err(HINES_ERR_STATE, "v_in and v_out must be whole rows of states after the first, or apart from it");
+  if (v_out != v_in && overlap(v_in, n, v_out, n)) return set_err(HINES_ERR_STATE, "v_out overlaps v_in");
+  if (overlap(traces, nt, v_in, n) || overlap(traces, nt, v_out, n) || overlap(traces, nt, states, nr))
+    return set_err(HINES_ERR_STATE, "traces must not alias another array");
   if (flow_only(p)) {
     for (int32_t k = 0; k < nsteps; k += kLoopStretch) {
       const int32_t m = std::min(kLoopStretch, nsteps - k);
@@ -1692,7 +1708,7 @@ hines_status hines_run_steps(hines_plan* p, const double* diag, const double* up
     if (st != HINES_OK) return st;
     from = to;
   }
-  if (states && v_out) {
+  if (states && v_out && v_out != from) {
     const hipError_t e = hipMemcpyAsync(v_out, from, 8 * (size_t)n, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return set_err(HINES_ERR_HIP, "copy: %s", hipGetErrorString(e));
   }
@@ -1707,9 +1723,11 @@ hines_status hines_adjoint_steps(hines_plan* p, const double* diag, const double
   if (nsteps < 1) return set_err(HINES_ERR_OPTION, "nsteps must be >= 1");
   if (p->host.n == 0) return ok();
   if (!diag || !upper || !c || !g_roots || !lams) return set_err(HINES_ERR_NULL, "a device array is NULL");
-  for (const void* o : {(const void*)diag, (const void*)upper, (const void*)c, (const void*)lam_in})
-    if (o == lams) return set_err(HINES_ERR_STATE, "lams must not alias an input");
-  const int64_t n = p->host.n;
+  const int64_t n = p->host.n, nr = nsteps * n;
+  for (const double* in : {diag, upper, c})
+    if (overlap(in, n, lams, nr)) return set_err(HINES_ERR_STATE, "lams must not alias an input");
+  if (overlap(g_roots, (int64_t)nsteps * ncells, lams, nr) || (overlap(lam_in, n, lams, nr) && !later_row(lam_in, n, lams)))
+    return set_err(HINES_ERR_STATE, "lams must not alias an input (lam_in may be a whole row after the first)");
   const double* from = lam_in;
   int32_t k = nsteps - 1;
   // the last step starts from no adjoint when lam_in is NULL: a solve of its own
