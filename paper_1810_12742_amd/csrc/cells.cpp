@@ -890,6 +890,142 @@ Status build_seq_lanes(const int32_t* parent, int64_t n, const int64_t* cell_off
   return OK;
 }
 
+bool check_cell_lanes(const CellLanes& C, const int64_t* cell_offsets, int64_t ncells, std::string& why) {
+  if ((int64_t)C.range.size() != 64 * C.nwaves || (int64_t)C.mbsrc.size() != 64 * C.nwaves) {
+    why = "per-lane tables of the wrong size";
+    return false;
+  }
+  for (int64_t w = 0; w < C.nwaves; ++w) {
+    const KCellWave& W = C.waves[w];
+    if (W.chunk_off < 0 || W.nchunk < 0 || W.chunk_off + W.nchunk > C.nchunks || W.ncell < 1 || W.ncell > 64) {
+      why = "wave " + std::to_string(w) + " record out of range";
+      return false;
+    }
+    for (int c = 0; c < 64; ++c) {
+      const int32_t cell = C.lane_cell[w * 64 + c];
+      const int64_t lo = C.base[w * 64 + c];
+      int64_t size = 0;
+      if (cell >= 0) {
+        if (cell >= ncells || lo != cell_offsets[cell]) {
+          why = "wave " + std::to_string(w) + " lane cell out of range";
+          return false;
+        }
+        size = cell_offsets[cell + 1] - lo;
+      } else if (lo != 0) {
+        why = "empty lane with a base";
+        return false;
+      }
+      // the steps outside the lane's range are its padding, and only those
+      // (the step kernel reads the zero block in their place)
+      const uint64_t rg = C.range[w * 64 + c];
+      const int64_t q0 = (int64_t)(rg & 0xffffffffu), q1 = (int64_t)(rg >> 32);
+      if (q0 > q1 || q1 > (int64_t)W.nchunk * kCellChunk || (cell < 0 && rg != 0)) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " step range out of bounds";
+        return false;
+      }
+      // stack entries per sweep
+      int m = 0;
+      uint8_t before = 0;
+      bool ok_b = true;
+      for (int64_t k = 0; k < W.nchunk && ok_b; ++k)
+        for (int e = 0; e < kCellChunk && ok_b; ++e) {
+          const int64_t g = W.chunk_off + k;
+          const uint8_t f = C.flags[cell_flag_index(g, c, e)];
+          const uint16_t ps = C.pos[cell_pos_index(g, c, e)];
+          if ((ps == kCellPadPos) != ((f & CF_PAD) != 0) || (ps != kCellPadPos && ps >= size)) {
+            why = "wave " + std::to_string(w) + " position out of range";
+            return false;
+          }
+          const int64_t q = k * kCellChunk + e;
+          if (((f & CF_PAD) != 0) == (q >= q0 && q < q1)) {
+            why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " padding outside its step range";
+            return false;
+          }
+          if ((f & CF_POP) && (before & (CF_PUSH | CF_MERGE))) {
+            why = "wave " + std::to_string(w) + " lane " + std::to_string(c) +
+                  " takes a stack entry in the step after it was left";
+            return false;
+          }
+          before = f;
+          if (f & CF_POP) ok_b = m-- >= 1;
+          if ((f & CF_MERGE) && m < 1) ok_b = false;
+          if (f & CF_PUSH) ok_b = ok_b && m++ < kCellStack;
+        }
+      if (!ok_b || m != 0) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " backward stack unbalanced";
+        return false;
+      }
+      bool ok_f = true;
+      for (int64_t k = W.nchunk - 1; k >= 0 && ok_f; --k)
+        for (int e = kCellChunk - 1; e >= 0 && ok_f; --e) {
+          const uint8_t f = C.flags[cell_flag_index(W.chunk_off + k, c, e)];
+          if ((f & (CF_PUSH | CF_MERGE)) && m < 1) ok_f = false;
+          if (f & CF_PUSH) --m;
+          if (f & CF_POP) ok_f = ok_f && m++ < kCellStack;
+        }
+      if (!ok_f || m != 0) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " forward stack unbalanced";
+        return false;
+      }
+    }
+    // mailboxes: a lane posts at most once (the root of its cut-off subtree);
+    // every post is taken exactly once, by a lane of the same cell, at a
+    // strictly later step, from the mailbox its source list names next; the
+    // forward list is the backward list reversed
+    const int64_t steps = (int64_t)W.nchunk * kCellChunk;
+    int64_t post_at[64];
+    int taken[64] = {0};
+    for (int c = 0; c < 64; ++c) {
+      post_at[c] = -1;
+      int no = 0;
+      for (int64_t q = 0; q < steps; ++q) {
+        const uint8_t f = C.flags[cell_flag_index(W.chunk_off + q / kCellChunk, c, (int)(q % kCellChunk))];
+        if (f & CF_MBOUT) {
+          ++no;
+          post_at[c] = q;
+        }
+      }
+      if (no > 1) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " posts more than once";
+        return false;
+      }
+    }
+    for (int c = 0; c < 64; ++c) {
+      const uint64_t ms = C.mbsrc[w * 64 + c];
+      const uint32_t bw = (uint32_t)ms, fw = (uint32_t)(ms >> 32);
+      int src[6], ni = 0;
+      bool ok = true;
+      for (int64_t q = 0; q < steps && ok; ++q) {
+        const uint8_t f = C.flags[cell_flag_index(W.chunk_off + q / kCellChunk, c, (int)(q % kCellChunk))];
+        if (!(f & CF_MBIN)) continue;
+        if (ni >= 5) {
+          ok = false;
+          break;
+        }
+        const int s = (int)((bw >> (6 * ni)) & 63u);
+        src[ni++] = s;
+        ok = s != c && post_at[s] >= 0 && post_at[s] < q && C.lane_cell[w * 64 + s] == C.lane_cell[w * 64 + c] &&
+             taken[s]++ == 0;
+      }
+      uint32_t bw2 = 0, fw2 = 0;
+      for (int i = 0; i < ni && ok; ++i) {
+        bw2 |= (uint32_t)src[i] << (6 * i);
+        fw2 |= (uint32_t)src[ni - 1 - i] << (6 * i);
+      }
+      if (!ok || bw != bw2 || fw != fw2) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " mailbox takes unpaired or out of order";
+        return false;
+      }
+    }
+    for (int c = 0; c < 64; ++c)
+      if ((post_at[c] >= 0) != (taken[c] == 1)) {
+        why = "wave " + std::to_string(w) + " lane " + std::to_string(c) + " mailbox post not taken";
+        return false;
+      }
+  }
+  return true;
+}
+
 bool check_seq_lanes(const SeqLanes& Q, const int32_t* parent, int64_t n, const int64_t* cell_offsets,
                      int64_t ncells, std::string& why) {
   std::vector<uint8_t> seen(n, 0);

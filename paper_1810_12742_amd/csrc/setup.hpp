@@ -181,6 +181,14 @@ Status build_cell_lanes(const int32_t* parent, int64_t n, const int64_t* cell_of
                         CellLanes& out, std::string& err, int32_t cut_percent = 80,
                         int32_t max_cuts = kCellMaxCuts);
 
+// Cell-lane tables: every wave's chunks inside the tables, every position inside
+// its lane's cell, and per lane a stack that never underflows nor leaves its
+// kCellStack LDS slots, in both sweeps, so that no kernel access leaves its
+// buffers whatever the tables hold; no entry is taken in the step after one that
+// leaves into it (the kernels read the top entry a step ahead); every mailbox
+// post is taken once, at a later step.
+bool check_cell_lanes(const CellLanes& C, const int64_t* cell_offsets, int64_t ncells, std::string& why);
+
 // Index-order cell lanes (option cell_lanes 2).  Same one-lane-per-cell
 // elimination, but a lane walks its piece of a cell in decreasing user index in
 // the backward sweep.  The parent of every compartment has a lower index (the
