@@ -1273,7 +1273,7 @@ static hipError_t follow(hipStream_t from, hipEvent_t ev, hipStream_t to) {
   return e == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e;
 }
 constexpr unsigned kDrawSlabs = 16;       // blocks per wave of k_cells_draw
-constexpr int64_t kDrawMaxWaves = 4 * 256;  // waves of a sweep with a SIMD each
+constexpr int64_t kDrawMaxWaves = 1200;  // waves of a sweep beside which the draws are faster
 
 hines_status hines_timeloop_create(const hines_plan* p, const double* diag, const double* upper, const double* c,
                                    double* v, const double* i_inj, double noise_sigma, uint32_t noise_seed,
@@ -1301,12 +1301,17 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
   bool factored = p->host.cl.built && p->host.n > 0;
   hdev::CellLoop L{};
   // Noise draws: on a second branch of the graph, one step ahead, as a current
-  // that the step adds -- as long as every wave of the sweep has a SIMD to
-  // itself (4 per CU).  Those waves wait most of the time and leave lanes of
-  // the chip idle, and draws inside them lengthen the one chain that is waited
-  // for.  20 steps of C2 cells, in the steps -> beside them: 64 cells (5 waves)
-  // 21.1 -> 9.3 ms, 12,288 (620) 24.5 -> 14.7, 22,528 (1,003) 23.9 -> 19.0; ten
-  // steps of 32,768 cells (1,263 waves), bound by memory, 14.3 -> 15.1 ms.
+  // that the step adds -- as long as few waves share a SIMD (there are 1,024).
+  // The waves of a sweep wait most of the time and leave lanes of the chip idle,
+  // and draws inside them lengthen the one chain that is waited for; a sweep of
+  // more waves is bound by memory, and the draws are 16 bytes more a step and
+  // compartment.  In the steps -> beside them, ms: 20 steps of C2 cells, 64 cells (5
+  // waves) 21.1 -> 9.3, 16,384 (822) 27.7 -> 18.9, 22,528 (1,003) 23.9 -> 20.5,
+  // 24,576 (1,075) 24.7 -> 23.4, 26,624 (1,107) 25.6 -> 24.1, 28,672 (1,199) 25.3 ->
+  // 24.7, 32,768 (1,263) 26.8 -> 28.4; 40 steps of cells of 1,000, 20,000 cells (1,153
+  // waves) 22.4 -> 21.3, 32,768 (1,302) 29.6 -> 31.2, 24,576 (1,340) 25.3 -> 25.4.  Only
+  // cells so small that the whole state stays in cache gain above the line too:
+  // 100 steps of cells of 75, 70,000 cells (2,188 waves) 13.8 -> 12.1.
   bool drawn = factored && noise && p->host.cl.nwaves <= kDrawMaxWaves;
   if (factored) {
     const int64_t S = p->t.cslots;
