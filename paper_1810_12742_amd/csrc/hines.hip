@@ -1343,11 +1343,12 @@ hines_status hines_timeloop_create(const hines_plan* p, const double* diag, cons
     L.sigma = noise_sigma;
     L.seed = noise_seed;
   }
-  // flow groups: whole stretches of steps in LDS; the plan's other groups, and
-  // every other plan, one step after the other.  The two kinds of groups share
-  // no cell, so they are two branches of the graph.
-  const bool flow = !factored && !p->host.sq.built && !p->host.cl.built && !p->flow_launches.empty();
-  const bool fork = flow && (!p->buckets.empty() || p->stream_count > 0);
+  // flow groups: whole stretches of steps in LDS; streamed groups: one step after
+  // the other with the factors kept; the plan's other groups, and every other
+  // plan, one plain step after the other.  The kinds of groups share no cell, so
+  // the flow groups and the rest are two branches of the graph.
+  const bool flow = !factored && !p->host.sq.built && !p->host.cl.built && (!p->flow_launches.empty() || p->stream_count > 0);
+  const bool fork = flow && !p->flow_launches.empty() && (!p->buckets.empty() || p->stream_count > 0);
   hipStream_t cs = nullptr, fs = nullptr;
   hipEvent_t forked = nullptr, joined = nullptr;
   hipEvent_t made[2] = {nullptr, nullptr}, used[2] = {nullptr, nullptr};  // a step's draws
