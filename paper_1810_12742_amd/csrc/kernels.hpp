@@ -691,7 +691,10 @@ __device__ __forceinline__ void flow_batch_put(FlowBatch<RHS, MT>& S, const RhsS
   // nothing is computed from a loaded value before this point: formed between
   // the loads, the right-hand sides would wait for them one by one
 #pragma unroll
-  for (int k = 0; k < kStageUnroll; ++k) __asm__ volatile("" : "+v"(S.b[k]), "+v"(S.d[k]));
+  for (int k = 0; k < kStageUnroll; ++k) {
+    __asm__ volatile("" : "+v"(S.b[k]), "+v"(S.d[k]));
+    if constexpr (sizeof(MT) == 4) __asm__ volatile("" : "+v"(S.u[k]));  // nor widened
+  }
 #pragma unroll
   for (int k = 0; k < kStageUnroll; ++k) {
     double b = S.b[k];
