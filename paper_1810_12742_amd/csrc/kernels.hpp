@@ -1143,9 +1143,9 @@ struct FlowRun {
 
 // Elements of a lane whose c (and I) stay in registers, and elements staged, or
 // handled beyond those, at a time: what 256 registers hold beside the sweeps.
-template <int RHS, bool OUT>
+template <int RHS>
 constexpr int kLoopKeep = RHS == kFlowNoise ? 24 : RHS == kFlowCVI ? 18 : 24;
-template <int RHS, bool OUT>
+template <int RHS>
 constexpr int kLoopBatch = RHS == kFlowNoise ? 4 : RHS == kFlowCVI ? 4 : 6;
 
 // OUT: the states and root traces of every step are stored (the forward run of
@@ -1154,7 +1154,7 @@ template <int RHS, bool OUT = false>
 __global__ __launch_bounds__(512) void k_flow_loop(DevTables tb, FlowRun L, const double* __restrict__ d,
                                                    const double* __restrict__ u) {
   extern __shared__ __attribute__((aligned(16))) char flow_raw[];
-  constexpr int NK = kLoopKeep<RHS, OUT>, NB = kLoopBatch<RHS, OUT>;
+  constexpr int NK = kLoopKeep<RHS>, NB = kLoopBatch<RHS>;
   const int lane = threadIdx.x & 63;
   const FlowTeam g = flow_team(tb);
   const int T = g.T, t = g.t;
@@ -2300,7 +2300,8 @@ __global__ __launch_bounds__(64) void k_solve_res(DevTables tb, const double* __
 // Streamed groups: the flow schedule for cells whose image exceeds LDS.  The
 // whole device lays d, u and the right-hand side out in step order; one wave
 // per group sweeps them there, each step's operands loaded two steps ahead in
-// register sets used in turn, f over u and y over b, then x over y; the whole
+// three register sets used in turn (four or five measured the same), f over u and
+// y over b, then x over y; the whole
 // device puts x back in user order.  What a light path pushes waits in an LDS
 // slot of its parent, where the parent's x waits for the path in the forward
 // sweep; the setup keeps two steps between a push and its taking.
@@ -2314,7 +2315,6 @@ __global__ __launch_bounds__(64) void k_solve_res(DevTables tb, const double* __
 // device, 17.  One solve of 64 cells of 20,000 takes 101 us (219 level by
 // level), of one of 7,000 44 (109), of 2,000 of 8,000 649 (698).
 // ---------------------------------------------------------------------------
-constexpr int kStreamSets = 3;  // register sets in turn: a step's loads run two steps ahead (three or four measured the same)
 enum : int { kStreamSolve = 0, kStreamKeep = 1, kStreamKept = 2 };
 
 // Thread v: sub-steps 2 p and 2 p + 1 (p = v % 4) of block v / 4, so that four
