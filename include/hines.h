@@ -143,7 +143,8 @@ typedef struct hines_plan_info {
   int32_t max_makespan;       /* flow plans: longest schedule, in chunk steps; cell-lane plans:
                                  chunks per sweep of the longest wave; resident plans: steps
                                  per sweep of the longest group                              */
-  int64_t workspace_groups;   /* groups too large for LDS, solved from a global workspace */
+  int64_t workspace_groups;   /* groups whose level-synchronous image exceeds LDS: streamed on
+                                 plans with a step schedule, else solved from a global workspace */
 } hines_plan_info;
 
 typedef struct hines_timeloop hines_timeloop; /* opaque: a captured multi-step graph */
@@ -239,9 +240,10 @@ void hines_default_options(hines_options* opt);
  *   opt: NULL for defaults.
  * Host arrays are only read during the call.  The plan's device tables are
  * allocated on the current device.  On error *out is set to NULL.
- * The per-cell tables of cell-lane plans are built by host threads, as many
- * as the environment variable HINES_SETUP_THREADS says, else one per host
- * core (at most 16); the tables do not depend on the count. */
+ * The per-cell tables of cell-lane plans and the step schedules of the groups
+ * are built by host threads, as many as the environment variable
+ * HINES_SETUP_THREADS says, else one per host core (at most 16); the tables do
+ * not depend on the count. */
 hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch_offsets,
                          int64_t nbranches, const int64_t* cell_offsets, int32_t ncells,
                          const hines_options* opt, hines_plan** out);
@@ -253,6 +255,9 @@ hines_status hines_setup(const int32_t* parent, int64_t n, const int64_t* branch
  *   ncells must equal the plan's cell count.
  * Infinite and NaN values of a cell reach no other cell on plans with a step
  * schedule (hines_plan_info.kernel == 1), in this and in every other call.
+ * Calls on one plan must not overlap (on several streams or from several threads)
+ * if the plan keeps a scratch or streams of its own: cell lanes, resident plans,
+ * and plans with workspace_groups.
  * Inputs are not modified.  Asynchronous on stream. */
 hines_status hines_solve(const hines_plan* plan, const double* diag, const double* upper,
                          const double* rhs, double* x, int32_t ncells, void* stream);
@@ -339,7 +344,7 @@ hines_status hines_timestep_assembled(const hines_plan* plan, const double* g, c
  * hines_timeloop_launch replays the same steps on `stream`; the arrays are
  * bound at creation and must stay valid.  The plan must outlive the loop.
  * On a cell-lane plan (option cell_lanes) the loop allocates, at creation,
- * up to 40 bytes per walk slot (cell compartments plus padding) and each
+ * up to 50 bytes per walk slot (cell compartments plus padding) and each
  * launch factors A once (f = u / d' and 1 / d' per compartment), moves c, the
  * current and v into the lanes' walk order, runs the nsteps right-hand-side
  * sweeps there and writes v back in user order at the end: the result equals
@@ -347,8 +352,9 @@ hines_status hines_timestep_assembled(const hines_plan* plan, const double* g, c
  * loop captures nsteps plain hines_timestep launches instead (same results);
  * hines_timeloop_destroy frees what was allocated.  On a plan whose groups
  * have a step schedule (hines_plan_info.kernel == 1) the loop runs up to 256
- * steps of those groups in one launch, with their factors and state in LDS;
- * the result again equals single steps bit for bit.  On a plan with no compartments the
+ * steps of those groups in one launch, with their factors and state in LDS
+ * (groups that exceed LDS keep them in the plan's scratch, a few launches a
+ * step); the result again equals single steps bit for bit.  On a plan with no compartments the
  * loop holds no graph and its launch does nothing (the arrays may be NULL). */
 hines_status hines_timeloop_create(const hines_plan* plan, const double* diag, const double* upper,
                                    const double* c, double* v, const double* i_inj, double noise_sigma,

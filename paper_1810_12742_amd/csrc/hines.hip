@@ -434,7 +434,7 @@ hipError_t launch_solve(const hines_plan* p, const RhsSpec& rs, const double* d,
 // matrix, and one FP64 elimination of it gives that.  FP64 and FP32 vector
 // arithmetic issue at the same rate here, so every correction sweep costs as
 // much as the whole FP64 solve, in a kernel with a barrier per level on top
-// (4,096 C2 cells, 3 sweeps: 4.40 ms against 0.144).  So groups with a step
+// (4,096 C2 cells, 3 sweeps: 4.40 ms against 0.141).  So groups with a step
 // schedule are solved by the flow kernel from the FP32 storage whenever a
 // correction was asked for; sweep 0 alone is the FP32 result and stays FP32.
 hipError_t launch_mixed(const hines_plan* p, const float* d32, const float* u32, const double* b, double* x,

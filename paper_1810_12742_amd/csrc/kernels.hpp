@@ -1035,8 +1035,9 @@ __device__ __forceinline__ FlowTeam flow_team(const DevTables& tb) {
 // and store are memory latency (6,700 and 1,600 cycles with four waves a group,
 // 15,000 and 5,000 with one beside others).  The two register sets of the
 // sweeps, the staging batches in flight together, the bins and the helping
-// waves took 64 C2 cells from 207 to 24 us (11 launches before, one now), 4,099
-// from 424 to 160 us, a step of 8,192 cells of 1,000 from 217 to 187 us.
+// waves took 64 C2 cells from 207 to 24.5 us (11 launches before, one now), 4,099
+// from 424 to 161 us, a step of 8,192 cells of 1,000 from 217 to 188 us (24.0, 160
+// and 188 before the cells of a group were kept apart where a path begins).
 template <int RHS, typename MT = double>
 __global__ __launch_bounds__(512) void k_solve_flow(DevTables tb, RhsSpec rs, const MT* __restrict__ d,
                                                     const MT* __restrict__ u, double* x) {
@@ -2301,8 +2302,9 @@ __global__ __launch_bounds__(64) void k_solve_res(DevTables tb, const double* __
 // whole device lays d, u and the right-hand side out in step order; one wave
 // per group sweeps them there, each step's operands loaded two steps ahead in
 // three register sets used in turn (four or five measured the same), f over u and
-// y over b, then x over y; the whole
-// device puts x back in user order.  What a light path pushes waits in an LDS
+// y over b, then x over y; the whole device puts x back in user order.  A path that
+// begins takes no carry and a root starts from zero, as in the flow kernel, so a
+// cell's values reach no other.  What a light path pushes waits in an LDS
 // slot of its parent, where the parent's x waits for the path in the forward
 // sweep; the setup keeps two steps between a push and its taking.
 //
@@ -2311,9 +2313,9 @@ __global__ __launch_bounds__(64) void k_solve_res(DevTables tb, const double* __
 // itself, in one pass, was bound by the memory operations a wave can have in
 // flight (63): 143 us for 68 cells of 20,000, 163 with the gather turned
 // through LDS; the level-synchronous kernel took 273.  In a loop the sweep takes
-// 59 us a step of those cells and its right-hand sides, drawn on the whole
-// device, 17.  One solve of 64 cells of 20,000 takes 101 us (219 level by
-// level), of one of 7,000 44 (109), of 2,000 of 8,000 649 (698).
+// 60 us a step of those cells and its right-hand sides, drawn on the whole
+// device, 17.  One solve of 64 cells of 20,000 takes 105 us (224 level by
+// level), of one of 7,000 42 (98), of 2,000 of 8,000 639 (694).
 // ---------------------------------------------------------------------------
 enum : int { kStreamSolve = 0, kStreamKeep = 1, kStreamKept = 2 };
 
