@@ -83,5 +83,10 @@ class _SomaTraces(torch.autograd.Function):
 
 def soma_traces(plan, a, c, I, steps: int, checkpoint_every: int = 10):
     """Soma voltages [steps, ncells] of the simulation, differentiable w.r.t.
-    a (edge conductance stored at the child; roots ignored), c and I."""
-    return _SomaTraces.apply(a, c, I, plan, int(steps), int(checkpoint_every))
+    a (edge conductance stored at the child; roots ignored), c and I.  The
+    backward pass holds the states of ``checkpoint_every`` steps (its sign is
+    ignored) and the adjoints of up to ``ADJOINT_ROWS`` of them at a time."""
+    every = abs(int(checkpoint_every))
+    if every == 0 and steps > 0:
+        raise ValueError("checkpoint_every must not be 0")
+    return _SomaTraces.apply(a, c, I, plan, int(steps), max(every, 1))
